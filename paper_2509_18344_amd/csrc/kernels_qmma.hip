@@ -54,7 +54,7 @@ __global__ __launch_bounds__(256) void k_xsum(const uint16_t* __restrict__ x, in
   if (k < K) v = piece_sum(*reinterpret_cast<const u32x4_t*>(x + static_cast<size_t>(m) * K + k), 0.f);
 #pragma unroll
   for (int d = 1; d < LANES; d *= 2) v += __shfl_xor(v, d);
-  if (k < K && lane % LANES == 0) out[static_cast<size_t>(m) * (K / GROUP) + k / GROUP] = v;
+  if (k < K && lane % LANES == 0) out[static_cast<size_t>(k / GROUP) * M + m] = v;
 }
 
 hipError_t launch_xsum(const uint16_t* x, int M, int K, int group, float* out, hipStream_t st) {

@@ -110,15 +110,15 @@ struct MmaBody {
     uint32_t sz[NB];       // byte offset of the lane's column in a row of scales
     uint32_t x;            // byte offset of the lane's first copied piece in chunk 0
     int a;                 // LDS piece index of the lane's A row in row block 0, piece 0
-    uint32_t xs;           // byte offset of x-sum (row lane % 32, group lane / 32)
+    uint32_t xs;           // byte offset of x-sum (group lane / 32, row lane % 32)
   };
 
   static __device__ __forceinline__ int slot(int row, int piece) { return row * 16 + (piece ^ (row & 15)); }
 
   // Chunk kb's weights, scales and zero-points, and the sums of x of groups fg (lanes
-  // 0-31) and fg + 1 (lanes 32-63) for each row block; ng = K / GROUP groups per row.
-  static __device__ __forceinline__ void load_w(W& r, const QBuffers& bu, const Lanes& ln, int N, int kb, int fg,
-                                                int ng) {
+  // 0-31) and fg + 1 (lanes 32-63) for each row block.
+  static __device__ __forceinline__ void load_w(W& r, const QBuffers& bu, const Lanes& ln, int M, int N, int kb,
+                                                int fg) {
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
@@ -133,11 +133,10 @@ struct MmaBody {
         r.z[gi][nb] = __builtin_amdgcn_raw_buffer_load_b16(bu.z, ln.sz[nb], soff, 0);
       }
     }
+    const uint32_t xo = ln.xs + static_cast<uint32_t>(fg) * M * 4;
 #pragma unroll
     for (int i = 0; i < MB; ++i)
-      r.xs[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
-                                              bu.xs, ln.xs + static_cast<uint32_t>(32 * i) * ng * 4,
-                                              static_cast<uint32_t>(fg) * 4, 0));
+      r.xs[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(bu.xs, xo + 128 * i, 0, 0));
   }
 
   // Copy chunk kb of x (all ROWS rows; rows past M read zeros) straight from memory
@@ -303,7 +302,6 @@ __attribute__((amdgpu_waves_per_eu(WAVES == 8 || XB <= 2 ? 2 : 1))) void k_qmma(
   const int nchunks = team == 0 ? h0 : nwg - h0;
   const int nsteps = h0;
   const int last = nchunks - 1;
-  const int ngroups = a.K / GROUP;
   const QBuffers bu(a, BITS, GROUP);
   // Block of the team's chunk c, held inside the workgroup's range: loads past the
   // team's last chunk repeat it (L2 hits, never used).
@@ -333,7 +331,7 @@ __attribute__((amdgpu_waves_per_eu(WAVES == 8 || XB <= 2 ? 2 : 1))) void k_qmma(
     const int row = 4 * tw + (lane >> 4), pc = (lane & 15) ^ (row & 15);
     ln.x = (static_cast<uint32_t>(row) * a.K + pc * 8) * 2;
     ln.a = r32 * 16;
-    ln.xs = (static_cast<uint32_t>(r32) * ngroups + hi) * 4;
+    ln.xs = (static_cast<uint32_t>(hi) * a.M + r32) * 4;
   }
 
   f32x16_t tot[MB][NB];
@@ -368,7 +366,7 @@ __attribute__((amdgpu_waves_per_eu(WAVES == 8 || XB <= 2 ? 2 : 1))) void k_qmma(
     static_for<XB - 1>([&](auto u) __attribute__((always_inline)) {
       constexpr int U = decltype(u)::value;
       Body::stage(ring(u), bu, ln, a.K, blk(U), tw);
-      Body::load_w(w[U], bu, ln, a.N, blk(U), pair_first(U, U & 1), ngroups);
+      Body::load_w(w[U], bu, ln, a.M, a.N, blk(U), pair_first(U, U & 1));
     });
     chunk_barrier(ring(std::integral_constant<int, 0>{}), touch);
 
@@ -382,7 +380,7 @@ __attribute__((amdgpu_waves_per_eu(WAVES == 8 || XB <= 2 ? 2 : 1))) void k_qmma(
       constexpr int U = decltype(u)::value;
       const int cn = cc + XB - 1;
       Body::stage(ring(std::integral_constant<int, (U + XB - 1) % XB>{}), bu, ln, a.K, blk(cn), tw);
-      Body::load_w(w[(U + PF - 1) % PF], bu, ln, a.N, blk(cn), pair_first(cn, (U + PF - 1) & 1), ngroups);
+      Body::load_w(w[(U + PF - 1) % PF], bu, ln, a.M, a.N, blk(cn), pair_first(cn, (U + PF - 1) & 1));
       if (TEAMS == 1 || cc < nchunks) {
         float cneg[GPC][NB];
         Body::compute(w[U], ring(u), lane, ln, tot, cneg);
