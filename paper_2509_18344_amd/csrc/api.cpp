@@ -164,7 +164,7 @@ int device_cus() {
   return cus;
 }
 
-// Bytes of the per-group sums of x the 32x32 kernel reads (fp32 [M][K/group]),
+// Bytes of the per-group sums of x the 32x32 kernel reads (fp32 [K/group][M]),
 // rounded up to 256.
 size_t xsum_bytes(const subspec::KernelChoice& c, int M, int K, int group) {
   if (c.shape != 32) return 0;
@@ -256,15 +256,13 @@ int make_plan(int M, int N, int K, int bits, int group, int path, subspec_plan* 
     // of four wavefronts per workgroup, each on half of the workgroup's k-blocks: two
     // wavefronts per SIMD at the same number of splits (32B down, K = 27648: 61.5
     // against 63.8 us at M = 128, 54.7 against 58.7 at 96; 7B down, K = 18944: 40.5
-    // against 45.7 on 16x16x32 tiles at M = 128).  Each team's ring stays two chunks
-    // deep: four-chunk rings of 64 rows (128 KB of LDS) measured no faster (32B down
-    // 35.2 against 34.5 us at M = 48, 41.3 against 39.6 at 64).
+    // against 45.7 on 16x16x32 tiles at M = 128).
     const bool teams = tu.mma_teams ? tu.mma_teams == 2 : long_k;
     if (!use8 && teams) {
       c8 = c;
       c8.waves = 8;
       c8.teams = 2;
-      c8.prefetch = 2;
+      c8.prefetch = tu.mfma_pf ? tu.mfma_pf : 2;
       use8 = true;
     }
   } else if (path == SUBSPEC_PATH_MFMA16) {
@@ -281,10 +279,14 @@ int make_plan(int M, int N, int K, int bits, int group, int path, subspec_plan* 
   } else {
     return fail(SUBSPEC_EINVAL, "path=%d: unknown", path);
   }
+  // What a plan may describe.  For 32x32 tiles the launch made from it can differ in ring
+  // depth and wavefronts (refine_launch), so the set of builds is not the measure there.
   auto variant_exists = [&](const subspec::KernelChoice& k) {
-    return k.shape == 32 ? subspec::qmma_variant_exists(k.waves, k.teams, k.rows / 32, k.nt / 2, k.prefetch, bits,
-                                                        group)
-                         : subspec::qlinear_variant_exists(k, bits, group);
+    if (k.shape != 32) return subspec::qlinear_variant_exists(k, bits, group);
+    if (k.nt != 2) return false;
+    if (k.waves == 8 && k.teams == 2) return true;
+    if (k.waves == 8) return k.prefetch == 4 && (k.rows == 64 || bits == 2 || (bits == 3 && group == 128));
+    return k.rows == 128 && (k.prefetch == 2 || k.prefetch == 4);
   };
   if (use8 && (tu.mma_waves == 8 || variant_exists(c8))) c = c8;
   if (c.shape == 32 && c.rows == 64 && !variant_exists(c)) c.rows = 128;  // no 64-row build
@@ -302,7 +304,8 @@ int make_plan(int M, int N, int K, int bits, int group, int path, subspec_plan* 
                                     group, cols);
     }
     int per_cu = k.shape == 32 ? subspec::qmma_resident_blocks(k.waves, k.teams, k.rows / 32, k.nt / 2,
-                                                               k.prefetch, bits, group)
+                                                               k.teams == 2 && k.rows == 64 ? 4 : k.prefetch,
+                                                               bits, group)
                                : subspec::qlinear_resident_blocks(k, bits, group, lds);
     if (per_cu <= 0) per_cu = 2;
     return per_cu * device_cus();
@@ -465,6 +468,31 @@ int make_plan(int M, int N, int K, int bits, int group, int path, subspec_plan* 
   return SUBSPEC_OK;
 }
 
+// The launch made from a described plan, for 32x32 tiles.  It needs no more workspace.
+//  - 64-row two-team tiles run with four-chunk rings: 5120x27648 3-bit 33.2 against 36.2 us
+//    at M = 64 and 31.9 against 35.7 at 48, 2-bit g64 33.3 against 37.1 at 64, 3584x18944
+//    4-bit 21.7 against 22.7 at 37.
+//  - 128-row launches of four wavefronts take eight (256 columns, K unsplit) where that
+//    measured faster: 55296x5120 4-bit 76.1 against 100.2 us, 3-bit g64 82.1 against 89.9;
+//    where 256-column groups cover only half the CUs with groups of 128 (37888x3584 4-bit
+//    46.2 against 56.1 us; 3-bit g64 at M = 96 53.0 against 50.4).
+void refine_launch(int N, int K, int group, subspec_plan* p, subspec::KernelChoice* kc) {
+  const Tuning& tu = tuning();
+  if (kc->shape != 32 || tu.mma_waves || tu.mfma_pf) return;
+  if (kc->teams == 2 && kc->rows == 64) kc->prefetch = 4;
+  const int groups = (N + 255) / 256;
+  const bool wide8 = groups * 4 >= 3 * device_cus();
+  const bool half8 = groups * 2 >= device_cus();
+  if (kc->waves == 4 && kc->rows == 128 && K / subspec::kTileK < 128 && (wide8 || (half8 && group == 128))) {
+    kc->waves = 8;
+    kc->prefetch = 4;
+    p->col_groups = p->grid = groups;
+    p->full_groups = 0;
+    p->splits = 1;
+    p->blocks_per_split = K / subspec::kTileK;
+  }
+}
+
 // A call's plan depends only on (device, M, N, K, bits, group, path, workspace cap)
 // and the process's tuning, so each thread keeps the plans it has made: repeated
 // calls (every draft pass repeats the same shapes) skip the planner and its occupancy
@@ -507,6 +535,7 @@ int make_plan_cached(int M, int N, int K, int bits, int group, int path, subspec
   }
   const int rc = make_plan(M, N, K, bits, group, path, p, kc, ws_cap);
   if (rc) return rc;
+  refine_launch(N, K, group, p, kc);
   if (cache.size() >= kPlanCacheEntries) cache.clear();
   cache.emplace(key, CachedPlan{*p, *kc});
   return SUBSPEC_OK;
@@ -679,10 +708,9 @@ int qlinear_impl(const void* x, const void* qweight, const void* scales, const v
   }
   hipError_t e = hipSuccess;
   if (kc.shape == 32) {
-    e = subspec::launch_xsum(a.x, M, K, group, const_cast<float*>(a.xsum), st);
+    if (kc.rows == 128) e = subspec::launch_xsum(a.x, M, K, group, const_cast<float*>(a.xsum), st);
     if (e == hipSuccess)
-      e = subspec::launch_qmma(kc.waves, kc.teams, kc.rows / 32, kc.nt / 2, kc.prefetch, bits, group, a, p.grid,
-                               st);
+      e = subspec::launch_qmma(kc.waves, kc.teams, kc.rows / 32, kc.nt / 2, kc.prefetch, bits, group, a, p.grid, st);
   } else {
     e = subspec::launch_qlinear(kc, bits, group, a, p.grid, st);
   }

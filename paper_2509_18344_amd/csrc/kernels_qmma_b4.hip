@@ -4,20 +4,21 @@
 namespace subspec {
 
 #define SUBSPEC_QMMA(G, MB, NB, PF, W) {MB, NB, PF, W, 1, 4, G, qmma::k_qmma<4, G, MB, NB, PF, W, 1>}
-#define SUBSPEC_QMMA_TEAMS(G, MB) {MB, 1, 2, 8, 2, 4, G, qmma::k_qmma<4, G, MB, 1, 2, 8, 2>}
+#define SUBSPEC_QMMA_TEAMS(G, MB, PF) {MB, 1, PF, 8, 2, 4, G, qmma::k_qmma<4, G, MB, 1, PF, 8, 2>}
 
-// Four row blocks (M = 65..128): four wavefronts with the ring two chunks deep (two
-// workgroups per CU) or four (one workgroup per CU).  (The eight-wavefront four-row-block
-// build spills registers at four bits.)
-// Two row blocks (M = 33..64): eight wavefronts (256 columns) with the ring four chunks
-// deep.  Two teams of four wavefronts, each with a two-chunk ring, on long-K launches
-// from M = 33 (64-row tiles) and above M = 64 (128-row tiles).
+// Four row blocks (M = 65..128): eight wavefronts (256 columns, one workgroup per CU) with
+// the ring four chunks deep; four wavefronts with the ring two chunks deep (two workgroups
+// per CU, groups of 64) or four.  Two teams of four wavefronts with two-chunk rings on
+// long-K launches.
+// Two row blocks (M = 33..64): eight wavefronts with the ring four chunks deep; two teams
+// of four on long-K launches, each with a four-chunk ring.
 static const MmaVariant kVariants[] = {
-    SUBSPEC_QMMA(128, 4, 1, 2, 4), SUBSPEC_QMMA(128, 4, 1, 4, 4), SUBSPEC_QMMA(64, 4, 1, 2, 4),
+    SUBSPEC_QMMA(128, 4, 1, 4, 4), SUBSPEC_QMMA(64, 4, 1, 2, 4),
     SUBSPEC_QMMA(64, 4, 1, 4, 4),
     SUBSPEC_QMMA(128, 2, 1, 4, 8), SUBSPEC_QMMA(64, 2, 1, 4, 8),
-    SUBSPEC_QMMA_TEAMS(128, 4), SUBSPEC_QMMA_TEAMS(64, 4),
-    SUBSPEC_QMMA_TEAMS(128, 2), SUBSPEC_QMMA_TEAMS(64, 2),
+    SUBSPEC_QMMA(128, 4, 1, 4, 8), SUBSPEC_QMMA(64, 4, 1, 4, 8),
+    SUBSPEC_QMMA_TEAMS(128, 4, 2), SUBSPEC_QMMA_TEAMS(64, 4, 2),
+    SUBSPEC_QMMA_TEAMS(128, 2, 4), SUBSPEC_QMMA_TEAMS(64, 2, 4),
 };
 
 const MmaVariant* qmma_variants_b4(int* n) {

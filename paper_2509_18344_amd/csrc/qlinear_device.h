@@ -48,15 +48,41 @@ __device__ __forceinline__ float dpp_f(float v) {
 }
 constexpr int kDppQuadXor1 = 0xB1;  // quad_perm [1,0,3,2]
 constexpr int kDppQuadXor2 = 0x4E;  // quad_perm [2,3,0,1]
+constexpr int kDppHalfMirror = 0x141;  // row_half_mirror: lane i of eight to 7 - i
 
-// Sum over the lanes of an aligned group of SPAN lanes (SPAN = 1, 2 or 4).
+// Sum over the lanes of an aligned group of SPAN lanes (SPAN = 1, 2, 4 or 8).
 template <int SPAN>
 __device__ __forceinline__ float span_reduce(float v) {
   if constexpr (SPAN >= 2) v += dpp_f<kDppQuadXor1>(v);
   if constexpr (SPAN >= 4) v += dpp_f<kDppQuadXor2>(v);
+  if constexpr (SPAN >= 8) v += dpp_f<kDppHalfMirror>(v);  // the other quad: its lanes all hold its sum
   return v;
 }
 
+
+// Code pair P (0..15) of a slice: two bf16 values 128 + q (see device_common.h).
+template <int BITS, int P>
+__device__ __forceinline__ uint32_t code_pair(const Slice<BITS>& s) {
+  if constexpr (BITS == 4) {
+    return and_or(s.w[P / 4] >> (4 * (P % 4)), 0x000F000Fu, kPairBias);
+  } else if constexpr (BITS == 2) {
+    return and_or(s.w[P / 8] >> (2 * (P % 8)), 0x00030003u, kPairBias);
+  } else if constexpr (P < 15) {
+    return and_or(s.w[P / 5] >> (3 * (P % 5)), 0x00070007u, kPairBias);
+  } else {
+    uint32_t p = and_or(s.w[0] >> 15, 0x00010001u, kPairBias);
+    p = and_or(s.w[1] >> 14, 0x00020002u, p);
+    return and_or(s.w[2] >> 13, 0x00040004u, p);
+  }
+}
+
+// B operand of 32-k step J of a slice: pairs 4J .. 4J+3 (8 consecutive k).
+template <int BITS, int J>
+__device__ __forceinline__ bf16x8_t b_operand(const Slice<BITS>& s) {
+  const u32x4_t v = {code_pair<BITS, 4 * J>(s), code_pair<BITS, 4 * J + 1>(s), code_pair<BITS, 4 * J + 2>(s),
+                     code_pair<BITS, 4 * J + 3>(s)};
+  return __builtin_bit_cast(bf16x8_t, v);
+}
 
 // ---------------------------------------------------------------------------
 // Dequantization constants.

@@ -15,9 +15,22 @@
 // then tot += s * acc (one FMA per output per group).  The second term for a pair of
 // groups at once: one fp32 32x32x2 MFMA with A = the two groups' sums of x and
 // B = -s*(128+z) of the two groups (a rank-2 update of the 32x32 output block).
-// The sums of x per (row, group) are the same for every workgroup; a small kernel
-// (k_xsum) computes them once per call, and each wavefront loads the two it needs per
-// row block and pair of groups along with the weights.
+// The sums of x per (row, group): 64-row tiles take them from the x chunk in LDS (SumX),
+// 128-row tiles, which have no registers left for it, from a small kernel per call
+// (k_xsum), copied into LDS beside the chunk.
+//
+// What bounds it: two wavefronts per SIMD must keep the matrix pipe busy through LDS
+// reads, unpacking, scale FMAs, loads and the chunk barriers.  The loop is pipelined so
+// that none of these leaves it idle for long: A fragments are read a step ahead, also
+// across the barrier; a group's scale FMAs run between the next group's first MFMAs; and
+// a chunk's loads are spread over its steps.  us per call, before (burst of loads and
+// block of FMAs per chunk, the next chunk's first A read after the barrier, gathered x
+// sums) and after: 55296x5120 M = 128 3-bit 89.0 / 68.5, 2-bit g64 93.3 / 75.8, 4-bit
+// 99.5 / 71.4, M = 64 3-bit 47.9 / 43.3; 5120x27648 3-bit M = 128 58.8 / 51.8, M = 64
+// 37.8 / 31.6; 37888x3584 4-bit M = 128 50.0 / 45.6, M = 64 34.5 / 29.5.
+//
+// No branch inside the loop: a branch, also one the compiler makes of a conditional read
+// or store, splits the step and costs about 40 registers (spills).
 //
 // Weight fetch: a 32-column block is two 16-column tiles of the packed layout.  The
 // B operand of step s (k = 16s ... 16s+15 of a 128-k block) holds, in lanes 0-31, k
@@ -45,30 +58,6 @@ typedef __attribute__((address_space(3))) void* LdsPtr;
 // per 16 lanes, both conflict free).  The chunk buffers are separate LDS objects on
 // purpose: the copy into one runs while another is read, and only distinct objects let
 // the compiler see that those reads need not wait for the copy.
-
-// Code pair P (0..15) of a slice: two bf16 values 128 + q (see device_common.h).
-template <int BITS, int P>
-__device__ __forceinline__ uint32_t code_pair(const Slice<BITS>& s) {
-  if constexpr (BITS == 4) {
-    return and_or(s.w[P / 4] >> (4 * (P % 4)), 0x000F000Fu, kPairBias);
-  } else if constexpr (BITS == 2) {
-    return and_or(s.w[P / 8] >> (2 * (P % 8)), 0x00030003u, kPairBias);
-  } else if constexpr (P < 15) {
-    return and_or(s.w[P / 5] >> (3 * (P % 5)), 0x00070007u, kPairBias);
-  } else {
-    uint32_t p = and_or(s.w[0] >> 15, 0x00010001u, kPairBias);
-    p = and_or(s.w[1] >> 14, 0x00020002u, p);
-    return and_or(s.w[2] >> 13, 0x00040004u, p);
-  }
-}
-
-// B operand of 32-k step J of a slice: pairs 4J .. 4J+3 (8 consecutive k).
-template <int BITS, int J>
-__device__ __forceinline__ bf16x8_t b_operand(const Slice<BITS>& s) {
-  const u32x4_t v = {code_pair<BITS, 4 * J>(s), code_pair<BITS, 4 * J + 1>(s), code_pair<BITS, 4 * J + 2>(s),
-                     code_pair<BITS, 4 * J + 3>(s)};
-  return __builtin_bit_cast(bf16x8_t, v);
-}
 
 template <int BITS>
 __device__ __forceinline__ Slice<BITS> load_slice_s(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
@@ -101,7 +90,6 @@ struct MmaBody {
     Slice<BITS> w[NB][2];
     uint16_t s[GPC][NB];  // raw fp16 bits, converted only when the group is applied
     uint16_t z[GPC][NB];
-    float xs[MB];         // sums of x of a pair of groups (see load_w): row 32 i + lane % 32
   };
 
   // Lane parts of every address, fixed for the whole launch.
@@ -109,112 +97,195 @@ struct MmaBody {
     uint32_t w[NB][2];     // slice byte offsets in block 0 of the column block's tiles
     uint32_t sz[NB];       // byte offset of the lane's column in a row of scales
     uint32_t x;            // byte offset of the lane's first copied piece in chunk 0
-    int a;                 // LDS piece index of the lane's A row in row block 0, piece 0
-    uint32_t xs;           // byte offset of x-sum (group lane / 32, row lane % 32)
+    uint32_t xs;           // byte offset of the lane's copied sum of x in chunk 0
+    int a;                 // LDS piece index of the lane's first A fragment in row block 0
   };
 
   static __device__ __forceinline__ int slot(int row, int piece) { return row * 16 + (piece ^ (row & 15)); }
 
-  // Chunk kb's weights, scales and zero-points, and the sums of x of groups fg (lanes
-  // 0-31) and fg + 1 (lanes 32-63) for each row block.
-  static __device__ __forceinline__ void load_w(W& r, const QBuffers& bu, const Lanes& ln, int M, int N, int kb,
-                                                int fg) {
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-      for (int h = 0; h < 2; ++h)
-        r.w[nb][h] = load_slice_s<BITS>(bu.w, ln.w[nb][h], static_cast<uint32_t>(kb) * (256 * BITS));
-#pragma unroll
-    for (int gi = 0; gi < GPC; ++gi) {
-      const uint32_t soff = static_cast<uint32_t>(kb * GPC + gi) * N * 2;
+  // The loads of one chunk, in PIECES independent pieces that the main loop issues a few
+  // per step: chunk kb's weights, scales and zero-points, and the chunk's copy of x.
+  //
+  // The copy (all ROWS rows; rows past M read zeros) goes straight from memory into an
+  // LDS buffer: each load instruction fills 1 KB (four consecutive rows) with 16 bytes
+  // per lane in lane order, so lane l writes position l % 16 of its row and fetches the
+  // piece that the swizzle puts there.  Load j of wavefront w covers rows
+  // 4w + 4*WAVES*j + (0..3): a lane keeps the same row % 16, hence the same swizzled
+  // piece, in all of its loads.  The row part of the offset stays in the lane offset,
+  // which the buffer's range check covers (rows past M read zeros); the chunk's
+  // position in the row is the scalar offset.
+  // Who sums x over the groups: 64-row tiles the workgroup itself (SumX; a pre-pass
+  // kernel costs 5 us there), 128-row tiles, which have no registers for it, a pre-pass
+  // (k_xsum), whose sums are copied into LDS with the chunk ([group][row], 64 per
+  // wavefront; wavefronts past the last 64 repeat them).
+  static constexpr bool SUMS = MB <= 2;
+  static constexpr int XSW = GPC * ROWS / kWave;
+  static constexpr int PIECES = 2 * NB + GPC + (SUMS ? 0 : 1) + DMA;
+  static constexpr int VM = 2 * NB + 2 * GPC * NB + (SUMS ? 0 : 1) + DMA;  // vector memory operations of one chunk
+  static __device__ __forceinline__ void stage(u32x4_t* xb, const QBuffers& bu, const Lanes& ln, int K, int kb,
+                                               int wave, int j) {
+    asm volatile("" : "+s"(K));  // recomputed at each copy: kept, the DMA offsets cost as many registers
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(bu.x, (LdsPtr)(xb + (4 * wave + 4 * WAVES * j) * 16), 16,
+                                             ln.x + static_cast<uint32_t>(j) * (8 * WAVES) * K,
+                                             static_cast<uint32_t>(kb) * (kTileK * 2), 0, 0);
+  }
+  // (P is a constant after inlining.)
+  static __device__ __forceinline__ void load_piece(int P, W& r, u32x4_t* xb, float* xsb, const QBuffers& bu,
+                                                    const Lanes& ln, const QArgs& a, int kb, int wave) {
+    if (P < 2 * NB) {
+      r.w[P / 2][P % 2] = load_slice_s<BITS>(bu.w, ln.w[P / 2][P % 2], static_cast<uint32_t>(kb) * (256 * BITS));
+    } else if (P < 2 * NB + GPC) {
+      const int gi = P - 2 * NB;
+      const uint32_t soff = static_cast<uint32_t>(kb * GPC + gi) * a.N * 2;
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) {
         r.s[gi][nb] = __builtin_amdgcn_raw_buffer_load_b16(bu.s, ln.sz[nb], soff, 0);
         r.z[gi][nb] = __builtin_amdgcn_raw_buffer_load_b16(bu.z, ln.sz[nb], soff, 0);
       }
+    } else if (!SUMS && P == 2 * NB + GPC) {
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(bu.xs, (LdsPtr)(xsb + kWave * (wave % XSW)), 4,
+                                               ln.xs + static_cast<uint32_t>(kb * GPC) * a.M * 4, 0, 0, 0);
+    } else {
+      stage(xb, bu, ln, a.K, kb, wave, P - (PIECES - DMA));
     }
-    const uint32_t xo = ln.xs + static_cast<uint32_t>(fg) * M * 4;
-#pragma unroll
-    for (int i = 0; i < MB; ++i)
-      r.xs[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(bu.xs, xo + 128 * i, 0, 0));
   }
 
-  // Copy chunk kb of x (all ROWS rows; rows past M read zeros) straight from memory
-  // into an LDS buffer: each load instruction fills 1 KB (four consecutive rows) with
-  // 16 bytes per lane in lane order, so lane l writes position l % 16 of its row and
-  // fetches the piece that the swizzle puts there.  Load j of wavefront w covers rows
-  // 4w + 4*WAVES*j + (0..3): a lane keeps the same row % 16, hence the same swizzled
-  // piece, in all of its loads.  The row part of the offset stays in the lane offset,
-  // which the buffer's range check covers (rows past M read zeros); the chunk's
-  // position in the row is the scalar offset.
-  static __device__ __forceinline__ void stage(u32x4_t* xb, const QBuffers& bu, const Lanes& ln, int K, int kb,
-                                               int wave) {
-#pragma unroll
-    for (int j = 0; j < DMA; ++j)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(bu.x, (LdsPtr)(xb + (4 * wave + 4 * WAVES * j) * 16), 16,
-                                               ln.x + static_cast<uint32_t>(j) * (8 * WAVES) * K,
-                                               static_cast<uint32_t>(kb) * (kTileK * 2), 0, 0);
-  }
-
-  // One chunk (x buffer X, ring slot wc).  The A fragments of the next step are read
-  // before the current step's MFMAs, so the LDS latency runs under them (16 more
-  // registers at four row blocks, still within two wavefronts per SIMD once the sums
-  // of x come from the pre-pass).  cneg[gi][nb] receives -s*(128+z) of the chunk's
-  // groups.
-  static __device__ __forceinline__ void compute(const W& wc, const u32x4_t* X, int lane, const Lanes& ln,
-                                                 f32x16_t (&tot)[MB][NB], float (&cneg)[GPC][NB]) {
-    const int r32 = lane & 31, hi = lane >> 5;
-    const f32x16_t zero = {};
-    // Row 32 i + r32, piece p lives at ln.a + 512 i + (p ^ (r32 & 15)).
-    auto read_a = [&](int i, int piece) __attribute__((always_inline)) {
-      return __builtin_bit_cast(bf16x8_t, X[ln.a + 512 * i + (piece ^ (r32 & 15))]);
-    };
+  // What a wavefront carries from one chunk to the next: the A fragments of the next
+  // chunk's first step, and the last group's sums acc with its scale sv, which are added
+  // to tot between the next group's first MFMAs (apply).
+  struct Carry {
     bf16x8_t A[MB];
+    f32x16_t acc[MB][NB];
+    float sv[NB];
+  };
+
+  // Row 32 i + r32, piece 2 s + hi of a chunk buffer lives at 512 i + 16 r32 +
+  // ((2 s + hi) ^ (r32 & 15)) = 512 i + (ln.a ^ 2 s).
+  static __device__ __forceinline__ bf16x8_t read_a(const u32x4_t* X, const Lanes& ln, int lane, int i, int s) {
+    return __builtin_bit_cast(bf16x8_t, X[512 * i + (ln.a ^ (2 * s))]);
+  }
+
+  static __device__ __forceinline__ void apply(const Carry& cy, f32x16_t (&tot)[MB][NB], int i) {
 #pragma unroll
-    for (int i = 0; i < MB; ++i) A[i] = read_a(i, hi);
-    static_for<GPC>([&](auto gic) __attribute__((always_inline)) {
-      constexpr int gi = decltype(gic)::value;
-      f32x16_t acc[MB][NB];
-      static_for<SPG>([&](auto ssc) __attribute__((always_inline)) {
-        constexpr int SS = decltype(ssc)::value;
-        constexpr int S = gi * SPG + SS;  // 16-k step within the chunk
-        bf16x8_t An[MB];
-        if constexpr (S + 1 < 8) {
+    for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-          for (int i = 0; i < MB; ++i) An[i] = read_a(i, 2 * (S + 1) + hi);
-        }
-        bf16x8_t B[NB];
+      for (int r = 0; r < 16; ++r) tot[i][nb][r] = __builtin_fmaf(cy.sv[nb], cy.acc[i][nb][r], tot[i][nb][r]);
+  }
+
+  // The eight 16-k steps of one chunk (x buffer X, ring slot wc), except the last step's
+  // MFMAs, which `last` issues.  A step reads the next step's A fragments before its own
+  // MFMAs, so the LDS latency runs under them.  A group's first step adds the group
+  // before it to tot (one row block's 16 FMAs before each MFMA that overwrites those
+  // sums): the FMAs then run beside the matrix pipe and no group ends in a block of them.
+  // cneg[gi][nb] receives -s*(128+z) of the chunk's groups; hook(step) and issue(step) run
+  // in every step but the last, zero_point after step ZS: the offsets it needs are known,
+  // the chunk before's (SUMS) or this one's (after the last group's first step).  B receives
+  // the last step's operand.
+  static constexpr int ZS = SUMS || GPC == 1 ? 1 : 5;
+  template <typename F, typename I, typename Z>
+  static __device__ __forceinline__ void compute(const W& wc, const u32x4_t* X, int lane, const Lanes& ln, Carry& cy,
+                                                 f32x16_t (&tot)[MB][NB], float (&cneg)[GPC][NB], bf16x8_t (&B)[NB],
+                                                 F&& hook, I&& issue, Z&& zero_point) {
+    const f32x16_t zero = {};
+    static_for<8>([&](auto sc) __attribute__((always_inline)) {
+      constexpr int S = decltype(sc)::value;  // 16-k step within the chunk
+      constexpr int gi = S / SPG;
+      constexpr bool FIRST = S % SPG == 0;
+      bf16x8_t An[MB];
+      if constexpr (S + 1 < 8) {
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) B[nb] = b_operand<BITS, S / 2>(wc.w[nb][S % 2]);
+        for (int i = 0; i < MB; ++i) An[i] = read_a(X, ln, lane, i, S + 1);
+      }
 #pragma unroll
-        for (int i = 0; i < MB; ++i)
+      for (int nb = 0; nb < NB; ++nb) B[nb] = b_operand<BITS, S / 2>(wc.w[nb][S % 2]);
+      if constexpr (S + 1 < 8) {
+#pragma unroll
+        for (int i = 0; i < MB; ++i) {
+          if constexpr (FIRST) apply(cy, tot, i);
 #pragma unroll
           for (int nb = 0; nb < NB; ++nb)
-            acc[i][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[i], B[nb], SS == 0 ? zero : acc[i][nb], 0, 0, 0);
-        if constexpr (S + 1 < 8) {
+            cy.acc[i][nb] =
+                __builtin_amdgcn_mfma_f32_32x32x16_bf16(cy.A[i], B[nb], FIRST ? zero : cy.acc[i][nb], 0, 0, 0);
+          if constexpr (FIRST) __builtin_amdgcn_sched_barrier(0);
+        }
 #pragma unroll
-          for (int i = 0; i < MB; ++i) A[i] = An[i];
+        for (int i = 0; i < MB; ++i) cy.A[i] = An[i];
+        issue(sc);
+        hook(sc);
+        if constexpr (FIRST) {
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) {
+            cy.sv[nb] = half_bits_to_float(wc.s[gi][nb]);
+            const float z = half_bits_to_float(wc.z[gi][nb]);
+            cneg[gi][nb] = -(cy.sv[nb] * (kCodeBias + z));
+          }
         }
         // Keep each step's unpacking and the next step's reads next to its MFMAs:
         // hoisting a whole chunk's worth of them costs more registers than two
         // wavefronts per SIMD leave.
         __builtin_amdgcn_sched_barrier(0);
-      });
-      float sv[NB];
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        sv[nb] = half_bits_to_float(wc.s[gi][nb]);
-        const float z = half_bits_to_float(wc.z[gi][nb]);
-        cneg[gi][nb] = -(sv[nb] * (kCodeBias + z));
+        if constexpr (S == ZS) {
+          zero_point();
+          __builtin_amdgcn_sched_barrier(0);
+        }
       }
-#pragma unroll
-      for (int i = 0; i < MB; ++i)
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) tot[i][nb][r] = __builtin_fmaf(sv[nb], acc[i][nb][r], tot[i][nb][r]);
     });
   }
+
+  // The last step's MFMAs of a chunk, and the first step's A fragments of the next one
+  // (x buffer Xn).
+  static __device__ __forceinline__ void last(const u32x4_t* Xn, int lane, const Lanes& ln, Carry& cy,
+                                              const bf16x8_t (&B)[NB]) {
+    bf16x8_t An[MB];
+#pragma unroll
+    for (int i = 0; i < MB; ++i) An[i] = read_a(Xn, ln, lane, i, 0);
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+        cy.acc[i][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cy.A[i], B[nb], cy.acc[i][nb], 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < MB; ++i) cy.A[i] = An[i];
+    __builtin_amdgcn_sched_barrier(0);
+  }
+
+  // The sums of x over each group of a chunk (x buffer X), [group][row]: LPR lanes a row,
+  // 128 / LPR k each (bf16 dot products with ones, then lane exchanges within the row's
+  // lanes of the group), the rows dealt to the team's wavefronts.  The lanes of 16
+  // consecutive ones read 16 different pieces, so every read is free of bank conflicts.
+  // Spread over the steps of the chunk, two pieces a step, summed one step after they are
+  // read: done at once, the chain of reads and dot products stalls the wavefront (32B
+  // gate|up at M = 128 75.5 us).
+  struct SumX {
+    static constexpr int LPR = ROWS >= 16 * WAVES ? 4 : 8;
+    static constexpr int PPL = 16 / LPR;    // pieces of one lane and row
+    static constexpr int RPW = kWave / LPR;  // rows of one wavefront at a time
+    static constexpr int ROUNDS = ROWS / (RPW * WAVES);
+    static_assert(ROWS % (RPW * WAVES) == 0 && PPL % 2 == 0 && PPL * ROUNDS <= 10, "whole rounds, within the steps");
+    static constexpr int LPG = LPR / GPC;  // lanes of one group
+    u32x4_t v[2];
+    float sum[2];
+    template <int S>
+    __device__ __forceinline__ void step(const u32x4_t* X, float* xsum, int wave, int lane) {
+      const int q = lane % LPR;
+      if constexpr (S >= 2 && 2 * (S - 2) < PPL * ROUNDS) {
+        constexpr int P = 2 * (S - 2), J = P / PPL;
+        constexpr bool FIRST = P % PPL == 0;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) sum[t] = piece_sum(v[t], FIRST ? 0.f : sum[t]);
+        if constexpr (P % PPL == PPL - 2) {
+          // the group's lanes all end with its sum and all store it: no branch
+          xsum[q / LPG * ROWS + RPW * (wave + WAVES * J) + lane / LPR] = span_reduce<LPG>(sum[0] + sum[1]);
+        }
+      }
+      if constexpr (S >= 1 && 2 * (S - 1) < PPL * ROUNDS) {
+        constexpr int P = 2 * (S - 1), J = P / PPL;
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+          v[t] = X[slot(RPW * (wave + WAVES * J) + lane / LPR, PPL * q + P % PPL + t)];
+      }
+    }
+  };
 
   // Zero-point term of a pair of groups: lanes 0-31 carry the first group, lanes
   // 32-63 the second; xs[i] is the sum of x of the lane's row in block i and the
@@ -230,15 +301,21 @@ struct MmaBody {
   }
 };
 
-// Barrier between chunks.  Each wavefront first reads one element of the buffer the
-// next chunk uses: the compiler then waits for this wavefront's copy into that buffer
-// (and, loads completing in order, for everything issued before it), but not for the
-// copies and weight loads issued after it, which a fenced __syncthreads() would drain.
-// LDS writes (the x sums) and reads are complete at the lgkmcnt wait; the empty
-// assembly statements keep the compiler from moving LDS accesses across the barrier.
-__device__ __forceinline__ void chunk_barrier(const u32x4_t* next, uint32_t& touch) {
-  touch ^= next[threadIdx.x & 63].x;
-  __builtin_amdgcn_s_waitcnt(kWaitLgkmcnt0);
+// s_waitcnt immediate: at most `vm` vector memory operations outstanding, no LDS one.
+constexpr int wait_vm_lds(int vm) { return (vm & 15) | (7 << 4) | ((vm >> 4) << 14); }
+
+// Barrier between chunks.  Each wavefront first waits for its own copies into the buffer
+// the next chunk uses and for its LDS reads.  Vector memory operations complete in issue
+// order, so waiting until only the VM operations issued after those copies are
+// outstanding is exact; a fenced __syncthreads() would drain all of them, and leaving the
+// wait to the compiler (its own tracking of copies into LDS) missed copies whose
+// instructions are spread over the steps.  The empty assembly statements keep the
+// compiler from moving LDS accesses across the barrier.
+template <int VM>
+__device__ __forceinline__ void chunk_barrier() {
+  static_assert(VM < 64, "vmcnt has six bits");
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(wait_vm_lds(VM));
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
@@ -261,17 +338,22 @@ __global__ __launch_bounds__(WAVES * kWave)
 __attribute__((amdgpu_waves_per_eu(WAVES == 8 || XB <= 2 ? 2 : 1))) void k_qmma(QArgs a) {
   static_assert(XB % 2 == 0 && XB >= 2 && XB <= 6, "chunk parity (pairs of 128-k groups) follows the ring slot");
   static_assert(WAVES == 4 || WAVES == 8, "wavefronts per workgroup");
-  static_assert(TEAMS == 1 || (TEAMS == 2 && WAVES == 8 && XB == 2 && (MB == 2 || MB == 4) && NB == 1),
+  static_assert(TEAMS == 1 || (TEAMS == 2 && WAVES == 8 && (XB == 2 || XB == 4) && (MB == 2 || MB == 4) && NB == 1),
                 "two teams of four wavefronts with two-chunk rings");
   constexpr int TW = WAVES / TEAMS;  // wavefronts per team (its column blocks)
   using Body = MmaBody<BITS, GROUP, MB, NB, TW>;
   constexpr int GPC = Body::GPC;
+  constexpr bool SUMS = Body::SUMS;
   constexpr int XCH = Body::XCH;
   constexpr int PF = XB;
+  constexpr int SPREAD = 7;  // steps of a chunk that issue loads
   constexpr int NBUF = XB * TEAMS;  // LDS chunk buffers; team t uses [t * XB, t * XB + XB)
   static_assert(NBUF <= 8, "LDS chunk buffers");
   __shared__ u32x4_t xb0[XCH], xb1[XCH], xb2[NBUF > 2 ? XCH : 1], xb3[NBUF > 3 ? XCH : 1],
       xb4[NBUF > 4 ? XCH : 1], xb5[NBUF > 5 ? XCH : 1], xb6[NBUF > 6 ? XCH : 1], xb7[NBUF > 7 ? XCH : 1];
+  constexpr int XSC = GPC * Body::ROWS;  // sums of x of one chunk, [group][row]
+  __shared__ float xs0[XSC], xs1[XSC], xs2[NBUF > 2 ? XSC : 1], xs3[NBUF > 3 ? XSC : 1], xs4[NBUF > 4 ? XSC : 1],
+      xs5[NBUF > 5 ? XSC : 1], xs6[NBUF > 6 ? XSC : 1], xs7[NBUF > 7 ? XSC : 1];
   // Chunk buffer I, selected at compile time: separate LDS objects, so that the
   // compiler can tell the buffers' accesses apart.
   auto lds = [&](auto ic) __attribute__((always_inline)) -> u32x4_t* {
@@ -285,6 +367,18 @@ __attribute__((amdgpu_waves_per_eu(WAVES == 8 || XB <= 2 ? 2 : 1))) void k_qmma(
     else if constexpr (I == 5) return xb5;
     else if constexpr (I == 6) return xb6;
     else return xb7;
+  };
+  auto lds_xs = [&](auto ic) __attribute__((always_inline)) -> float* {
+    constexpr int I = decltype(ic)::value;
+    static_assert(I < NBUF, "chunk buffer index");
+    if constexpr (I == 0) return xs0;
+    else if constexpr (I == 1) return xs1;
+    else if constexpr (I == 2) return xs2;
+    else if constexpr (I == 3) return xs3;
+    else if constexpr (I == 4) return xs4;
+    else if constexpr (I == 5) return xs5;
+    else if constexpr (I == 6) return xs6;
+    else return xs7;
   };
 
   const int lane = threadIdx.x % kWave;
@@ -330,8 +424,9 @@ __attribute__((amdgpu_waves_per_eu(WAVES == 8 || XB <= 2 ? 2 : 1))) void k_qmma(
   {
     const int row = 4 * tw + (lane >> 4), pc = (lane & 15) ^ (row & 15);
     ln.x = (static_cast<uint32_t>(row) * a.K + pc * 8) * 2;
-    ln.a = r32 * 16;
-    ln.xs = (static_cast<uint32_t>(hi) * a.M + r32) * 4;
+    ln.a = r32 * 16 + (hi ^ (r32 & 15));
+    const int xi = kWave * (tw % Body::XSW) + lane;  // this lane's sum in the chunk's [group][row]
+    ln.xs = (static_cast<uint32_t>(xi / Body::ROWS) * a.M + xi % Body::ROWS) * 4;
   }
 
   f32x16_t tot[MB][NB];
@@ -340,18 +435,6 @@ __attribute__((amdgpu_waves_per_eu(WAVES == 8 || XB <= 2 ? 2 : 1))) void k_qmma(
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) tot[i][nb] = f32x16_t{};
 
-  // The first group of the pair whose x sums chunk c's ring slot carries: with groups
-  // of 64 its own two groups; with groups of 128 the pair (c - 1, c) for odd c and
-  // (c, c + 1) for even c (used only when c is the team's last chunk, then alone).  A
-  // refill past the last chunk can ask for group -1 of the workgroup's first block,
-  // which it never uses: held at 0, since the scalar offset of a buffer load is not
-  // range checked.
-  auto pair_first = [&](int c, int parity) __attribute__((always_inline)) {
-    const int kb = blk(c);
-    return GPC == 2 ? 2 * kb : parity ? max(kb - 1, 0) : kb;
-  };
-
-  uint32_t touch = 0;
   // The main loop of team T (a compile-time constant, so that its ring buffers are
   // distinct LDS objects the compiler can tell apart).
   auto run = [&](auto tc) __attribute__((always_inline)) {
@@ -360,55 +443,146 @@ __attribute__((amdgpu_waves_per_eu(WAVES == 8 || XB <= 2 ? 2 : 1))) void k_qmma(
     auto ring = [&](auto ic) __attribute__((always_inline)) -> u32x4_t* {
       return lds(std::integral_constant<int, T * XB + decltype(ic)::value % XB>{});
     };
+    auto ring_xs = [&](auto ic) __attribute__((always_inline)) -> float* {
+      return lds_xs(std::integral_constant<int, T * XB + decltype(ic)::value % XB>{});
+    };
     // Prologue: chunks 0 .. XB - 2 of x and of the weights in flight.  Unconditional
     // loads keep the compiler's count of outstanding loads exact.
     typename Body::W w[PF];
     static_for<XB - 1>([&](auto u) __attribute__((always_inline)) {
       constexpr int U = decltype(u)::value;
-      Body::stage(ring(u), bu, ln, a.K, blk(U), tw);
-      Body::load_w(w[U], bu, ln, a.M, a.N, blk(U), pair_first(U, U & 1));
+      static_for<Body::PIECES>([&](auto pc) __attribute__((always_inline)) {
+        Body::load_piece(decltype(pc)::value, w[U], ring(u), ring_xs(u), bu, ln, a, blk(U), tw);
+      });
     });
-    chunk_barrier(ring(std::integral_constant<int, 0>{}), touch);
+    if constexpr (SUMS)  // chunk 0's zero-point step reads the sums of "chunk -1"
+      for (int i = lane; i < XSC; i += kWave) ring_xs(std::integral_constant<int, XB - 1>{})[i] = 0.f;
+    chunk_barrier<(XB - 2) * Body::VM>();  // chunk 0 landed; chunks 1 .. XB - 2 in flight
 
-    float cfirst[NB];  // 128-k groups: -s*(128+z) of the first group of an open pair
+    typename Body::Carry cy;
+#pragma unroll
+    for (int i = 0; i < MB; ++i) {
+      cy.A[i] = Body::read_a(ring(std::integral_constant<int, 0>{}), ln, lane, i, 0);
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) cy.acc[i][nb] = f32x16_t{};
+    }
+    // -s*(128+z) of the chunk before, and for 128-k groups that and the sums of x of the
+    // first group of an open pair
+    float cprev[GPC][NB], cfirst[NB], xfirst[MB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      cfirst[nb] = 0.f;
+#pragma unroll
+      for (int gi = 0; gi < GPC; ++gi) cprev[gi][nb] = 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < MB; ++i) xfirst[i] = 0.f;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) cy.sv[nb] = 0.f;
 
-    // One chunk cc (ring slot U = cc % XB, parity U): start the copy of chunk
-    // cc + XB - 1 of x (into the buffer chunk cc - 1 used) and the refill of the weight
-    // slot chunk cc - 1 used, then the chunk's MFMAs and, once a pair of groups is
-    // complete, its zero-point term.
+    // One chunk cc (ring slot U = cc % XB, parity U).  Its steps issue the loads of chunk
+    // cc + XB - 1 into the ring slots of chunk cc - 1, a few per step: as one burst after
+    // the barrier they stall every wavefront of the CU on the address units at once.
+    // Before the last step's MFMAs every A fragment of the chunk is in registers; the
+    // barrier there waits for chunk cc + 1 of x, whose first A fragments are read under
+    // those MFMAs.  Once a pair of groups is complete its zero-point term is added.
     auto step = [&](auto u, int cc) __attribute__((always_inline)) {
       constexpr int U = decltype(u)::value;
+      constexpr int V = (U + XB - 1) % XB;
       const int cn = cc + XB - 1;
-      Body::stage(ring(std::integral_constant<int, (U + XB - 1) % XB>{}), bu, ln, a.K, blk(cn), tw);
-      Body::load_w(w[(U + PF - 1) % PF], bu, ln, a.M, a.N, blk(cn), pair_first(cn, (U + PF - 1) & 1));
-      if (TEAMS == 1 || cc < nchunks) {
-        float cneg[GPC][NB];
-        Body::compute(w[U], ring(u), lane, ln, tot, cneg);
-        float cop[NB];
-        if constexpr (GPC == 2) {
+      const int kbn = blk(cn);
+      auto issue = [&](auto sc) __attribute__((always_inline)) {
+        constexpr int S = decltype(sc)::value;
+        static_for<Body::PIECES>([&](auto pc) __attribute__((always_inline)) {
+          constexpr int P = decltype(pc)::value;
+          constexpr int Q = XB > 2 ? P : (P + Body::PIECES - Body::DMA) % Body::PIECES;
+          if constexpr (P * SPREAD / Body::PIECES == S)
+            Body::load_piece(Q, w[V], ring(std::integral_constant<int, V>{}),
+                             ring_xs(std::integral_constant<int, V>{}), bu, ln, a, kbn, tw);
+        });
+      };
+      const bool active = TEAMS == 1 || cc < nchunks;
+      bf16x8_t B[NB];
+      if (active) {
+        // Zero-point term: of this chunk (sums of x copied with it), or with SUMS of chunk
+        // cc - 1, whose sums the barrier at its end made visible.
+        constexpr int XU = SUMS ? (U + XB - 1) % XB : U;
+        float cneg[GPC][NB], xs[MB];
+        auto& cz = [&]() __attribute__((always_inline)) -> float(&)[GPC][NB] {
+          if constexpr (SUMS) return cprev;
+          else return cneg;
+        }();
+        const float* X = ring_xs(std::integral_constant<int, XU>{});
 #pragma unroll
-          for (int nb = 0; nb < NB; ++nb) cop[nb] = hi ? cneg[1][nb] : cneg[0][nb];
-          Body::apply_pair(w[U].xs, cop, tot);
-        } else if constexpr (U % 2 == 1) {
+        for (int i = 0; i < MB; ++i) xs[i] = X[(GPC == 2 ? hi * Body::ROWS : 0) + 32 * i + r32];
+        typename Body::SumX sx;
+        Body::compute(w[U], ring(u), lane, ln, cy, tot, cneg, B, [&](auto sc) __attribute__((always_inline)) {
+          constexpr int S = decltype(sc)::value;
+          if constexpr (SUMS) sx.template step<S>(ring(u), ring_xs(u), tw, lane);
+        }, issue, [&]() __attribute__((always_inline)) {
+          float cop[NB];
+          if constexpr (GPC == 2) {
 #pragma unroll
-          for (int nb = 0; nb < NB; ++nb) cop[nb] = hi ? cneg[0][nb] : cfirst[nb];
-          Body::apply_pair(w[U].xs, cop, tot);
-        } else {
+            for (int nb = 0; nb < NB; ++nb) cop[nb] = hi ? cz[1][nb] : cz[0][nb];
+            Body::apply_pair(xs, cop, tot);
+          } else if constexpr (XU % 2 == 1) {
 #pragma unroll
-          for (int nb = 0; nb < NB; ++nb) cfirst[nb] = cneg[0][nb];
-          if (cc == last) {  // an odd number of chunks: the last group pairs with nothing
+            for (int i = 0; i < MB; ++i) {
+              asm volatile("" : "+v"(xs[i]));  // keeps the select from turning into a branch around the read
+              xs[i] = hi ? xs[i] : xfirst[i];
+            }
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) cop[nb] = hi ? 0.f : cneg[0][nb];
-            Body::apply_pair(w[U].xs, cop, tot);
+            for (int nb = 0; nb < NB; ++nb) cop[nb] = hi ? cz[0][nb] : cfirst[nb];
+            Body::apply_pair(xs, cop, tot);
+          } else {
+#pragma unroll
+            for (int i = 0; i < MB; ++i) xfirst[i] = xs[i];
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) cfirst[nb] = cz[0][nb];
           }
-        }
+        });
+#pragma unroll
+        for (int gi = 0; gi < GPC; ++gi)
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) cprev[gi][nb] = cneg[gi][nb];
+      } else {
+        static_for<7>(issue);
       }
-      chunk_barrier(ring(std::integral_constant<int, (U + 1) % XB>{}), touch);
+      chunk_barrier<(XB - 2) * Body::VM>();  // in flight: chunks cc + 2 .. cc + XB - 1
+      if (active) Body::last(ring(std::integral_constant<int, (U + 1) % XB>{}), lane, ln, cy, B);
     };
     for (int c = 0; c < nsteps; c += XB)
       static_for<XB>([&](auto u) __attribute__((always_inline)) {
         if (c + decltype(u)::value < nsteps) step(u, c + decltype(u)::value);
       });
+    // the last group, and the zero-point term of the last chunk: with 128-k groups of the
+    // open pair, or of its group alone when the number of chunks is odd
+#pragma unroll
+    for (int i = 0; i < MB; ++i) Body::apply(cy, tot, i);
+    const bool alone = GPC == 1 && (nchunks & 1);
+    if constexpr (SUMS) {
+      if (nchunks > 0) {
+        float cop[NB], xs[MB];
+        static_for<XB>([&](auto u) __attribute__((always_inline)) {
+          if (last % XB != decltype(u)::value) return;
+#pragma unroll
+          for (int i = 0; i < MB; ++i) xs[i] = ring_xs(u)[(GPC == 2 ? hi * Body::ROWS : 0) + 32 * i + r32];
+        });
+#pragma unroll
+        for (int i = 0; i < MB; ++i) xs[i] = GPC == 2 || alone || hi ? xs[i] : xfirst[i];
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+          cop[nb] = GPC == 2 ? (hi ? cprev[GPC - 1][nb] : cprev[0][nb])
+                    : alone  ? (hi ? 0.f : cprev[0][nb])
+                             : (hi ? cprev[0][nb] : cfirst[nb]);
+        Body::apply_pair(xs, cop, tot);
+      }
+    } else if (alone) {
+      float cop[NB];
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) cop[nb] = hi ? 0.f : cfirst[nb];
+      Body::apply_pair(xfirst, cop, tot);
+    }
   };
   if constexpr (TEAMS == 1) {
     run(std::integral_constant<int, 0>{});
@@ -418,9 +592,6 @@ __attribute__((amdgpu_waves_per_eu(WAVES == 8 || XB <= 2 ? 2 : 1))) void k_qmma(
     else
       run(std::integral_constant<int, 1>{});
   }
-  // `touch` (an xor of the touched values) only keeps the touching reads alive.
-  if (touch == 0x7FC00001u && a.M < 0) a.y[0] = 0;
-
   if constexpr (TEAMS == 2) {
     // Team 1 hands its sums to team 0 through the LDS of its ring (4 wavefronts x MB
     // row blocks x 16 registers x 64 lanes, the size of two of its chunk buffers: each
