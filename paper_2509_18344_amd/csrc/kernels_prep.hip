@@ -106,27 +106,100 @@ constexpr double kHqqBeta = 10.0;
 constexpr double kHqqKappa = 1.01;
 constexpr int kHqqIters = 20;
 
-// The group's weights sit in LDS, transposed (element i of thread t at [i][t]), so
-// the rounds index them without spilling registers and without bank conflicts.
+// What bounds it, and the layout.  The rounds are float64 arithmetic; a float64 division
+// costs about as much as the rest of an element's step and the power function several
+// times that, so both leave the rounds (7B down, 3584 x 18944, 4-bit groups of 64:
+// 7000 us with them):
+//  - w / s does not change from round to round: the quotients are computed once.
+//  - the residual x of an unclamped weight is at most s / 2, where the soft threshold is
+//    zero: |x| - |x|^(p-1) / beta > 0 needs |x|^(2-p) > 1 / beta.  For |x| <= kHqqNoShrink
+//    it cannot hold in any round (the largest beta of the rounds is 12.2, and
+//    0.125^(p-1) / 12.2 = 0.153 > 0.125, a margin far beyond rounding): e is zero and
+//    the refitted term is q - w / s.  A group that meets a larger residual (or a NaN)
+//    starts over with the plain rounds (hqq_group).
+//  - the error sum of a new zero and the next refit need the same codes: one pass
+//    computes both (the refit of the last pass is not used).
+// Every value that decides anything comes from the same operations in the same order as
+// in the plain rounds, so the results are bit for bit theirs.  One thread works on one
+// group, since its sums run in index order, with the weights and quotients in registers
+// (in LDS they would leave less than one wavefront per SIMD).
+constexpr double kHqqNoShrink = 0.125;
+
+__device__ __forceinline__ double hqq_code(double quot, double z, double qmax) {
+  const double c = __builtin_rint(quot + z);
+  return c < 0.0 ? 0.0 : (c > qmax ? qmax : c);
+}
+
+__device__ __forceinline__ uint32_t hqq_word(const double* quot, double z, double qmax) {
+  uint32_t b = 0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) b |= static_cast<uint32_t>(hqq_code(quot[k], z, qmax)) << (8 * k);
+  return b;
+}
+
+// The plain rounds for one group from its weights in memory: returns the zero's fp16
+// bits and stores the codes.
+__device__ __attribute__((noinline)) uint16_t hqq_group(const float* src, uint8_t* dst, int group, double s,
+                                                        uint16_t z16, double qmax) {
+  auto l1 = [&](double z) {
+    double tot = 0.0;
+    for (int i = 0; i < group; ++i) {
+      const double x = src[i];
+      tot += fabs(x - (hqq_code(x / s, z, qmax) - z) * s);
+    }
+    return tot;
+  };
+  const double z0 = f16_bits_to_f64(z16);
+  const double e0 = l1(z0);
+  double z = z0, best_z = z0, best = e0, beta = kHqqBeta;
+  for (int it = 0; it < kHqqIters; ++it) {
+    double acc = 0.0;
+    for (int i = 0; i < group; ++i) {
+      const double x = src[i];
+      const double q = hqq_code(x / s, z, qmax);
+      const double r = x - (q - z) * s;
+      const double a = fabs(r);
+      const double e = r == 0.0 ? 0.0 : copysign(fmax(a - pow(a, kHqqP - 1.0) / beta, 0.0), r);
+      acc += q - (x - e) / s;
+    }
+    const double z_new = acc / group;
+    const double err = l1(z_new);
+    if (!(err < best)) break;
+    best = err;
+    best_z = z_new;
+    z = z_new;
+    beta = beta * kHqqKappa;
+  }
+  const uint16_t zb = f64_to_f16_bits(best_z);
+  if (l1(f16_bits_to_f64(zb)) < e0) z16 = zb;
+  const double zf = f16_bits_to_f64(z16);
+  for (int i = 0; i < group; i += 4) {
+    double quot[4];
+    for (int k = 0; k < 4; ++k) quot[k] = static_cast<double>(src[i + k]) / s;
+    *reinterpret_cast<uint32_t*>(dst + i) = hqq_word(quot, zf, qmax);
+  }
+  return z16;
+}
+
 template <int GROUP>
-__global__ __launch_bounds__(kWave) void k_quantize_hqq(const float* __restrict__ w, int bits, int N, int K,
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(GROUP == 64 ? 2 : 1))) void k_quantize_hqq(const float* __restrict__ w, int bits, int N, int K,
                                                        uint8_t* __restrict__ codes, uint16_t* __restrict__ sc,
                                                        uint16_t* __restrict__ zr) {
-  __shared__ float wl[GROUP][kWave];
-  const int t = threadIdx.x;
   const int gpr = K / GROUP;
-  const long long gid = static_cast<long long>(blockIdx.x) * kWave + t;  // g * N + n
-  if (gid >= static_cast<long long>(N) * gpr) return;  // no barrier follows
+  const long long gid = static_cast<long long>(blockIdx.x) * kWave + threadIdx.x;  // g * N + n
+  if (gid >= static_cast<long long>(N) * gpr) return;
   const long long n = gid % N;
   const int g = static_cast<int>(gid / N);
   const float* src = w + n * K + static_cast<long long>(g) * GROUP;
+  float wv[GROUP];
   float mn = INFINITY, mx = -INFINITY;
+#pragma unroll
   for (int i = 0; i < GROUP; i += 4) {
     const float4 q4 = *reinterpret_cast<const float4*>(src + i);
-    wl[i][t] = q4.x;
-    wl[i + 1][t] = q4.y;
-    wl[i + 2][t] = q4.z;
-    wl[i + 3][t] = q4.w;
+    wv[i] = q4.x;
+    wv[i + 1] = q4.y;
+    wv[i + 2] = q4.z;
+    wv[i + 3] = q4.w;
     mn = fminf(fminf(mn, q4.x), fminf(fminf(q4.y, q4.z), q4.w));
     mx = fmaxf(fmaxf(mx, q4.x), fmaxf(fmaxf(q4.y, q4.z), q4.w));
   }
@@ -143,56 +216,75 @@ __global__ __launch_bounds__(kWave) void k_quantize_hqq(const float* __restrict_
   } else {
     z16 = f64_to_f16_bits(-wmin / s);
   }
-  auto code = [&](double x, double z) __attribute__((always_inline)) {
-    const double c = __builtin_rint(x / s + z);
-    return c < 0.0 ? 0.0 : (c > qmax ? qmax : c);
-  };
-  auto l1 = [&](double z) __attribute__((always_inline)) {
-    double tot = 0.0;
+  double quot[GROUP];
+#pragma unroll
+  for (int i = 0; i < GROUP; ++i) {
+    quot[i] = static_cast<double>(wv[i]) / s;
+    asm volatile("" : "+v"(quot[i]));
+  }
+  // The error sum of zero z, and the refit sum of the round that starts from it.
+  bool large = false;
+  auto pass = [&](double z, double& refit) __attribute__((always_inline)) {
+    double err = 0.0, acc = 0.0, amax = 0.0;
+#pragma unroll
     for (int i = 0; i < GROUP; ++i) {
-      const double x = wl[i][t];
-      tot += fabs(x - (code(x, z) - z) * s);
+      const double q = hqq_code(quot[i], z, qmax);
+      double x;  // converted in every pass: kept across passes, it would take two registers more
+      asm volatile("v_cvt_f64_f32 %0, %1" : "=v"(x) : "v"(wv[i]));
+      const double a = fabs(x - (q - z) * s);
+      err += a;
+      acc += q - quot[i];
+      amax = fmax(amax, a);
+      // four elements at a time: with all 64 in flight the values spill
+      if (i % 4 == 3) asm volatile("" : "+v"(err), "+v"(acc), "+v"(amax));
     }
-    return tot;
+    refit = acc;
+    large = !(amax <= kHqqNoShrink);
+    return err;
   };
   if (!degenerate) {
     const double z0 = f16_bits_to_f64(z16);
-    const double e0 = l1(z0);
-    double z = z0, best_z = z0, best = e0, beta = kHqqBeta;
-    for (int it = 0; it < kHqqIters; ++it) {
-      double acc = 0.0;
-      for (int i = 0; i < GROUP; ++i) {
-        const double x = wl[i][t];
-        const double q = code(x, z);
-        const double r = x - (q - z) * s;
-        const double a = fabs(r);
-        const double e = r == 0.0 ? 0.0 : copysign(fmax(a - pow(a, kHqqP - 1.0) / beta, 0.0), r);
-        acc += q - (x - e) / s;
+    // Pass 0 is the min/max zero, pass p > 0 the zero of round p - 1; the pass after the
+    // search ended is the best zero in fp16.  One copy of the unrolled pass serves all.
+    double z = z0, best_z = z0, best = 0.0, e0 = 0.0;
+    for (int p = 0;; ++p) {
+      double refit;
+      const double err = pass(z, refit);
+      if (large) break;
+      if (p > kHqqIters + 1) {  // z is the best zero rounded to fp16
+        if (err < e0) z16 = f64_to_f16_bits(z);
+        break;
       }
-      const double z_new = acc / GROUP;
-      const double err = l1(z_new);
-      if (!(err < best)) break;
-      best = err;
-      best_z = z_new;
-      z = z_new;
-      beta = beta * kHqqKappa;
+      bool more = p < kHqqIters;
+      if (p == 0) {
+        e0 = best = err;
+      } else if (err < best) {
+        best = err;
+        best_z = z;
+      } else {
+        more = false;
+      }
+      if (more) {
+        z = refit / GROUP;
+      } else {
+        z = f16_bits_to_f64(f64_to_f16_bits(best_z));
+        p = kHqqIters + 1;  // the last pass follows
+      }
     }
-    const uint16_t zb = f64_to_f16_bits(best_z);
-    if (l1(f16_bits_to_f64(zb)) < e0) z16 = zb;
   }
-  const double zf = f16_bits_to_f64(z16);
   uint8_t* dst = codes + n * K + static_cast<long long>(g) * GROUP;
-  for (int i = 0; i < GROUP; i += 16) {
-    uint32_t word[4];
+  if (large) {
+    z16 = hqq_group(src, dst, GROUP, s, z16, qmax);
+  } else {
+    const double zf = f16_bits_to_f64(z16);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      uint32_t b = 0;
+    for (int i = 0; i < GROUP; i += 16) {
+      uint32_t word[4];
 #pragma unroll
-      for (int k = 0; k < 4; ++k)
-        b |= (degenerate ? 0u : static_cast<uint32_t>(code(wl[i + 4 * j + k][t], zf))) << (8 * k);
-      word[j] = b;
+      for (int j = 0; j < 4; ++j) word[j] = degenerate ? 0u : hqq_word(quot + i + 4 * j, zf, qmax);
+      __builtin_amdgcn_sched_barrier(0);
+      *reinterpret_cast<uint4*>(dst + i) = make_uint4(word[0], word[1], word[2], word[3]);
     }
-    *reinterpret_cast<uint4*>(dst + i) = make_uint4(word[0], word[1], word[2], word[3]);
   }
   sc[static_cast<long long>(g) * N + n] = s16;
   zr[static_cast<long long>(g) * N + n] = z16;
