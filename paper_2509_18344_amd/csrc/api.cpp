@@ -99,6 +99,7 @@ struct Tuning {
   int mma8_half_min_m = 48;       // the same where 256-column groups cover only half the CUs
   int mma_teams = 0;              // 32x32 kernel, long-K launches: 1 = one team, 2 = two; 0 = choose
   int teams64_min_m = 33;         // long-K launches from this M up to 64: 64-row two-team 32x32 tiles
+  int rb_splits = 0;              // 32-row 32x32 tiles: splits of K; 0 = choose, -1 = not these tiles
   int row_split = 0;              // 16x16x32 tiles: 1 = two row blocks where possible, 2 = never; 0 = choose
 };
 
@@ -139,6 +140,7 @@ const Tuning& tuning() {
         else if (k == "mma8_min_m") r.mma8_min_m = v;
         else if (k == "mma8_half_min_m") r.mma8_half_min_m = v;
         else if (k == "mma_teams") r.mma_teams = v;
+        else if (k == "rb_splits") r.rb_splits = v;
         else if (k == "row_split") r.row_split = v;
         else if (k == "teams64_min_m") r.teams64_min_m = v;
       }
@@ -468,7 +470,20 @@ int make_plan(int M, int N, int K, int bits, int group, int path, subspec_plan* 
   return SUBSPEC_OK;
 }
 
-// The launch made from a described plan, for 32x32 tiles.  It needs no more workspace.
+// The launch made from a described plan, where the 32x32 kernel has a better form for it.
+// It needs no more workspace.  us per call, described against made, one run each:
+//  - 16x16x32 launches of two row blocks (q|k|v, o) run as 32-row two-team tiles, the rows
+//    in blocks of 32 along grid y, K split only as far as one workgroup per CU goes:
+//    without partial sums, 7168x5120 3-bit 25.3 against 18.5 us and 5120x5120 21.1 against
+//    18.1 at M = 128, 2-bit g64 27.8 against 19.3, 4608x3584 4-bit 17.2 against 14.9; two and
+//    three splits at M = 64 16.5 against 14.3 and 13.5 against 12.6.  Not from M = 65 where
+//    they exceed a workgroup per CU (14336x4096 4-bit 30.0 against 31.4), and up to M = 64 not
+//    for a K under 36 blocks (4608x3584 11.1 against 11.6) or few columns (2048x8192 11.9
+//    against 12.1).  What bounds them is the L2: every block of rows reads the weights
+//    again and every column group x, 128 MB at 7168x5120.
+//  - 16x16x32 launches of four row tiles on half-wide column groups (37888x3584, M = 33 to
+//    47) run as 64-row eight-wavefront tiles: 30.9 against 29.1 us at M = 37, 3-bit 30.8
+//    against 28.3 at 44, 4-bit g64 35.7 against 32.3 at 40.
 //  - 64-row two-team tiles run with four-chunk rings: 5120x27648 3-bit 33.2 against 36.2 us
 //    at M = 64 and 31.9 against 35.7 at 48, 2-bit g64 33.3 against 37.1 at 64, 3584x18944
 //    4-bit 21.7 against 22.7 at 37.
@@ -476,20 +491,60 @@ int make_plan(int M, int N, int K, int bits, int group, int path, subspec_plan* 
 //    measured faster: 55296x5120 4-bit 76.1 against 100.2 us, 3-bit g64 82.1 against 89.9;
 //    where 256-column groups cover only half the CUs with groups of 128 (37888x3584 4-bit
 //    46.2 against 56.1 us; 3-bit g64 at M = 96 53.0 against 50.4).
-void refine_launch(int N, int K, int group, subspec_plan* p, subspec::KernelChoice* kc) {
+void refine_launch(int M, int N, int K, int group, int path, subspec_plan* p, subspec::KernelChoice* kc) {
   const Tuning& tu = tuning();
-  if (kc->shape != 32 || tu.mma_waves || tu.mfma_pf) return;
-  if (kc->teams == 2 && kc->rows == 64) kc->prefetch = 4;
+  const bool any_shape = path == SUBSPEC_PATH_AUTO || path == SUBSPEC_PATH_MFMA;
+  const int KB = K / subspec::kTileK;
+  const int units32 = (N + 127) / 128 * ((M + 31) / 32);
+  if (any_shape && kc->shape == 16 && kc->row_blocks == 2 && tu.rb_splits >= 0 &&
+      (M > 64 ? units32 <= device_cus() : KB >= 36 && units32 * 4 >= device_cus())) {
+    const int row_blocks = (M + 31) / 32;
+    const int groups = (N + 127) / 128;
+    int splits = tu.rb_splits ? tu.rb_splits : std::max(1, std::min(device_cus() / units32, KB / 8));
+    // no more partial sums than the described launch stores
+    const long long room = p->splits > 1 ? static_cast<long long>(p->splits) * 2 * kc->rows / (32ll * row_blocks) : 1;
+    splits = static_cast<int>(std::min<long long>(splits, std::max(1ll, room)));
+    kc->shape = 32;
+    kc->rows = 32;
+    kc->row_blocks = row_blocks;
+    kc->nt = 2;
+    kc->waves = 8;
+    kc->teams = 2;
+    kc->chunk = 1;
+    kc->prefetch = 4;
+    p->col_groups = groups;
+    p->full_groups = 0;
+    p->blocks_per_split = (KB + splits - 1) / splits;
+    p->splits = (KB + p->blocks_per_split - 1) / p->blocks_per_split;
+    p->grid = groups * p->splits;
+    return;
+  }
   const int groups = (N + 255) / 256;
   const bool wide8 = groups * 4 >= 3 * device_cus();
   const bool half8 = groups * 2 >= device_cus();
-  if (kc->waves == 4 && kc->rows == 128 && K / subspec::kTileK < 128 && (wide8 || (half8 && group == 128))) {
+  if (any_shape && kc->shape == 16 && kc->rows == 64 && kc->row_blocks == 1 && half8 && KB < 128 && !tu.mma_shape &&
+      tu.mma8_half_min_m == Tuning().mma8_half_min_m) {
+    kc->shape = 32;
+    kc->nt = 2;
+    kc->waves = 8;
+    kc->teams = 1;
+    kc->chunk = 1;
+    kc->prefetch = 4;
+    p->col_groups = p->grid = groups;
+    p->full_groups = 0;
+    p->splits = 1;
+    p->blocks_per_split = KB;
+    return;
+  }
+  if (kc->shape != 32 || tu.mma_waves || tu.mfma_pf) return;
+  if (kc->teams == 2 && kc->rows == 64) kc->prefetch = 4;
+  if (kc->waves == 4 && kc->rows == 128 && KB < 128 && (wide8 || (half8 && group == 128))) {
     kc->waves = 8;
     kc->prefetch = 4;
     p->col_groups = p->grid = groups;
     p->full_groups = 0;
     p->splits = 1;
-    p->blocks_per_split = K / subspec::kTileK;
+    p->blocks_per_split = KB;
   }
 }
 
@@ -535,7 +590,7 @@ int make_plan_cached(int M, int N, int K, int bits, int group, int path, subspec
   }
   const int rc = make_plan(M, N, K, bits, group, path, p, kc, ws_cap);
   if (rc) return rc;
-  refine_launch(N, K, group, p, kc);
+  refine_launch(M, N, K, group, path, p, kc);
   if (cache.size() >= kPlanCacheEntries) cache.clear();
   cache.emplace(key, CachedPlan{*p, *kc});
   return SUBSPEC_OK;
@@ -701,7 +756,8 @@ int qlinear_impl(const void* x, const void* qweight, const void* scales, const v
       if (rc) return rc;
     }
     char* base = static_cast<char*>(ws);
-    const size_t xsb = xsum_bytes(kc, M, K, group);
+    // only 128-row 32x32 tiles read pre-pass sums of x
+    const size_t xsb = kc.rows == 128 ? xsum_bytes(kc, M, K, group) : 0;
     a.cnt = reinterpret_cast<unsigned*>(base);
     a.xsum = xsb ? reinterpret_cast<const float*>(base + subspec::kSplitCounterBytes) : nullptr;
     a.ws = reinterpret_cast<float*>(base + subspec::kSplitCounterBytes + xsb);
@@ -710,7 +766,8 @@ int qlinear_impl(const void* x, const void* qweight, const void* scales, const v
   if (kc.shape == 32) {
     if (kc.rows == 128) e = subspec::launch_xsum(a.x, M, K, group, const_cast<float*>(a.xsum), st);
     if (e == hipSuccess)
-      e = subspec::launch_qmma(kc.waves, kc.teams, kc.rows / 32, kc.nt / 2, kc.prefetch, bits, group, a, p.grid, st);
+      e = subspec::launch_qmma(kc.waves, kc.teams, kc.rows / 32, kc.nt / 2, kc.prefetch, bits, group, a, p.grid,
+                               kc.row_blocks, st);
   } else {
     e = subspec::launch_qlinear(kc, bits, group, a, p.grid, st);
   }

@@ -30,10 +30,10 @@ int qmma_resident_blocks(int waves, int teams, int mb, int nb, int pf, int bits,
 }
 
 hipError_t launch_qmma(int waves, int teams, int mb, int nb, int pf, int bits, int group, const QArgs& a,
-                       int grid, hipStream_t st) {
+                       int grid, int row_blocks, hipStream_t st) {
   const MmaVariant* v = find_mma(waves, teams, mb, nb, pf, bits, group);
   if (!v) return hipErrorInvalidDeviceFunction;
-  hipLaunchKernelGGL(v->fn, dim3(grid), dim3(waves * kWave), 0, st, a);
+  hipLaunchKernelGGL(v->fn, dim3(grid, row_blocks), dim3(waves * kWave), 0, st, a);
   return hipGetLastError();
 }
 

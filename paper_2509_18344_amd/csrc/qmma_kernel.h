@@ -83,6 +83,11 @@ struct MmaBody {
   static constexpr int XCH = ROWS * 16;       // 16-byte pieces per chunk buffer
   static constexpr int DMA = ROWS / (4 * WAVES);  // x copy loads per wavefront per chunk
   static_assert(DMA * 4 * WAVES == ROWS, "each copy load fills four rows");
+  static_assert(WAVES >= 4, "a lane's copies share their row % 16");
+  // A fragments are read D steps ahead: a step is MB MFMAs of 32 cycles, an LDS read some
+  // 130 cycles and more under load.  M = 128 q|k|v (7168x5120, 32-row tiles) 20.8 us with
+  // D = 1.
+  static constexpr int D = MB == 1 ? 4 : MB == 2 ? 2 : 1;
 
   // One ring slot: the chunk's two slices per column block and the fp16 scale and
   // zero-point of the lane's column for each of the chunk's groups.
@@ -151,10 +156,10 @@ struct MmaBody {
   }
 
   // What a wavefront carries from one chunk to the next: the A fragments of the next
-  // chunk's first step, and the last group's sums acc with its scale sv, which are added
-  // to tot between the next group's first MFMAs (apply).
+  // chunk's first D steps, and the last group's sums acc with its scale sv, which are
+  // added to tot between the next group's first MFMAs (apply).
   struct Carry {
-    bf16x8_t A[MB];
+    bf16x8_t A[D][MB];
     f32x16_t acc[MB][NB];
     float sv[NB];
   };
@@ -172,81 +177,77 @@ struct MmaBody {
       for (int r = 0; r < 16; ++r) tot[i][nb][r] = __builtin_fmaf(cy.sv[nb], cy.acc[i][nb][r], tot[i][nb][r]);
   }
 
-  // The eight 16-k steps of one chunk (x buffer X, ring slot wc), except the last step's
-  // MFMAs, which `last` issues.  A step reads the next step's A fragments before its own
-  // MFMAs, so the LDS latency runs under them.  A group's first step adds the group
-  // before it to tot (one row block's 16 FMAs before each MFMA that overwrites those
-  // sums): the FMAs then run beside the matrix pipe and no group ends in a block of them.
-  // cneg[gi][nb] receives -s*(128+z) of the chunk's groups; hook(step) and issue(step) run
-  // in every step but the last, zero_point after step ZS: the offsets it needs are known,
-  // the chunk before's (SUMS) or this one's (after the last group's first step).  B receives
-  // the last step's operand.
+  // The eight 16-k steps of one chunk (x buffer X, ring slot wc).  A step reads the A
+  // fragments of the step D ahead before its own MFMAs, so the LDS latency runs under
+  // them; after step 7 - D every fragment of the chunk is in registers, the barrier runs
+  // and the next chunk's first D steps (x buffer Xn) are read.  A group's first step adds
+  // the group before it to tot (one row block's 16 FMAs before each MFMA that overwrites
+  // those sums): the FMAs then run beside the matrix pipe and no group ends in a block of
+  // them.  cneg[gi][nb] receives -s*(128+z) of the chunk's groups; hook(step) runs in
+  // every step, issue(step) in the steps up to the barrier, zero_point after step ZS: the
+  // offsets it needs are known, the chunk before's (SUMS) or this one's (after the last
+  // group's first step).
   static constexpr int ZS = SUMS || GPC == 1 ? 1 : 5;
-  template <typename F, typename I, typename Z>
-  static __device__ __forceinline__ void compute(const W& wc, const u32x4_t* X, int lane, const Lanes& ln, Carry& cy,
-                                                 f32x16_t (&tot)[MB][NB], float (&cneg)[GPC][NB], bf16x8_t (&B)[NB],
-                                                 F&& hook, I&& issue, Z&& zero_point) {
+  template <typename F, typename I, typename Z, typename R>
+  static __device__ __forceinline__ void compute(const W& wc, const u32x4_t* X, const u32x4_t* Xn, int lane,
+                                                 const Lanes& ln, Carry& cy, f32x16_t (&tot)[MB][NB],
+                                                 float (&cneg)[GPC][NB], F&& hook, I&& issue, Z&& zero_point,
+                                                 R&& barrier) {
     const f32x16_t zero = {};
+    bf16x8_t A[8][MB], An[D][MB];
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+#pragma unroll
+      for (int i = 0; i < MB; ++i) A[d][i] = cy.A[d][i];
     static_for<8>([&](auto sc) __attribute__((always_inline)) {
       constexpr int S = decltype(sc)::value;  // 16-k step within the chunk
       constexpr int gi = S / SPG;
       constexpr bool FIRST = S % SPG == 0;
-      bf16x8_t An[MB];
-      if constexpr (S + 1 < 8) {
+      if constexpr (S + D < 8) {
 #pragma unroll
-        for (int i = 0; i < MB; ++i) An[i] = read_a(X, ln, lane, i, S + 1);
+        for (int i = 0; i < MB; ++i) A[S + D][i] = read_a(X, ln, lane, i, S + D);
       }
+      bf16x8_t B[NB];
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) B[nb] = b_operand<BITS, S / 2>(wc.w[nb][S % 2]);
-      if constexpr (S + 1 < 8) {
 #pragma unroll
-        for (int i = 0; i < MB; ++i) {
-          if constexpr (FIRST) apply(cy, tot, i);
+      for (int i = 0; i < MB; ++i) {
+        if constexpr (FIRST) apply(cy, tot, i);
 #pragma unroll
-          for (int nb = 0; nb < NB; ++nb)
-            cy.acc[i][nb] =
-                __builtin_amdgcn_mfma_f32_32x32x16_bf16(cy.A[i], B[nb], FIRST ? zero : cy.acc[i][nb], 0, 0, 0);
-          if constexpr (FIRST) __builtin_amdgcn_sched_barrier(0);
-        }
+        for (int nb = 0; nb < NB; ++nb)
+          cy.acc[i][nb] =
+              __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[S][i], B[nb], FIRST ? zero : cy.acc[i][nb], 0, 0, 0);
+        if constexpr (FIRST) __builtin_amdgcn_sched_barrier(0);
+      }
+      issue(sc);
+      hook(sc);
+      if constexpr (FIRST) {
 #pragma unroll
-        for (int i = 0; i < MB; ++i) cy.A[i] = An[i];
-        issue(sc);
-        hook(sc);
-        if constexpr (FIRST) {
-#pragma unroll
-          for (int nb = 0; nb < NB; ++nb) {
-            cy.sv[nb] = half_bits_to_float(wc.s[gi][nb]);
-            const float z = half_bits_to_float(wc.z[gi][nb]);
-            cneg[gi][nb] = -(cy.sv[nb] * (kCodeBias + z));
-          }
-        }
-        // Keep each step's unpacking and the next step's reads next to its MFMAs:
-        // hoisting a whole chunk's worth of them costs more registers than two
-        // wavefronts per SIMD leave.
-        __builtin_amdgcn_sched_barrier(0);
-        if constexpr (S == ZS) {
-          zero_point();
-          __builtin_amdgcn_sched_barrier(0);
+        for (int nb = 0; nb < NB; ++nb) {
+          cy.sv[nb] = half_bits_to_float(wc.s[gi][nb]);
+          const float z = half_bits_to_float(wc.z[gi][nb]);
+          cneg[gi][nb] = -(cy.sv[nb] * (kCodeBias + z));
         }
       }
+      // Keep each step's unpacking and reads next to its MFMAs: hoisting a whole chunk's
+      // worth of them costs more registers than two wavefronts per SIMD leave.
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (S == ZS) {
+        zero_point();
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if constexpr (S == 7 - D) {
+        barrier();
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+#pragma unroll
+          for (int i = 0; i < MB; ++i) An[d][i] = read_a(Xn, ln, lane, i, d);
+      }
     });
-  }
-
-  // The last step's MFMAs of a chunk, and the first step's A fragments of the next one
-  // (x buffer Xn).
-  static __device__ __forceinline__ void last(const u32x4_t* Xn, int lane, const Lanes& ln, Carry& cy,
-                                              const bf16x8_t (&B)[NB]) {
-    bf16x8_t An[MB];
 #pragma unroll
-    for (int i = 0; i < MB; ++i) An[i] = read_a(Xn, ln, lane, i, 0);
+    for (int d = 0; d < D; ++d)
 #pragma unroll
-    for (int i = 0; i < MB; ++i)
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
-        cy.acc[i][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cy.A[i], B[nb], cy.acc[i][nb], 0, 0, 0);
-#pragma unroll
-    for (int i = 0; i < MB; ++i) cy.A[i] = An[i];
-    __builtin_amdgcn_sched_barrier(0);
+      for (int i = 0; i < MB; ++i) cy.A[d][i] = An[d][i];
   }
 
   // The sums of x over each group of a chunk (x buffer X), [group][row]: LPR lanes a row,
@@ -326,27 +327,27 @@ __device__ __forceinline__ void chunk_barrier() {
 // earlier; the only weight load issued before that copy and not yet needed is the one
 // for chunk c + 1 itself, so every weight load has XB - 1 chunks to arrive.
 // WAVES: wavefronts per workgroup, one 32-column block each (NB = 1).  TEAMS = 1: all
-// of them share the workgroup's x ring.  TEAMS = 2: two teams of four wavefronts on
-// the same four column blocks, each with an x ring of its own, take the first and the
-// second half of the workgroup's k-blocks, and add their sums through LDS in team
-// order at the end (twice the wavefronts per column group without more partial sums).
+// of them share the workgroup's x ring.  TEAMS > 1: teams of WAVES / TEAMS wavefronts on
+// the same column blocks, each with an x ring of its own, take consecutive parts of the
+// workgroup's k-blocks, and add their sums through LDS in team order at the end (more
+// wavefronts per column group without more partial sums).
 template <int BITS, int GROUP, int MB, int NB, int XB, int WAVES, int TEAMS>
 // Four wavefronts: two workgroups per CU (two wavefronts per SIMD) fit the LDS of a
 // two-chunk ring; a deeper ring takes one workgroup per CU and may use the SIMD's
 // whole register file.  Eight wavefronts: one workgroup per CU, two per SIMD.
 __global__ __launch_bounds__(WAVES * kWave)
-__attribute__((amdgpu_waves_per_eu(WAVES == 8 || XB <= 2 ? 2 : 1))) void k_qmma(QArgs a) {
+__attribute__((amdgpu_waves_per_eu(WAVES == 8 || XB <= 2 ? 2 : 1))) void k_qmma(QArgs args) {
+  const QArgs a = row_block(args);
   static_assert(XB % 2 == 0 && XB >= 2 && XB <= 6, "chunk parity (pairs of 128-k groups) follows the ring slot");
   static_assert(WAVES == 4 || WAVES == 8, "wavefronts per workgroup");
-  static_assert(TEAMS == 1 || (TEAMS == 2 && WAVES == 8 && (XB == 2 || XB == 4) && (MB == 2 || MB == 4) && NB == 1),
-                "two teams of four wavefronts with two-chunk rings");
+  static_assert(TEAMS == 1 || NB == 1, "teams of one column block per wavefront");
   constexpr int TW = WAVES / TEAMS;  // wavefronts per team (its column blocks)
   using Body = MmaBody<BITS, GROUP, MB, NB, TW>;
   constexpr int GPC = Body::GPC;
   constexpr bool SUMS = Body::SUMS;
   constexpr int XCH = Body::XCH;
   constexpr int PF = XB;
-  constexpr int SPREAD = 7;  // steps of a chunk that issue loads
+  constexpr int SPREAD = 8 - Body::D;  // steps of a chunk that issue loads: up to the barrier
   constexpr int NBUF = XB * TEAMS;  // LDS chunk buffers; team t uses [t * XB, t * XB + XB)
   static_assert(NBUF <= 8, "LDS chunk buffers");
   __shared__ u32x4_t xb0[XCH], xb1[XCH], xb2[NBUF > 2 ? XCH : 1], xb3[NBUF > 3 ? XCH : 1],
@@ -387,14 +388,13 @@ __attribute__((amdgpu_waves_per_eu(WAVES == 8 || XB <= 2 ? 2 : 1))) void k_qmma(
   const int r32 = lane & 31, hi = lane >> 5;
   const WorkItem wi(a);
   const int ng = wi.ng;
-  // The team's k-blocks: team 0 the first half of the workgroup's (rounded up), team 1
-  // the rest (possibly none).  Both run team 0's number of chunk steps, so that their
+  // The team's k-blocks: a TEAMS-th of the workgroup's (rounded up) each, the last ones
+  // the rest (possibly none).  All run team 0's number of chunk steps, so that their
   // barriers pair up; a team past its last chunk skips the arithmetic.
   const int nwg = wi.kb_end - wi.kb0;
-  const int h0 = TEAMS == 1 ? nwg : (nwg + 1) / 2;
-  const int kb0 = wi.kb0 + (team == 0 ? 0 : h0);
-  const int nchunks = team == 0 ? h0 : nwg - h0;
-  const int nsteps = h0;
+  const int nsteps = (nwg + TEAMS - 1) / TEAMS;
+  const int kb0 = wi.kb0 + team * nsteps;
+  const int nchunks = min(max(nwg - team * nsteps, 0), nsteps);
   const int last = nchunks - 1;
   const QBuffers bu(a, BITS, GROUP);
   // Block of the team's chunk c, held inside the workgroup's range: loads past the
@@ -462,7 +462,9 @@ __attribute__((amdgpu_waves_per_eu(WAVES == 8 || XB <= 2 ? 2 : 1))) void k_qmma(
     typename Body::Carry cy;
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
-      cy.A[i] = Body::read_a(ring(std::integral_constant<int, 0>{}), ln, lane, i, 0);
+#pragma unroll
+      for (int d = 0; d < Body::D; ++d)
+        cy.A[d][i] = Body::read_a(ring(std::integral_constant<int, 0>{}), ln, lane, i, d);
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) cy.acc[i][nb] = f32x16_t{};
     }
@@ -483,9 +485,8 @@ __attribute__((amdgpu_waves_per_eu(WAVES == 8 || XB <= 2 ? 2 : 1))) void k_qmma(
     // One chunk cc (ring slot U = cc % XB, parity U).  Its steps issue the loads of chunk
     // cc + XB - 1 into the ring slots of chunk cc - 1, a few per step: as one burst after
     // the barrier they stall every wavefront of the CU on the address units at once.
-    // Before the last step's MFMAs every A fragment of the chunk is in registers; the
-    // barrier there waits for chunk cc + 1 of x, whose first A fragments are read under
-    // those MFMAs.  Once a pair of groups is complete its zero-point term is added.
+    // Once every A fragment of the chunk is in registers the barrier waits for chunk
+    // cc + 1 of x.  Once a pair of groups is complete its zero-point term is added.
     auto step = [&](auto u, int cc) __attribute__((always_inline)) {
       constexpr int U = decltype(u)::value;
       constexpr int V = (U + XB - 1) % XB;
@@ -495,14 +496,15 @@ __attribute__((amdgpu_waves_per_eu(WAVES == 8 || XB <= 2 ? 2 : 1))) void k_qmma(
         constexpr int S = decltype(sc)::value;
         static_for<Body::PIECES>([&](auto pc) __attribute__((always_inline)) {
           constexpr int P = decltype(pc)::value;
-          constexpr int Q = XB > 2 ? P : (P + Body::PIECES - Body::DMA) % Body::PIECES;
           if constexpr (P * SPREAD / Body::PIECES == S)
-            Body::load_piece(Q, w[V], ring(std::integral_constant<int, V>{}),
+            Body::load_piece(P, w[V], ring(std::integral_constant<int, V>{}),
                              ring_xs(std::integral_constant<int, V>{}), bu, ln, a, kbn, tw);
         });
       };
       const bool active = TEAMS == 1 || cc < nchunks;
-      bf16x8_t B[NB];
+      auto barrier = [&]() __attribute__((always_inline)) {
+        chunk_barrier<(XB - 2) * Body::VM>();  // in flight: chunks cc + 2 .. cc + XB - 1
+      };
       if (active) {
         // Zero-point term: of this chunk (sums of x copied with it), or with SUMS of chunk
         // cc - 1, whose sums the barrier at its end made visible.
@@ -516,7 +518,7 @@ __attribute__((amdgpu_waves_per_eu(WAVES == 8 || XB <= 2 ? 2 : 1))) void k_qmma(
 #pragma unroll
         for (int i = 0; i < MB; ++i) xs[i] = X[(GPC == 2 ? hi * Body::ROWS : 0) + 32 * i + r32];
         typename Body::SumX sx;
-        Body::compute(w[U], ring(u), lane, ln, cy, tot, cneg, B, [&](auto sc) __attribute__((always_inline)) {
+        Body::compute(w[U], ring(u), ring(std::integral_constant<int, (U + 1) % XB>{}), lane, ln, cy, tot, cneg, [&](auto sc) __attribute__((always_inline)) {
           constexpr int S = decltype(sc)::value;
           if constexpr (SUMS) sx.template step<S>(ring(u), ring_xs(u), tw, lane);
         }, issue, [&]() __attribute__((always_inline)) {
@@ -540,16 +542,15 @@ __attribute__((amdgpu_waves_per_eu(WAVES == 8 || XB <= 2 ? 2 : 1))) void k_qmma(
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) cfirst[nb] = cz[0][nb];
           }
-        });
+        }, barrier);
 #pragma unroll
         for (int gi = 0; gi < GPC; ++gi)
 #pragma unroll
           for (int nb = 0; nb < NB; ++nb) cprev[gi][nb] = cneg[gi][nb];
       } else {
-        static_for<7>(issue);
+        static_for<SPREAD>(issue);
+        barrier();
       }
-      chunk_barrier<(XB - 2) * Body::VM>();  // in flight: chunks cc + 2 .. cc + XB - 1
-      if (active) Body::last(ring(std::integral_constant<int, (U + 1) % XB>{}), lane, ln, cy, B);
     };
     for (int c = 0; c < nsteps; c += XB)
       static_for<XB>([&](auto u) __attribute__((always_inline)) {
@@ -587,37 +588,37 @@ __attribute__((amdgpu_waves_per_eu(WAVES == 8 || XB <= 2 ? 2 : 1))) void k_qmma(
   if constexpr (TEAMS == 1) {
     run(std::integral_constant<int, 0>{});
   } else {
-    if (team == 0)
-      run(std::integral_constant<int, 0>{});
-    else
-      run(std::integral_constant<int, 1>{});
+    static_for<TEAMS>([&](auto tc) __attribute__((always_inline)) {
+      if (team == decltype(tc)::value) run(tc);
+    });
   }
-  if constexpr (TEAMS == 2) {
-    // Team 1 hands its sums to team 0 through the LDS of its ring (4 wavefronts x MB
-    // row blocks x 16 registers x 64 lanes, the size of two of its chunk buffers: each
-    // holds MB / 2 row blocks).  Copies into the rings issued past the last chunk may
-    // still be landing, so every wavefront first waits for its own.
+  if constexpr (TEAMS > 1) {
+    // The other teams hand their sums to team 0 through the LDS of their rings, RPB of a
+    // wavefront's 16 MB registers per chunk buffer.  Copies into the rings issued past the
+    // last chunk may still be landing, so every wavefront first waits for its own.
+    constexpr int RPB = XCH * 4 / (TW * kWave);
+    static_assert(RPB * XB >= 16 * MB && RPB > 0, "a team's sums fit its ring");
     __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
     __syncthreads();
-    constexpr int PER = MB / 2;  // row blocks per buffer
-    float* red0 = reinterpret_cast<float*>(lds(std::integral_constant<int, XB>{}));      // row blocks [0, PER)
-    float* red1 = reinterpret_cast<float*>(lds(std::integral_constant<int, XB + 1>{}));  // row blocks [PER, MB)
-    auto at = [&](int i, int r) __attribute__((always_inline)) {
-      return ((tw * PER + i % PER) * 16 + r) * kWave + lane;
-    };
-    if (team == 1) {
-#pragma unroll
-      for (int i = 0; i < MB; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) (i < PER ? red0 : red1)[at(i, r)] = tot[i][0][r];
-    }
+    static_for<TEAMS - 1>([&](auto uc) __attribute__((always_inline)) {
+      constexpr int T = decltype(uc)::value + 1;
+      if (team != T) return;
+      static_for<16 * MB>([&](auto ec) __attribute__((always_inline)) {
+        constexpr int E = decltype(ec)::value;
+        float* red = reinterpret_cast<float*>(lds(std::integral_constant<int, T * XB + E / RPB>{}));
+        red[(tw * RPB + E % RPB) * kWave + lane] = tot[E / 16][0][E % 16];
+      });
+    });
     __syncthreads();
-    if (team == 0) {
-#pragma unroll
-      for (int i = 0; i < MB; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) tot[i][0][r] += (i < PER ? red0 : red1)[at(i, r)];
-    }
+    if (team == 0)
+      static_for<TEAMS - 1>([&](auto uc) __attribute__((always_inline)) {
+        constexpr int T = decltype(uc)::value + 1;
+        static_for<16 * MB>([&](auto ec) __attribute__((always_inline)) {
+          constexpr int E = decltype(ec)::value;
+          const float* red = reinterpret_cast<const float*>(lds(std::integral_constant<int, T * XB + E / RPB>{}));
+          tot[E / 16][0][E % 16] += red[(tw * RPB + E % RPB) * kWave + lane];
+        });
+      });
   }
 
   // D layout of the 32x32 MFMA: lane l holds column l % 32 and, in register r, row

@@ -272,3 +272,41 @@ def test_qlinear_does_not_touch_outside_y():
         ss.subspec_qlinear_path(x, p["qweight"], p["scales"], p["zeros"], 4, 64, M, N, K, y, path)
         torch.cuda.synchronize()
         assert torch.all(guard[:4096] == -7) and torch.all(guard[4096 + M * N:] == -7)
+
+
+@pytest.mark.parametrize("M,N,K,bits,group", [
+    (128, 7168, 1152, 3, 128),   # 32-row blocks, K unsplit: nine k-blocks on two teams
+    (65, 528, 1024, 4, 64),      # a last row block of one row, columns past N
+    (97, 512, 128, 2, 128),      # one k-block: the second team has none
+    (128, 48, 384, 3, 64),       # fewer columns than a wavefront's block; three k-blocks
+    (33, 7168, 5120, 3, 128),    # up to M = 64: K split two or three ways
+    (64, 5120, 5120, 2, 64),
+    (40, 32768, 256, 4, 128),    # 64-row tiles from M = 33 on half-wide launches
+    (47, 32784, 640, 3, 64),
+    (100, 32784, 384, 4, 128),   # eight wavefronts at four row blocks, 4-bit
+    (128, 55296, 256, 4, 64),
+    (70, 49168, 384, 3, 64),
+])
+def test_qlinear_refined_launches(M, N, K, bits, group):
+    """Shapes whose automatic launch is a 32x32 form other than the described plan's:
+    against the oracle, and within the workspace the plan states."""
+    plan = ss.subspec_qlinear_plan(M, N, K, bits, group)
+    p = device_projection(torch.from_numpy(_w(N, K, 360, M, N, K, bits, group)).to(DEV), bits, group)
+    q, s16, z16 = p["codes"].cpu().numpy(), p["scales"].cpu().numpy(), p["zeros"].cpu().numpy()
+    x = synth.activations(M, K, 361, M, N, K)
+    if plan["workspace_bytes"]:
+        ss.subspec_reserve(plan["workspace_bytes"])
+    before = ss.subspec_workspace_info()["allocations"]
+    cols = np.unique(np.r_[0:min(N, 512), max(0, N - 512):N])  # the first and last column groups
+    y_ref = oracle.qlinear_ref(synth.bf16_bits(x), q[cols], s16[:, cols], z16[:, cols], group)
+    first = None
+    for _ in range(2):
+        y = run_qlinear(p, x.to(DEV))
+        assert_close(bf16_to_f64(y)[:, cols], y_ref, f"M={M} N={N} K={K} bits={bits} g={group} plan={plan}")
+        assert first is None or torch.equal(first, y)
+        first = y
+    # every column against the 16x16x32 kernel on the same operands (each output within
+    # one bf16 rounding of the same sum: 2^-8 relative, and fp32 sums of K terms)
+    other = run_qlinear(p, x.to(DEV), ss.SUBSPEC_PATH_MFMA16)
+    assert_close(bf16_to_f64(y), bf16_to_f64(other), "against 16x16x32 tiles")
+    assert ss.subspec_workspace_info()["allocations"] <= before + 1
