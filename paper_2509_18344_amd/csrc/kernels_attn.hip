@@ -20,6 +20,19 @@
 //                      MFMAs each, so the probabilities keep 16 significant bits;
 //                      P is already in the B-operand layout in registers
 // and writes its unnormalised partial output with the running maximum and sum.
+// Kernel 1 for long ranges (k_attn_stream, eight tiles and more): its eight wavefronts take
+// the tiles in turn, each for up to two tiles of query rows (with more than 32 rows two
+// wavefronts share a key tile).  A wavefront keeps its own running maximum, sum and
+// output, so the loop has no barrier: keys go from memory straight into the A-operand
+// layout, values through a corner of LDS of its own that transposes them, and the next
+// tile is loaded under the current one's softmax and P.V.  At the end the wavefronts'
+// outputs are scaled to the workgroup's maximum and added in wavefront order.  Measured:
+// 16450 keys of eight heads, M = 6 (17 tiles a range) 27.7 us in k_attn_partial (2.4 TB/s,
+// bound by a barrier and one tile's computation after the other) against 18.4, 4180 keys
+// of 16 heads (9 tiles) 23.0 against 20.4 a call; 8480 keys of four heads (5 tiles) 21.0
+// against 23.3 and 2336 (3 tiles) 14.1 against 16.8, where the merge costs more than the
+// tiles.
+//
 // Kernel 2 (k_attn_combine): one workgroup per (token, query head) combines the
 // ranges in a fixed order and writes bf16; it also appends the new keys and values
 // to the cache (after kernel 1, so nothing in this call reads a slot it writes).
@@ -259,12 +272,250 @@ __global__ __launch_bounds__(kAttnThreads) void k_attn_partial(AttnArgs a) {
   }
 }
 
-// One workgroup per (token i, query head h), one thread per dimension.  Each range's
-// (max, sum) pair is read once into LDS and turned into a weight; the partial
-// outputs are then read in batches of independent loads and summed in range order.
+constexpr int kStreamWaves = 8;
+constexpr int kStreamThreads = kStreamWaves * kWave;
+constexpr int kStreamTiles = 8;        // tiles per range from which k_attn_stream is taken
+constexpr int kMergeRow = kAttnD + 4;  // floats per query row of a wavefront's merged output
+
+union alignas(16) WaveLds {
+  uint16_t vt[kAttnD][kVRow];  // a wavefront's values, transposed
+  float o[16][kMergeRow];      // its output of one query tile
+};
+
+struct StreamLds {
+  WaveLds w[kStreamWaves];
+  float m[kStreamWaves][32], l[kStreamWaves][32];  // its maxima and sums per query row
+  alignas(16) uint32_t mask[kAttnMaskWords];
+};
+
+// One lane's share of a tile.  Keys: A-operand fragments, key 16u + lane % 16, dimensions
+// 32j + 8 (lane / 16) .. + 7.  Values: keys 2 (lane % 16) + h, dimensions
+// 32j + 8 (lane / 16) .. + 7.
+struct StreamRegs {
+  uint4 k[2][4];
+  uint4 v[4][2];
+};
+
+__device__ __forceinline__ void stream_load(const AttnArgs& a, int g, int key0, int key_end, int lane, StreamRegs& r) {
+  const int col = lane & 15, d0 = 8 * (lane >> 4);
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    // keys past the range repeat its last one (masked below)
+    const uint16_t* row = key_row(a, a.k_cache, a.k_new, g, min(key0 + 16 * u + col, key_end - 1)) + d0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) r.k[u][j] = *reinterpret_cast<const uint4*>(row + 32 * j);
+  }
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const uint16_t* row = key_row(a, a.v_cache, a.v_new, g, min(key0 + 2 * col + h, key_end - 1)) + d0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) r.v[j][h] = *reinterpret_cast<const uint4*>(row + 32 * j);
+  }
+}
+
+__device__ __forceinline__ void store_values(uint16_t (&vt)[kAttnD][kVRow], const StreamRegs& r, int lane) {
+  // two keys (adjacent slots) of one dimension per 32-bit word
+  const int slot = value_slot(2 * (lane & 15));
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int d0 = 32 * j + 8 * (lane >> 4);
+    const uint32_t a0[4] = {r.v[j][0].x, r.v[j][0].y, r.v[j][0].z, r.v[j][0].w};
+    const uint32_t a1[4] = {r.v[j][1].x, r.v[j][1].y, r.v[j][1].z, r.v[j][1].w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const uint32_t lo = __builtin_amdgcn_perm(a1[e], a0[e], 0x05040100u);  // dimension 2e: key, key + 1
+      const uint32_t hi = __builtin_amdgcn_perm(a1[e], a0[e], 0x07060302u);  // dimension 2e + 1
+      *reinterpret_cast<uint32_t*>(&vt[d0 + 2 * e][slot]) = lo;
+      *reinterpret_cast<uint32_t*>(&vt[d0 + 2 * e + 1][slot]) = hi;
+    }
+  }
+}
+
+// QT: query tiles of 16 rows (1 .. 4); a wavefront takes QW of them.
+template <int QT>
+__global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_attn_stream(AttnArgs a) {
+  constexpr int QW = QT < 2 ? 1 : 2;
+  constexpr int QG = (QT + 1) / 2;            // wavefronts that share a key tile
+  constexpr int KW = kStreamWaves / QG;         // key tiles at a time
+  __shared__ StreamLds L;
+  const int s = blockIdx.x, g = blockIdx.y;
+  const int lane = threadIdx.x % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x / kWave));
+  const int qg = wave % QG, kw = wave / QG;
+  const int col = lane & 15, quarter = lane >> 4;
+  const int G = a.Hq / a.Hkv;
+  const int rows = G * a.M;
+  const int Ltot = a.P + a.T + a.M;
+  const int k_begin = s * a.tiles_per_split * kAttnTile;
+  const int k_end = min(Ltot, k_begin + a.tiles_per_split * kAttnTile);
+  const int ntiles = (k_end - k_begin + kAttnTile - 1) / kAttnTile;
+
+  StreamRegs r;
+  if (kw < ntiles) stream_load(a, g, k_begin + kw * kAttnTile, k_end, lane, r);
+
+  // this lane's query row in each of the wavefront's query tiles, and its fragments of q
+  bool live[QW];
+  int qi[QW];
+  bf16x8_t qf[QW][4];
+#pragma unroll
+  for (int t = 0; t < QW; ++t) {
+    const int row = 16 * (QW * qg + t) + col;
+    live[t] = row < rows;
+    qi[t] = live[t] ? row % a.M : 0;
+    const int hl = live[t] ? row / a.M : 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      uint4 w = make_uint4(0, 0, 0, 0);
+      if (live[t])
+        w = *reinterpret_cast<const uint4*>(a.q + (static_cast<size_t>(qi[t]) * a.Hq + g * G + hl) * kAttnD + 32 * j +
+                                            8 * quarter);
+      qf[t][j] = __builtin_bit_cast(bf16x8_t, w);
+    }
+  }
+  for (int w = threadIdx.x; w < a.M * a.W; w += kStreamThreads) L.mask[w] = a.mask[w];
+  __syncthreads();
+
+  float m[QW], lsum[QW];
+  f32x4_t o[QW][8];
+#pragma unroll
+  for (int t = 0; t < QW; ++t) {
+    m[t] = -INFINITY;
+    lsum[t] = 0.f;
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) o[t][dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  }
+  auto& vt = L.w[wave].vt;
+  for (int n = kw; n < ntiles; n += KW) {
+    store_values(vt, r, lane);
+    // S^T = K Q^T: lane holds keys 16u + 4 quarter + r of its query
+    f32x4_t st[QW][2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const bf16x8_t kf = __builtin_bit_cast(bf16x8_t, r.k[u][j]);
+#pragma unroll
+        for (int t = 0; t < QW; ++t)
+          st[t][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[t][j], j == 0 ? f32x4_t{0.f, 0.f, 0.f, 0.f} : st[t][u],
+                                                             0, 0, 0);
+      }
+    const int key0 = k_begin + n * kAttnTile;
+    if (n + KW < ntiles) stream_load(a, g, k_begin + (n + KW) * kAttnTile, k_end, lane, r);
+    bf16x8_t pfh[QW], pfl[QW];
+#pragma unroll
+    for (int t = 0; t < QW; ++t) {
+      // scale, mask (committed positions are always visible), online softmax
+      const uint32_t vis = live[t] ? tile_visibility(&L.mask[qi[t] * a.W], a.W, a.P, key0, k_end) : 0u;
+      float sv[2][4];
+      float mx = -INFINITY;
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const bool ok = (vis >> (16 * u + 4 * quarter + e)) & 1u;
+          const float sc = st[t][u][e];
+          sv[u][e] = ok ? sc * a.scale_log2 : -INFINITY;
+          mx = fmaxf(mx, sv[u][e]);
+        }
+      mx = fmaxf(mx, __shfl_xor(mx, 16));
+      mx = fmaxf(mx, __shfl_xor(mx, 32));
+      const float mn = fmaxf(m[t], mx);
+      // raw 2^x (a probability below 2^-126 flushing to zero does not matter)
+      const float alpha = m[t] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m[t] - mn);
+      // p = hi + lo in bf16; the same two terms feed P.V and the sum
+      uint32_t ph[4], pl[4];
+      float add = 0.f;
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; e += 2) {
+          const float p0 = sv[u][e] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sv[u][e] - mn);
+          const float p1 = sv[u][e + 1] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sv[u][e + 1] - mn);
+          const uint32_t h = pack_bf16(p0, p1);
+          const uint32_t l = pack_bf16(p0 - bf16_lo(h), p1 - bf16_hi(h));
+          ph[2 * u + e / 2] = h;
+          pl[2 * u + e / 2] = l;
+          add += (bf16_lo(h) + bf16_lo(l)) + (bf16_hi(h) + bf16_hi(l));
+        }
+      lsum[t] = lsum[t] * alpha + add;
+      m[t] = mn;
+      pfh[t] = __builtin_bit_cast(bf16x8_t, make_uint4(ph[0], ph[1], ph[2], ph[3]));
+      pfl[t] = __builtin_bit_cast(bf16x8_t, make_uint4(pl[0], pl[1], pl[2], pl[3]));
+      if (__builtin_amdgcn_ballot_w64(alpha != 1.f)) {  // some row's maximum moved
+#pragma unroll
+        for (int dt = 0; dt < 8; ++dt) o[t][dt] *= alpha;
+      }
+    }
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) {
+      const bf16x8_t vf = *reinterpret_cast<const bf16x8_t*>(&vt[16 * dt + col][8 * quarter]);
+#pragma unroll
+      for (int t = 0; t < QW; ++t) {
+        o[t][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pfh[t], o[t][dt], 0, 0, 0);
+        o[t][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pfl[t], o[t][dt], 0, 0, 0);
+      }
+    }
+  }
+
+  // The workgroup's maximum per row; every wavefront scales its output and sum to it.
+#pragma unroll
+  for (int t = 0; t < QW; ++t) {
+    // the four quarters hold partial sums of the same query
+    lsum[t] += __shfl_xor(lsum[t], 16);
+    lsum[t] += __shfl_xor(lsum[t], 32);
+    if (quarter == 0) L.m[wave][16 * t + col] = m[t];
+  }
+  __syncthreads();
+  float mall[QW];
+#pragma unroll
+  for (int t = 0; t < QW; ++t) {
+    mall[t] = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < KW; ++w) mall[t] = fmaxf(mall[t], L.m[w * QG + qg][16 * t + col]);
+    const float sc = m[t] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m[t] - mall[t]);
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) o[t][dt] *= sc;
+    if (quarter == 0) L.l[wave][16 * t + col] = lsum[t] * sc;
+  }
+  // One query tile of every wavefront at a time: outputs [row][dimension] in LDS, then the
+  // workgroup adds the wavefronts' in order, four dimensions a thread.
+#pragma unroll
+  for (int t = 0; t < QW; ++t) {
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt)
+      *reinterpret_cast<f32x4_t*>(&L.w[wave].o[col][16 * dt + 4 * quarter]) = o[t][dt];
+    __syncthreads();
+    for (int i = threadIdx.x; i < QG * 16 * (kAttnD / 4); i += kStreamThreads) {
+      const int qw = i / (16 * (kAttnD / 4)), rr = i / (kAttnD / 4) % 16, d4 = 4 * (i % (kAttnD / 4));
+      const int row = 16 * (QW * qw + t) + rr;
+      if (row >= rows) continue;  // padding rows are never read
+      f32x4_t sum = *reinterpret_cast<const f32x4_t*>(&L.w[qw].o[rr][d4]);
+#pragma unroll
+      for (int w = 1; w < KW; ++w) sum += *reinterpret_cast<const f32x4_t*>(&L.w[w * QG + qw].o[rr][d4]);
+      const size_t base = (static_cast<size_t>(g) * a.splits + s) * a.rows_pad + row;
+      *reinterpret_cast<f32x4_t*>(a.part_o + base * kAttnD + d4) = sum;
+      if (d4 == 0) {
+        float mm = -INFINITY, ls = 0.f;
+#pragma unroll
+        for (int w = 0; w < KW; ++w) {
+          mm = fmaxf(mm, L.m[w * QG + qw][16 * t + rr]);
+          ls += L.l[w * QG + qw][16 * t + rr];
+        }
+        a.part_ml[2 * base] = mm;
+        a.part_ml[2 * base + 1] = ls;
+      }
+    }
+    if (t + 1 < QW) __syncthreads();
+  }
+}
+
+// One workgroup per (token i, query head h), one thread per dimension.  The first kBatch
+// ranges' outputs are requested together with the (max, sum) pairs, so the usual call waits
+// for memory once; each pair is turned into a weight by one thread, and the outputs are
+// summed in range order.
 __global__ __launch_bounds__(kAttnD) void k_attn_combine(AttnArgs a) {
   __shared__ float sm[kAttnMaxSplits], sl[kAttnMaxSplits];
-  constexpr int kBatch = 16;
+  constexpr int kBatch = 32;
   const int i = blockIdx.x / a.Hq, h = blockIdx.x % a.Hq;
   const int d = threadIdx.x;
   const int G = a.Hq / a.Hkv;
@@ -272,11 +523,16 @@ __global__ __launch_bounds__(kAttnD) void k_attn_combine(AttnArgs a) {
   const int row = hl * a.M + i;
   const int ns = a.splits;
   const size_t base = static_cast<size_t>(g) * ns * a.rows_pad + row;
+  const float* po = a.part_o + base * kAttnD + d;
+  const size_t step = static_cast<size_t>(a.rows_pad) * kAttnD;
   for (int s = d; s < ns; s += kAttnD) {
-    const size_t b = base + static_cast<size_t>(s) * a.rows_pad;
-    sm[s] = a.part_ml[2 * b];
-    sl[s] = a.part_ml[2 * b + 1];
+    const float2 ml = *reinterpret_cast<const float2*>(a.part_ml + 2 * (base + static_cast<size_t>(s) * a.rows_pad));
+    sm[s] = ml.x;
+    sl[s] = ml.y;
   }
+  float v[kBatch];
+#pragma unroll
+  for (int u = 0; u < kBatch; ++u) v[u] = u < ns ? po[u * step] : 0.f;
   __syncthreads();
   float mmax = -INFINITY;
   for (int s = 0; s < ns; ++s) mmax = fmaxf(mmax, sm[s]);
@@ -285,10 +541,10 @@ __global__ __launch_bounds__(kAttnD) void k_attn_combine(AttnArgs a) {
   __syncthreads();
   float den = 0.f, num = 0.f;
   for (int s0 = 0; s0 < ns; s0 += kBatch) {
-    float v[kBatch];
+    if (s0 > 0) {
 #pragma unroll
-    for (int u = 0; u < kBatch; ++u)
-      v[u] = s0 + u < ns ? a.part_o[(base + static_cast<size_t>(s0 + u) * a.rows_pad) * kAttnD + d] : 0.f;
+      for (int u = 0; u < kBatch; ++u) v[u] = s0 + u < ns ? po[(s0 + u) * step] : 0.f;
+    }
 #pragma unroll
     for (int u = 0; u < kBatch; ++u)
       if (s0 + u < ns) {
@@ -334,8 +590,15 @@ size_t attn_workspace_bytes(int M, int Hq, int Hkv, int P, int T) {
 }
 
 hipError_t launch_tree_attention(const AttnArgs& a, hipStream_t st) {
-  const dim3 grid(a.splits, a.Hkv), block(kAttnThreads);
-  switch (a.rows_pad / 16) {
+  const dim3 grid(a.splits, a.Hkv), block(kAttnThreads), wide(kStreamThreads);
+  const bool stream = a.tiles_per_split >= kStreamTiles;
+  if (stream) switch (a.rows_pad / 16) {
+    case 1: hipLaunchKernelGGL(k_attn_stream<1>, grid, wide, 0, st, a); break;
+    case 2: hipLaunchKernelGGL(k_attn_stream<2>, grid, wide, 0, st, a); break;
+    case 3: hipLaunchKernelGGL(k_attn_stream<3>, grid, wide, 0, st, a); break;
+    default: hipLaunchKernelGGL(k_attn_stream<4>, grid, wide, 0, st, a); break;
+  }
+  else switch (a.rows_pad / 16) {
     case 1: hipLaunchKernelGGL(k_attn_partial<1>, grid, block, 0, st, a); break;
     case 2: hipLaunchKernelGGL(k_attn_partial<2>, grid, block, 0, st, a); break;
     case 3: hipLaunchKernelGGL(k_attn_partial<3>, grid, block, 0, st, a); break;

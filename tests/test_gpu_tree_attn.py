@@ -78,6 +78,19 @@ def test_tree_attention_matches_oracle(M, Hq, Hkv, P, T, k, qs):
     _check(M, Hq, Hkv, P, T, k, 7 * P + T + M, q_scale=qs, what=f"M={M} Hq={Hq} Hkv={Hkv} P={P} T={T}")
 
 
+@pytest.mark.parametrize("M,Hq,Hkv,P,T", [
+    (1, 16, 16, 4150, 0),    # one query tile; 8 tiles a range, as many as wavefronts
+    (5, 80, 16, 4097, 37),   # two; ragged ranges, a tile across the prefix's end
+    (6, 112, 16, 4700, 282),  # three: two wavefronts share a key tile
+    (8, 128, 16, 4224, 96),  # four full ones
+    (9, 56, 8, 16500, 5),    # 17 tiles a range: several rounds per wavefront
+])
+def test_tree_attention_long_ranges(M, Hq, Hkv, P, T):
+    """Ranges of eight tiles and more: one wavefront per key tile, merged at the end."""
+    assert ss.subspec_tree_attention_plan(M, Hq, Hkv, P, T)[1] >= 8
+    _check(M, Hq, Hkv, P, T, 6, 11 * P + T + M, q_scale=1.5, S=P + T + M, what=f"long M={M} Hq={Hq} Hkv={Hkv} P={P} T={T}")
+
+
 def test_tree_attention_query_without_visible_keys_gets_zeros():
     M, Hq, Hkv, P, T = 2, 4, 2, 0, 3
     mask = np.zeros((M, 1), np.uint32)
