@@ -5,6 +5,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_NAME = "libsubspec.so"
@@ -75,8 +76,8 @@ def load_library():
         "subspec_reserve": (I, [S]),
         "subspec_workspace_info": (I, [ctypes.POINTER(ctypes.c_size_t), ctypes.POINTER(ctypes.c_int),
                                        ctypes.POINTER(ctypes.c_ulonglong)]),
-        "subspec_stack_forward": (I, [ctypes.POINTER(SubspecProj), I, I, I, I, P]),
-        "subspec_stack_capture": (I, [ctypes.POINTER(SubspecProj), I, I, I, I, P,
+        "subspec_stack_forward": (I, [P, I, I, I, I, P]),
+        "subspec_stack_capture": (I, [P, I, I, I, I, P,
                                       ctypes.POINTER(ctypes.c_void_p)]),
         "subspec_graph_launch": (I, [P, P]),
         "subspec_graph_destroy": (I, [P]),
@@ -103,21 +104,33 @@ def load_library():
 
 def _ptr(t):
     """Data pointer of a torch tensor / numpy array, or an int address, or None."""
+    try:  # a tensor, the usual argument
+        return t.data_ptr()
+    except AttributeError:
+        pass
     if t is None:
         return None
     if isinstance(t, int):
         return t
-    if hasattr(t, "data_ptr"):
-        return t.data_ptr()
     if hasattr(t, "ctypes"):
         return t.ctypes.data
     raise TypeError(f"cannot take the address of {type(t)}")
 
 
+_torch = None
+
+
 def _stream(s):
     if s is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        global _torch
+        if _torch is None:
+            import torch as _torch
+        # The current stream's handle without a Stream object around it: a projection of
+        # a few microseconds is bound by this marshalling (7.9 us per eager call of a
+        # 512 x 256 projection with the object and a ctypes structure per field).
+        if _torch.cuda.is_initialized():
+            return _torch._C._cuda_getCurrentRawStream(_torch._C._cuda_getDevice())
+        return _torch.cuda.current_stream().cuda_stream
     if isinstance(s, int):
         return s
     return s.cuda_stream
@@ -201,9 +214,18 @@ def subspec_workspace_info() -> dict:
     return {"bytes": int(b.value), "retired": int(r.value), "allocations": int(a.value)}
 
 
+_PROJ_PACK = struct.Struct("@5P2i").pack  # the layout of SubspecProj
+
+
 def _projs(projs):
-    """A ctypes array of subspec_proj from dicts with keys x, qweight, scales, zeros,
+    """The bytes of an array of subspec_proj from dicts with keys x, qweight, scales, zeros,
     y, N, K (tensors or addresses)."""
+    try:  # the structures' bytes in one go
+        return b"".join([_PROJ_PACK(
+            _ptr(p["x"]) or 0, _ptr(p["qweight"]) or 0, _ptr(p["scales"]) or 0, _ptr(p["zeros"]) or 0,
+            _ptr(p["y"]) or 0, int(p["N"]), int(p["K"])) for p in projs])
+    except struct.error:  # a value outside its C type: ctypes' own conversion
+        pass
     arr = (SubspecProj * len(projs))()
     for i, p in enumerate(projs):
         arr[i] = SubspecProj(_ptr(p["x"]), _ptr(p["qweight"]), _ptr(p["scales"]), _ptr(p["zeros"]),
