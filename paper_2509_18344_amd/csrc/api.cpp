@@ -20,6 +20,7 @@
 #include "kernels_tree.h"
 #include "kernels_attn.h"
 #include "kernels_hqq.h"
+#include "kernels_qstream.h"
 
 namespace {
 
@@ -99,6 +100,7 @@ struct Tuning {
   int mma8_half_min_m = 48;       // the same where 256-column groups cover only half the CUs
   int mma_teams = 0;              // 32x32 kernel, long-K launches: 1 = one team, 2 = two; 0 = choose
   int teams64_min_m = 33;         // long-K launches from this M up to 64: 64-row two-team 32x32 tiles
+  int stream_nt = 0, stream_ks = 0;  // small-batch kernel: tiles and wavefronts per workgroup; 0 = choose, -1 = never
   int rb_splits = 0;              // 32-row 32x32 tiles: splits of K; 0 = choose, -1 = not these tiles
   int row_split = 0;              // 16x16x32 tiles: 1 = two row blocks where possible, 2 = never; 0 = choose
 };
@@ -140,6 +142,8 @@ const Tuning& tuning() {
         else if (k == "mma8_min_m") r.mma8_min_m = v;
         else if (k == "mma8_half_min_m") r.mma8_half_min_m = v;
         else if (k == "mma_teams") r.mma_teams = v;
+        else if (k == "stream_nt") r.stream_nt = v;
+        else if (k == "stream_ks") r.stream_ks = v;
         else if (k == "rb_splits") r.rb_splits = v;
         else if (k == "row_split") r.row_split = v;
         else if (k == "teams64_min_m") r.teams64_min_m = v;
@@ -711,6 +715,46 @@ void pack_host(const uint8_t* codes, int N, int K, uint8_t* out) {
       }
 }
 
+// Whether an automatic call takes the small-batch kernel (k_qstream), and its tiles and
+// wavefronts per workgroup.  It replaces launches that would split K across workgroups: at
+// a few megabytes of weights their completion (three trips to the coherent level in a
+// row) costs as much as the weights.  us per call, the described launch against this one,
+// 4-bit g128, one run: 1024x1024 M = 1 5.3 / 2.8, M = 16 5.8 / 3.5; 8192x1024 M = 6 7.0 / 4.1;
+// 4608x3584 M = 1 7.7 / 5.0, M = 6 8.4 / 5.6, M = 16 8.9 / 7.2; 7168x5120 M = 1 8.9 / 7.0, M = 8
+// 9.8 / 7.9; 12288x4096 M = 6 11.3 / 10.1; 2048x8192 M = 6 10.5 / 8.1.  Where the lines lie:
+//  - every pair of tiles reads the fragments of x from the L2 again, M * K * 2 bytes: from
+//    M = 9 that is more than the weights, and only a K of up to 36 blocks still gains
+//    (5120x5120 M = 16 9.8 / 9.8, 16384x512 M = 12 6.6 / 7.2; 256x4096, sixteen tiles, 6.2 / 6.3);
+//  - 16 wavefronts fill a CU: one workgroup per CU, or at least half as many again
+//    (10240x4096, 320 pairs, M = 1 9.0 / 9.2; 14000x3584, 438 pairs, 9.9 / 9.1); of eight two
+//    (22000x2048 8.5 / 8.6);
+//  - launches of more weights have enough column groups or blocks per workgroup to hide
+//    the completion (3584x18944 M = 1 12.1 / 12.4, 37888x3584 14.3 / 18.2);
+//  - a K of one or two blocks is not split anyway (512x256 M = 8 2.9 / 2.8, M = 16 2.9 / 3.3;
+//    29200x256 M = 1 4.1 / 6.3).
+bool stream_choice(int M, int N, int K, int* nt, int* ks) {
+  const Tuning& tu = tuning();
+  if (M > subspec::kStreamMaxRows || tu.stream_nt < 0) return false;
+  if (tu.stream_nt) {
+    *nt = tu.stream_nt;
+    *ks = tu.stream_ks;
+    return true;
+  }
+  const int KB = K / subspec::kTileK, tiles = N / subspec::kTileN, pairs = (tiles + 1) / 2;
+  const double mweights = static_cast<double>(N) * K / (1 << 20);
+  if (KB <= 8 || (KB < 24 && tiles <= 32)) {
+    *nt = 1;
+    *ks = 4;
+    if (KB <= 2) return M <= 8 && tiles <= 64;
+    return mweights <= 8 && (M <= 8 || tiles <= 512);
+  }
+  *nt = 2;
+  *ks = KB < 24 ? 8 : 16;
+  if (KB > 64 || mweights > 48) return false;
+  if (M > 8) return KB <= 36 && (KB < 24 || tiles >= 64) && mweights <= 18;
+  return KB < 24 ? pairs <= 2 * device_cus() : pairs <= device_cus() || 2 * pairs >= 3 * device_cus();
+}
+
 // noalloc: take the scratch from the library's fixed per-device array (no allocation,
 // splits capped to its size) instead of the growable workspace.
 int qlinear_impl(const void* x, const void* qweight, const void* scales, const void* zeros,
@@ -742,6 +786,11 @@ int qlinear_impl(const void* x, const void* qweight, const void* scales, const v
   if (kc.row_blocks > 1) {
     a.rb_rows = kc.rows;
     a.rb_counters = p.col_groups;
+  }
+  int snt = 0, sks = 0;
+  if (path == SUBSPEC_PATH_AUTO && stream_choice(M, N, K, &snt, &sks)) {
+    const hipError_t e = subspec::launch_qstream(snt, sks, bits, group, a, st);
+    return e == hipSuccess ? SUBSPEC_OK : hip_fail(e, "qlinear launch");
   }
   if (p.workspace_bytes) {
     void* ws = nullptr;

@@ -1,0 +1,170 @@
+// The substitute-layer linear y = x * dequant(q, s, z)^T (SubSpec Sec. 4.1) for draft
+// batches of up to 16 tree tokens (k_qstream): the weight stream is all the work there,
+// so a workgroup takes NT tiles of 16 columns over the whole of K and its KS wavefronts
+// take the 128-k blocks in turn (wavefront w blocks w, w + KS, ...).  Nothing is shared
+// until the end: no activations staged in LDS, no barrier in the loop and no partial sums
+// in memory, whose completion (stores acknowledged, counter, reads by the last workgroup)
+// is three trips to the coherent level in a row.  The wavefronts' sums meet once in LDS.
+//
+// One block: 16x16x32 bf16 MFMAs, A = x fragments loaded from memory straight into the
+// operand layout (x is small and stays in the L2; rows past M are outside the buffer
+// resource and read zeros without traffic), B = unpacked codes 128 + q, and one more MFMA
+// per step with B = 1 for the group's sum of x, which lands in the accumulator's layout:
+//     tot += s * ( sum x (128+q) - (128+z) * sum x ).
+// The weights, scales and activations of PF blocks are in flight per wavefront.
+//
+// Neighbouring column groups share cache lines of the scales (a line holds 64 columns),
+// so the grid is dealt to the eight XCDs in contiguous runs of column groups.
+//
+// What bounds it: the latency of the launch, of one or two rounds of loads per wavefront
+// and of the meeting in LDS (4608x3584 4-bit, 8.8 MB: 7.7 us split across workgroups with
+// its completion, 5.0 here, against some 3.2 for an empty launch and the bytes), and with
+// more rows the loads of x fragments, four per block.
+#include "kernels_qstream.h"
+#include "qlinear_device.h"
+
+namespace subspec {
+
+namespace {
+
+constexpr int kXcds = 8;
+
+template <int BITS, int GROUP, int NT, int KS, int PF>
+struct StreamBody {
+  static constexpr int GPB = kTileK / GROUP;  // groups per block
+  static constexpr int SPG = 4 / GPB;         // 32-k steps per group
+  struct Ring {
+    Slice<BITS> w[NT];
+    uint16_t s[GPB][NT], z[GPB][NT];
+    bf16x8_t a[4];
+  };
+
+  static __device__ __forceinline__ void load(Ring& r, const QBuffers& bu, int N, const uint32_t (&wofs)[NT],
+                                              const uint32_t (&szofs)[NT], uint32_t xofs, int kb) {
+#pragma unroll
+    for (int t = 0; t < NT; ++t) r.w[t] = load_slice<BITS>(bu.w, wofs[t] + static_cast<uint32_t>(kb) * (256 * BITS));
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      r.a[j] = __builtin_bit_cast(bf16x8_t, __builtin_amdgcn_raw_buffer_load_b128(bu.x, xofs + 64 * j, kb * (kTileK * 2), 0));
+#pragma unroll
+    for (int gi = 0; gi < GPB; ++gi) {
+      const uint32_t soff = static_cast<uint32_t>(kb * GPB + gi) * N * 2;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        r.s[gi][t] = __builtin_amdgcn_raw_buffer_load_b16(bu.s, szofs[t], soff, 0);
+        r.z[gi][t] = __builtin_amdgcn_raw_buffer_load_b16(bu.z, szofs[t], soff, 0);
+      }
+    }
+  }
+
+  static __device__ __forceinline__ void compute(const Ring& r, f32x4_t (&tot)[NT]) {
+    const bf16x8_t ones = __builtin_bit_cast(bf16x8_t, make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u));
+    const f32x4_t zero = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    static_for<GPB>([&](auto gc) __attribute__((always_inline)) {
+      constexpr int gi = decltype(gc)::value;
+      f32x4_t acc[NT], accx;
+      static_for<SPG>([&](auto sc) __attribute__((always_inline)) {
+        constexpr int js = decltype(sc)::value, j = gi * SPG + js;
+        accx = __builtin_amdgcn_mfma_f32_16x16x32_bf16(r.a[j], ones, js == 0 ? zero : accx, 0, 0, 0);
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+          acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(r.a[j], b_operand<BITS, j>(r.w[t]), js == 0 ? zero : acc[t], 0, 0, 0);
+      });
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const float s = half_bits_to_float(r.s[gi][t]);
+        const float nz = -(kCodeBias + half_bits_to_float(r.z[gi][t]));
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          tot[t][e] = __builtin_fmaf(s, __builtin_fmaf(nz, accx[e], acc[t][e]), tot[t][e]);
+      }
+    });
+  }
+};
+
+template <int BITS, int GROUP, int NT, int KS, int PF>
+__global__ __launch_bounds__(KS * kWave) void k_qstream(QArgs a) {
+  using Body = StreamBody<BITS, GROUP, NT, KS, PF>;
+  __shared__ float red[KS][NT * 4][kWave];
+  const int lane = threadIdx.x % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x / kWave));
+  const int groups = (a.n_tiles + NT - 1) / NT;
+  // XCD x (workgroups x, x + 8, ...) takes groups [x * per, x * per + per).
+  const int per = (groups + kXcds - 1) / kXcds;
+  const int ng = static_cast<int>(blockIdx.x % kXcds) * per + static_cast<int>(blockIdx.x / kXcds);
+  if (ng >= groups || static_cast<int>(blockIdx.x / kXcds) >= per) return;  // the whole workgroup
+  const QBuffers bu(a, BITS, GROUP);
+
+  uint32_t wofs[NT], szofs[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const int nt = min(ng * NT + t, a.n_tiles - 1);  // tiles past N repeat the last one, never stored
+    wofs[t] = static_cast<uint32_t>(nt) * a.KB * (256 * BITS) + lane * (4 * BITS);
+    szofs[t] = static_cast<uint32_t>(nt * kTileN + (lane & 15)) * 2;
+  }
+  const uint32_t xofs = (static_cast<uint32_t>(lane & 15) * a.K + 8 * (lane >> 4)) * 2;
+  // This wavefront's blocks: first + i * KS, i < n.  Loads past the last repeat it (and a
+  // wavefront without blocks loads one it never uses), so that every load is unconditional.
+  const int n = wave < a.KB ? (a.KB - wave + KS - 1) / KS : 0;
+  const int first = min(wave, a.KB - 1), lasti = max(n - 1, 0);
+  f32x4_t tot[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) tot[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+  typename Body::Ring ring[PF];
+  static_for<PF>([&](auto u) __attribute__((always_inline)) {
+    Body::load(ring[u.value], bu, a.N, wofs, szofs, xofs, first + min(static_cast<int>(u.value), lasti) * KS);
+  });
+  int c = 0;
+  for (; c + PF < n; c += PF)
+    static_for<PF>([&](auto u) __attribute__((always_inline)) {
+      Body::compute(ring[u.value], tot);
+      Body::load(ring[u.value], bu, a.N, wofs, szofs, xofs, first + min(c + static_cast<int>(u.value) + PF, lasti) * KS);
+    });
+  static_for<PF>([&](auto u) __attribute__((always_inline)) {
+    if (c + static_cast<int>(u.value) < n) Body::compute(ring[u.value], tot);
+  });
+
+  // The wavefronts' sums, added in wavefront order.  D layout of the 16x16 MFMA: lane
+  // holds column lane % 16, rows 4 (lane / 16) + e.
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) red[wave][4 * t + e][lane] = tot[t][e];
+  __syncthreads();
+  for (int i = threadIdx.x; i < NT * 4 * kWave; i += KS * kWave) {
+    const int v = i / kWave, ln = i % kWave;
+    const int m = 4 * (ln >> 4) + (v & 3), nt = ng * NT + v / 4;
+    if (m >= a.M || nt >= a.n_tiles) continue;
+    float sum = red[0][v][ln];
+#pragma unroll
+    for (int w = 1; w < KS; ++w) sum += red[w][v][ln];
+    a.y[static_cast<size_t>(m) * a.N + nt * kTileN + (ln & 15)] = float_to_bf16_bits(sum);
+  }
+}
+
+typedef void (*StreamKernel)(QArgs);
+struct StreamVariant {
+  int bits, group, nt, ks;
+  StreamKernel fn;
+};
+#define SUBSPEC_STREAM(B, G, T, W, P) {B, G, T, W, k_qstream<B, G, T, W, P>}
+#define SUBSPEC_STREAM_SET(B, G) \
+  SUBSPEC_STREAM(B, G, 1, 4, 3), SUBSPEC_STREAM(B, G, 2, 8, 3), SUBSPEC_STREAM(B, G, 2, 16, 2),
+const StreamVariant kVariants[] = {SUBSPEC_STREAM_SET(4, 128) SUBSPEC_STREAM_SET(4, 64) SUBSPEC_STREAM_SET(3, 128)
+                                       SUBSPEC_STREAM_SET(3, 64) SUBSPEC_STREAM_SET(2, 128) SUBSPEC_STREAM_SET(2, 64)};
+
+}  // namespace
+
+hipError_t launch_qstream(int nt, int ks, int bits, int group, const QArgs& a, hipStream_t st) {
+  for (const StreamVariant& v : kVariants) {
+    if (v.nt != nt || v.ks != ks || v.bits != bits || v.group != group) continue;
+    const int groups = (a.n_tiles + nt - 1) / nt;
+    const int grid = (groups + kXcds - 1) / kXcds * kXcds;
+    hipLaunchKernelGGL(v.fn, dim3(grid), dim3(ks * kWave), 0, st, a);
+    return hipGetLastError();
+  }
+  return hipErrorInvalidDeviceFunction;
+}
+
+}  // namespace subspec

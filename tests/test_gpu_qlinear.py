@@ -310,3 +310,23 @@ def test_qlinear_refined_launches(M, N, K, bits, group):
     other = run_qlinear(p, x.to(DEV), ss.SUBSPEC_PATH_MFMA16)
     assert_close(bf16_to_f64(y), bf16_to_f64(other), "against 16x16x32 tiles")
     assert ss.subspec_workspace_info()["allocations"] <= before + 1
+
+
+@pytest.mark.parametrize("M,N,K,bits,group", [
+    (1, 512, 256, 4, 64), (8, 1024, 256, 2, 128),     # two k-blocks for four wavefronts
+    (1, 2048, 384, 3, 128), (16, 8192, 1024, 4, 64),  # one tile a workgroup, odd and full rounds
+    (16, 512, 512, 2, 64), (5, 272, 1536, 3, 64),     # up to 32 tiles
+    (3, 528, 1152, 4, 128), (16, 1040, 2048, 3, 128),  # two tiles, the last one alone; eight wavefronts
+    (1, 4608, 3584, 4, 128), (6, 3584, 3584, 4, 64),  # sixteen
+    (16, 1024, 4480, 2, 64), (7, 528, 8192, 3, 64), (8, 7168, 5120, 2, 128),
+])
+def test_qlinear_small_batches_over_whole_k(M, N, K, bits, group):
+    """Small launches that would split K across workgroups run on workgroups whose
+    wavefronts split it (no workspace): against the oracle, and repeatable."""
+    p = device_projection(torch.from_numpy(_w(N, K, 370, M, N, K, bits, group)).to(DEV), bits, group)
+    q, s16, z16 = p["codes"].cpu().numpy(), p["scales"].cpu().numpy(), p["zeros"].cpu().numpy()
+    x = synth.activations(M, K, 371, M, N, K)
+    y_ref = oracle.qlinear_ref(synth.bf16_bits(x), q, s16, z16, group)
+    y = run_qlinear(p, x.to(DEV))
+    assert_close(bf16_to_f64(y), y_ref, f"M={M} N={N} K={K} bits={bits} g={group}")
+    assert torch.equal(y, run_qlinear(p, x.to(DEV)))
