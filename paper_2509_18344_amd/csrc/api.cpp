@@ -1131,15 +1131,12 @@ int subspec_tree_expand(const void* logits, const float* parent_logp, int R, int
   a.V = V;
   a.k = k;
   a.inv_t = 1.f / temperature;
-  subspec::tree_plan(R, V, &a.chunks, &a.chunk_len);
-  const size_t blocks = static_cast<size_t>(R) * a.chunks;
+  subspec::tree_launch_plan(R, V, &a.chunks, &a.chunk_len);
   char* base = static_cast<char*>(ws);
   a.cnt = reinterpret_cast<unsigned*>(base);
   char* p = base + subspec::kSplitCounterBytes;
-  a.stat_m = reinterpret_cast<float*>(p);
-  a.stat_s = a.stat_m + blocks;
-  a.cand_val = a.stat_s + blocks;
-  a.cand_idx = reinterpret_cast<int*>(a.cand_val + blocks * k);
+  a.stat = reinterpret_cast<float2*>(p);
+  a.cand = reinterpret_cast<uint2*>(p + static_cast<size_t>(R) * a.chunks * sizeof(float2));
   a.out_parent = parent_out;
   a.out_token = token_out;
   a.out_score = score_out;

@@ -15,16 +15,16 @@ struct TreeArgs {
   int R, V, k;
   float inv_t;            // 1 / temperature
   int chunks, chunk_len;  // workgroups per row and the logits each one covers
-  float* stat_m;          // [R * chunks] running maxima
-  float* stat_s;          // [R * chunks] sums of exp(z - m)
-  float* cand_val;        // [R * chunks][k] best z of each workgroup
-  int* cand_idx;          // [R * chunks][k] their tokens
+  float2* stat;           // [R * chunks] running maxima m and sums of exp(z - m)
+  uint2* cand;            // [R * chunks][k] best z of each workgroup (its bits) and their tokens
   unsigned* cnt;          // completion counter (zero between launches)
   int* out_parent;
   int* out_token;
   float* out_score;
 };
 void tree_plan(int R, int V, int* chunks, int* chunk_len);
+// The slices the launch takes: at most tree_plan's number (whose workspace they use).
+void tree_launch_plan(int R, int V, int* chunks, int* chunk_len);
 size_t tree_workspace_bytes(int R, int V, int k);
 hipError_t launch_tree_expand(const TreeArgs& a, hipStream_t st);
 

@@ -13,6 +13,13 @@
 // counter, as in the qlinear split-K) combines the pairs of each row into its
 // log-sum-exp, turns every stored candidate into a score and selects the k best.
 // Every reduction runs in a fixed order, so results are bit-reproducible.
+//
+// What bounds it is the chain of latencies of the two phases, not the logits: of 20.2 us
+// at R = 6, V = 152064, k = 6 with 450 workgroups, 2.2 were the launch, 3.0 the logits, 3.5
+// the workgroup's selection, 4.1 the completion and 7.4 the second phase.  So at most 256
+// workgroups run (one thread of the second phase per workgroup's list, half the atomics
+// on the counter), the lists arrive in the second phase's registers with one wait, and
+// the reductions stay in DPP moves.
 #include <climits>
 #include <cmath>
 
@@ -26,7 +33,6 @@ namespace {
 constexpr int kTreeThreads = 256;
 constexpr int kTreeWaves = kTreeThreads / kWave;
 constexpr int kTreeMaxBlocks = 1024;  // R * chunks never exceeds this (tree_plan)
-constexpr int kTreeBatch = 16;        // candidate loads in flight per thread
 constexpr int kTreeLoads = 4;         // logit loads in flight per thread
 constexpr int kTreeCoherent = 16;     // sc1: coherent at agent scope
 constexpr int kTreeCap = 2048;        // candidates ranked at once in LDS
@@ -141,6 +147,21 @@ __device__ __forceinline__ float wave_max(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), kWave - 1));
 }
 
+// Sum over the wavefront (same lane moves; rows that take no part add nothing), in every lane.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ float dpp_sum_step(float v) {
+  return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, ROW_MASK, 0xF, false));
+}
+__device__ __forceinline__ float wave_sum(float v) {
+  v = dpp_sum_step<0xB1, 0xF>(v);
+  v = dpp_sum_step<0x4E, 0xF>(v);
+  v = dpp_sum_step<0x141, 0xF>(v);
+  v = dpp_sum_step<0x140, 0xF>(v);
+  v = dpp_sum_step<0x142, 0xA>(v);
+  v = dpp_sum_step<0x143, 0xC>(v);
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), kWave - 1));
+}
+
 // Workgroup-wide best head of the threads' lists, removed from its owner; rounds
 // 0..k-1 give the workgroup's k best in order.  All threads get (value, index).
 // A thread can write the slot of round j + 2 only after every thread has reached
@@ -173,6 +194,21 @@ __device__ __forceinline__ void take_best(TopList<KMAX>& t, TreeShared& sh, int 
 // holds fewer than k finite heads.  Called with every lane active.
 __device__ __forceinline__ float wave_kth_head(float h, int k) {
   float th = -INFINITY;
+  if (k > 8) {
+    // Many rounds: the bound from its top 16 bits instead (any value that k heads reach
+    // will do), found bit by bit in the order-preserving integer form of a float.
+    if (__popcll(__ballot(h > -INFINITY)) < k) return th;
+    const uint32_t b = __float_as_uint(h);
+    const uint32_t u = b & 0x80000000u ? ~b : b | 0x80000000u;
+    uint32_t t = 0;
+#pragma unroll
+    for (int bit = 31; bit >= 16; --bit) {
+      const uint32_t c = t | (1u << bit);
+      if (__popcll(__ballot(u >= c)) >= k) t = c;
+    }
+    const float f = __uint_as_float(t & 0x80000000u ? t ^ 0x80000000u : ~t);
+    return f == f ? f : -INFINITY;  // a prefix below every number is no bound
+  }
   int cnt = 0;
   while (cnt < k) {
     const float mx = wave_max(h);
@@ -188,6 +224,14 @@ struct Cand {
   float v;
   int i;
 };
+
+// One 8-byte store that other XCDs' coherent loads see once it is acknowledged.
+template <typename T>
+__device__ __forceinline__ void store_pair(T* p, uint32_t lo, uint32_t hi) {
+  static_assert(sizeof(T) == 8, "a pair");
+  __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), (static_cast<unsigned long long>(hi) << 32) | lo,
+                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 // The k best of the n (<= kTreeCap) buffered candidates, by rank: each candidate
 // counts the candidates better than it (indices are distinct, so ranks are too) and
@@ -335,10 +379,10 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree_expand(TreeArgs a) {
     theta = fmaxf(theta, wave_kth_head(top.v[0], a.k));
   }
   // (m, s) over the workgroup: lanes, then wavefronts, in a fixed order.
-#pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-    const float om = __shfl_xor(m, off), os = __shfl_xor(s, off);
-    softmax_merge(m, s, om, os);
+  {
+    const float wm = wave_max(m);
+    s = wave_sum(m == -INFINITY ? 0.f : s * __expf(m - wm));
+    m = wm;
   }
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   if (lane == 0) {
@@ -351,14 +395,10 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree_expand(TreeArgs a) {
   for (int w = 1; w < kTreeWaves; ++w) softmax_merge(bm, bs, sh.wm[w], sh.ws[w]);
   select_from_lists(top, sh, cbuf, a.k);
   if (static_cast<int>(threadIdx.x) < a.k) {
-    const size_t o = static_cast<size_t>(blk) * a.k + threadIdx.x;
-    __hip_atomic_store(a.cand_val + o, sh.win_v[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(a.cand_idx + o, sh.win_i[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    store_pair(a.cand + static_cast<size_t>(blk) * a.k + threadIdx.x, __float_as_uint(sh.win_v[threadIdx.x]),
+               static_cast<uint32_t>(sh.win_i[threadIdx.x]));
   }
-  if (threadIdx.x == 0) {
-    __hip_atomic_store(a.stat_m + blk, bm, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(a.stat_s + blk, bs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+  if (threadIdx.x == 0) store_pair(a.stat + blk, __float_as_uint(bm), __float_as_uint(bs));
 
   // Completion: every workgroup waits for its own stores, the last one goes on.
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
@@ -369,57 +409,67 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree_expand(TreeArgs a) {
   __syncthreads();
   if (!sh.last) return;
 
-  // Phase 2.  The workgroups' results are read with the coherent cache policy; each
-  // read is a trip to the coherent level of the memory system, so the (m, s) pairs
-  // and the first batch of candidates are all requested before anything waits.
+  // Phase 2.  The workgroups' results are read with the coherent cache policy; each read
+  // is a trip to the coherent level of the memory system, so a thread requests the
+  // statistics and the whole list of its workgroup (and what is needed of the others where
+  // there are more than 256) before anything waits.
   const int nblk = gridDim.x;
-  const int per_row = a.chunks * a.k;
-  const int total = a.R * per_row;
-  const __amdgpu_buffer_rsrc_t rm_ = buffer_rsrc(a.stat_m, nblk * 4);
-  const __amdgpu_buffer_rsrc_t rs_ = buffer_rsrc(a.stat_s, nblk * 4);
-  const __amdgpu_buffer_rsrc_t rv_ = buffer_rsrc(a.cand_val, total * 4);
-  const __amdgpu_buffer_rsrc_t ri_ = buffer_rsrc(a.cand_idx, total * 4);
-  float z[kTreeBatch];
-  int v[kTreeBatch];
-  auto load_batch = [&](int q0) __attribute__((always_inline)) {
-#pragma unroll
-    for (int u = 0; u < kTreeBatch; ++u) {  // past the end: zeros, skipped when used
-      const uint32_t off = static_cast<uint32_t>(q0 + u * kTreeThreads) * 4;
-      z[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rv_, off, 0, kTreeCoherent));
-      v[u] = static_cast<int>(__builtin_amdgcn_raw_buffer_load_b32(ri_, off, 0, kTreeCoherent));
-    }
+  const __amdgpu_buffer_rsrc_t rst = buffer_rsrc(a.stat, nblk * 8);
+  const __amdgpu_buffer_rsrc_t rca = buffer_rsrc(a.cand, nblk * a.k * 8);
+  // list entry j of workgroup b; past the end zeros, skipped when used
+  auto load_cand = [&](int b, int j) __attribute__((always_inline)) {
+    const auto v = __builtin_amdgcn_raw_buffer_load_b64(rca, static_cast<uint32_t>(b * a.k + j) * 8, 0, kTreeCoherent);
+    return Cand{__uint_as_float(v[0]), static_cast<int>(v[1])};
   };
-  constexpr int kPer = kTreeMaxBlocks / kTreeThreads;
+  // A thread's slots: workgroups thread, thread + 256, ...  The lists of the first kHeld are
+  // held in registers; those of later ones (more than 256 or 512 workgroups) are read
+  // where they are needed, in loops that are not unrolled: this code runs once per call,
+  // so its size costs instruction fetches.
+  constexpr int kHeld = KMAX == 8 ? 2 : 1;
   static_assert(kTreeMaxRows <= kTreeMaxBlocks, "one parent score per block slot");
   const __amdgpu_buffer_rsrc_t rp_ = buffer_rsrc(a.parent, a.R * 4);
-  float pm[kPer], ps[kPer], pk[kPer], ph[kPer], pp[kPer];  // per block: (m, s), k-th and first candidate; parents
-#pragma unroll
-  for (int u = 0; u < kPer; ++u) {
-    const int b = threadIdx.x + u * kTreeThreads;
-    const uint32_t off = static_cast<uint32_t>(b) * 4;
-    pm[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rm_, off, 0, kTreeCoherent));
-    ps[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_, off, 0, kTreeCoherent));
-    pk[u] = __uint_as_float(
-        __builtin_amdgcn_raw_buffer_load_b32(rv_, static_cast<uint32_t>(b * a.k + a.k - 1) * 4, 0, kTreeCoherent));
-    ph[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rv_, static_cast<uint32_t>(b * a.k) * 4, 0, kTreeCoherent));
-    pp[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rp_, off, 0, 0));
-  }
-  load_batch(threadIdx.x);
-#pragma unroll
-  for (int u = 0; u < kPer; ++u) {
-    const int q = threadIdx.x + u * kTreeThreads;
-    if (q < nblk) {
-      stat_lds[2 * q] = pm[u];
-      stat_lds[2 * q + 1] = ps[u];
+  Cand list[kHeld][KMAX];
+  float hv[kHeld], kv[kHeld];  // their first and k-th candidates
+  auto load_stat = [&](int b) __attribute__((always_inline)) {
+    const auto st = __builtin_amdgcn_raw_buffer_load_b64(rst, static_cast<uint32_t>(b) * 8, 0, kTreeCoherent);
+    const float par = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rp_, static_cast<uint32_t>(b) * 4, 0, 0));
+    return f32x4_t{__uint_as_float(st[0]), __uint_as_float(st[1]), par, 0.f};
+  };
+  auto keep_stat = [&](int b, const f32x4_t& st) __attribute__((always_inline)) {
+    if (b < nblk) {
+      stat_lds[2 * b] = st[0];
+      stat_lds[2 * b + 1] = st[1];
     }
-    if (q < a.R) par_lds[q] = pp[u];
+    if (b < a.R) par_lds[b] = st[2];
+  };
+  {
+    f32x4_t st[kHeld];
+#pragma unroll
+    for (int h = 0; h < kHeld; ++h) {
+      const int b = threadIdx.x + h * kTreeThreads;  // past the end zeros, skipped when used
+#pragma unroll
+      for (int j = 0; j < KMAX; ++j)
+        if (j < a.k) list[h][j] = load_cand(b, j);
+      st[h] = load_stat(b);
+    }
+#pragma unroll
+    for (int h = 0; h < kHeld; ++h) {
+      hv[h] = list[h][0].v;
+#pragma unroll
+      for (int j = 0; j < KMAX; ++j)
+        if (j == a.k - 1) kv[h] = list[h][j].v;
+      keep_stat(threadIdx.x + h * kTreeThreads, st[h]);
+    }
+#pragma unroll 1
+    for (int b = threadIdx.x + kHeld * kTreeThreads; b < nblk; b += kTreeThreads) keep_stat(b, load_stat(b));
   }
   if (threadIdx.x == 0) sh.n = 0;
   __syncthreads();
   // The log-sum-exp of every row from its chunks' pairs: a group of G lanes per row
   // (G the power of two >= chunks, at most a wavefront), each lane over chunks
-  // lane, lane + G, ..., then a butterfly over the group.  Both merges of a
-  // butterfly pair give the same bits, so every lane ends with the same pair.
+  // lane, lane + G, ..., then DPP reductions over a wavefront or a butterfly over a smaller
+  // group.  Both merges of a butterfly pair give the same bits, so every lane ends with
+  // the same pair.
   {
     int G = 1;
     while (G < a.chunks && G < kWave) G <<= 1;
@@ -431,9 +481,15 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree_expand(TreeArgs a) {
       if (r < a.R)
         for (int c = gl; c < a.chunks; c += G)
           softmax_merge(rm, rs, stat_lds[2 * (r * a.chunks + c)], stat_lds[2 * (r * a.chunks + c) + 1]);
-      for (int off = 1; off < G; off <<= 1) {
-        const float om = __shfl_xor(rm, off), os = __shfl_xor(rs, off);
-        softmax_merge(rm, rs, om, os);
+      if (G == kWave) {
+        const float wm = wave_max(rm);
+        rs = wave_sum(rm == -INFINITY ? 0.f : rs * __expf(rm - wm));
+        rm = wm;
+      } else {
+        for (int off = 1; off < G; off <<= 1) {
+          const float om = __shfl_xor(rm, off), os = __shfl_xor(rs, off);
+          softmax_merge(rm, rs, om, os);
+        }
       }
       if (r < a.R && gl == 0) lse_row[r] = rm + __logf(rs);
     }
@@ -445,15 +501,17 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree_expand(TreeArgs a) {
   // or a value that k lanes' best block heads reach, whichever is larger.
   {
     float tb = -INFINITY, hb = -INFINITY;
+    auto bound = [&](int b, float head, float kth) __attribute__((always_inline)) {
+      if (b >= nblk) return;
+      const int r = b / a.chunks;
+      tb = fmaxf(tb, par_lds[r] + (kth - lse_row[r]));
+      hb = fmaxf(hb, par_lds[r] + (head - lse_row[r]));
+    };
 #pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-      const int b = threadIdx.x + u * kTreeThreads;
-      if (b < nblk) {
-        const int r = b / a.chunks;
-        tb = fmaxf(tb, par_lds[r] + (pk[u] - lse_row[r]));
-        hb = fmaxf(hb, par_lds[r] + (ph[u] - lse_row[r]));
-      }
-    }
+    for (int h = 0; h < kHeld; ++h) bound(threadIdx.x + h * kTreeThreads, hv[h], kv[h]);
+#pragma unroll 1
+    for (int b = threadIdx.x + kHeld * kTreeThreads; b < nblk; b += kTreeThreads)
+      bound(b, load_cand(b, 0).v, load_cand(b, a.k - 1).v);
     tb = fmaxf(wave_max(tb), wave_kth_head(hb, a.k));
     if (lane == 0) sh.wm[wave] = tb;
   }
@@ -461,48 +519,40 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree_expand(TreeArgs a) {
   float theta2 = sh.wm[0];
 #pragma unroll
   for (int w = 1; w < kTreeWaves; ++w) theta2 = fmaxf(theta2, sh.wm[w]);
-  // Every stored candidate becomes a score; those at or above theta are kept.
-  float sc[kTreeBatch];
-  auto score_batch = [&](int q0) __attribute__((always_inline)) -> unsigned {
-    unsigned ok = 0;
-#pragma unroll
-    for (int u = 0; u < kTreeBatch; ++u) {
-      const int q = q0 + u * kTreeThreads;
-      const bool valid = q < total && v[u] != INT_MAX;  // past the end, or an empty slot
-      const int r = valid ? q / per_row : 0;
-      sc[u] = par_lds[r] + (z[u] - lse_row[r]);
-      v[u] = r * a.V + v[u];
-      ok |= (valid && sc[u] >= theta2 ? 1u : 0u) << u;
-    }
-    return ok;
+  // Every stored candidate becomes a score; those at or above theta are kept: a prefix of
+  // each block's list, since its candidates come best first.
+  auto score = [&](int r, const Cand& c) __attribute__((always_inline)) {
+    // an empty slot of a short chunk scores below everything
+    return c.i == INT_MAX ? Cand{-INFINITY, INT_MAX} : Cand{par_lds[r] + (c.v - lse_row[r]), r * a.V + c.i};
   };
-  auto pick = [&](int u, float& su, int& iu) __attribute__((always_inline)) {
-    su = sc[0];
-    iu = v[0];
+  auto each = [&](auto&& take) __attribute__((always_inline)) {
 #pragma unroll
-    for (int w = 1; w < kTreeBatch; ++w) {
-      su = u == w ? sc[w] : su;
-      iu = u == w ? v[w] : iu;
+    for (int h = 0; h < kHeld; ++h)
+      if (static_cast<int>(threadIdx.x) + h * kTreeThreads < nblk)
+        take((threadIdx.x + h * kTreeThreads) / a.chunks, list[h]);
+#pragma unroll 1
+    for (int b = threadIdx.x + kHeld * kTreeThreads; b < nblk; b += kTreeThreads) {
+      Cand later[KMAX];
+#pragma unroll
+      for (int j = 0; j < KMAX; ++j)
+        if (j < a.k) later[j] = load_cand(b, j);
+      take(b / a.chunks, later);
     }
   };
   // Usually only a few candidates reach theta: they go to the LDS buffer and are
   // ranked there.
-  for (int q0 = threadIdx.x; q0 < total; q0 += kTreeThreads * kTreeBatch) {
-    if (q0 != static_cast<int>(threadIdx.x)) load_batch(q0);
-    unsigned ok = score_batch(q0);
-    if (ok) {
-      int off = atomicAdd(&sh.n, __popc(ok));
-      while (ok) {
-        const int u = __builtin_ctz(ok);
-        ok &= ok - 1;
-        float su;
-        int iu;
-        pick(u, su, iu);
-        if (off < kTreeCap) cbuf[off] = Cand{su, iu};
-        ++off;
-      }
+  each([&](int r, const Cand (&own)[KMAX]) __attribute__((always_inline)) {
+    int cnt = 0;
+#pragma unroll
+    for (int j = 0; j < KMAX; ++j)
+      if (j < a.k) cnt += own[j].i != INT_MAX && par_lds[r] + (own[j].v - lse_row[r]) >= theta2 ? 1 : 0;
+    if (cnt) {
+      const int off = atomicAdd(&sh.n, cnt);
+#pragma unroll
+      for (int j = 0; j < KMAX; ++j)
+        if (j < cnt && off + j < kTreeCap) cbuf[off + j] = score(r, own[j]);
     }
-  }
+  });
   __syncthreads();
   const int n = sh.n;
   if (n <= kTreeCap) {
@@ -511,18 +561,14 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree_expand(TreeArgs a) {
     // More ties than the buffer holds: the same candidates again, through the
     // threads' lists and k rounds of take_best.
     top.clear();
-    for (int q0 = threadIdx.x; q0 < total; q0 += kTreeThreads * kTreeBatch) {
-      load_batch(q0);
-      unsigned ok = score_batch(q0);
-      while (ok) {
-        const int u = __builtin_ctz(ok);
-        ok &= ok - 1;
-        float su;
-        int iu;
-        pick(u, su, iu);
-        top.insert(su, iu);
-      }
-    }
+    each([&](int r, const Cand (&own)[KMAX]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int j = 0; j < KMAX; ++j)
+        if (j < a.k) {
+          const Cand c = score(r, own[j]);
+          if (c.i != INT_MAX && c.v >= theta2) top.insert(c.v, c.i);
+        }
+    });
     for (int j = 0; j < a.k; ++j) {
       float val;
       int idx;
@@ -554,6 +600,19 @@ void tree_plan(int R, int V, int* chunks, int* chunk_len) {
   if (c < 1) c = 1;
   int len = (V + c - 1) / c;
   len = (len + 7) / 8 * 8;
+  *chunk_len = len;
+  *chunks = (V + len - 1) / len;
+}
+
+void tree_launch_plan(int R, int V, int* chunks, int* chunk_len) {
+  // At most one workgroup per thread of the second phase (256 in all; see the head of this
+  // file).  With more rows the slices get long (R = 64: 29.5 us with 256 workgroups, 28.3
+  // with 512).
+  tree_plan(R, V, chunks, chunk_len);
+  if (R > 32) return;
+  const int most = kTreeThreads / R;
+  if (*chunks <= most) return;
+  const int len = ((V + most - 1) / most + 7) / 8 * 8;
   *chunk_len = len;
   *chunks = (V + len - 1) / len;
 }

@@ -60,6 +60,29 @@ def test_tree_expand_matches_oracle(R, V, k, T):
     _check(bits, parent, T, k, f"R={R} V={V} k={k} T={T}")
 
 
+@pytest.mark.parametrize("R,V,k,shift", [
+    (512, 64, 8, 0.0), (513, 64, 8, 0.0), (256, 64, 9, 0.0), (257, 64, 16, -40.0), (700, 64, 32, 0.0),
+    (32, 20000, 20, -30.0), (33, 20000, 6, 0.0), (43, 8192, 12, 5.0), (5, 152064, 32, -20.0)])
+def test_tree_expand_list_slots_and_bounds(R, V, k, shift):
+    """Around the numbers of workgroup lists the second phase holds in registers (256 a
+    slot), the slicing rule's last row count, and bounds found from all-negative or
+    all-positive logits with k above eight."""
+    bits = oracle.bf16_round_bits(np.random.default_rng(R + V + k).normal(0.0, 2.0, (R, V)).astype(np.float32)
+                                  + np.float32(shift))
+    parent = np.random.default_rng(R * 5 + k).uniform(-6.0, 0.0, R)
+    _check(bits, parent, 0.3, k, f"R={R} V={V} k={k} shift={shift}")
+
+
+def test_tree_expand_ties_over_many_workgroups():
+    # more tied candidates than the ranking buffer holds, from lists past the held slots
+    R, V, k = 600, 64, 32
+    bits = np.full((R, V), oracle.bf16_round_bits(np.float32(0.5)), dtype=np.uint16)
+    parent = np.full(R, -1.0, np.float32)
+    parent[:3] = -9.0
+    pi, tok, _ = _run(bits, parent, 0.2, k)
+    assert list(pi) == [3] * k and list(tok) == list(range(k))
+
+
 def test_tree_expand_ties_follow_flat_index():
     R, V, k = 4, 4096, 10
     bits = np.full((R, V), oracle.bf16_round_bits(np.float32(1.25)), dtype=np.uint16)
