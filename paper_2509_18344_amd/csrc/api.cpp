@@ -720,7 +720,7 @@ void pack_host(const uint8_t* codes, int N, int K, uint8_t* out) {
 // a few megabytes of weights their completion (three trips to the coherent level in a
 // row) costs as much as the weights.  us per call, the described launch against this one,
 // 4-bit g128, one run: 1024x1024 M = 1 5.3 / 2.8, M = 16 5.8 / 3.5; 8192x1024 M = 6 7.0 / 4.1;
-// 4608x3584 M = 1 7.7 / 5.0, M = 6 8.4 / 5.6, M = 16 8.9 / 7.2; 7168x5120 M = 1 8.9 / 7.0, M = 8
+// 4608x3584 M = 1 7.8 / 4.6, M = 6 8.4 / 5.6, M = 16 8.9 / 7.2; 7168x5120 M = 1 8.9 / 7.0, M = 8
 // 9.8 / 7.9; 12288x4096 M = 6 11.3 / 10.1; 2048x8192 M = 6 10.5 / 8.1.  Where the lines lie:
 //  - every pair of tiles reads the fragments of x from the L2 again, M * K * 2 bytes: from
 //    M = 9 that is more than the weights, and only a K of up to 36 blocks still gains
@@ -729,7 +729,11 @@ void pack_host(const uint8_t* codes, int N, int K, uint8_t* out) {
 //    (10240x4096, 320 pairs, M = 1 9.0 / 9.2; 14000x3584, 438 pairs, 9.9 / 9.1); of eight two
 //    (22000x2048 8.5 / 8.6);
 //  - launches of more weights have enough column groups or blocks per workgroup to hide
-//    the completion (3584x18944 M = 1 12.1 / 12.4, 37888x3584 14.3 / 18.2);
+//    the completion (37888x3584 M = 1 14.3 / 15.9), except where one tile a workgroup fills
+//    the CUs once (K up to 160 blocks; 3584x18944 M = 1 11.9 / 10.1, M = 2 13.1 / 10.7; from
+//    M = 5, two loads of x per block, to 112: 2560x11008 3-bit M = 6 11.0 / 8.9, 4096x14336
+//    13.5 / 12.7, but 3584x18944 3-bit M = 8 14.8 / 15.2 and 2048x18944 M = 6 11.9 / 12.3); one
+//    tile against two at M = 1: 3584x3584 4.2 / 4.4, 1024x4096 3.9 / 4.3;
 //  - a K of one or two blocks is not split anyway (512x256 M = 8 2.9 / 2.8, M = 16 2.9 / 3.3;
 //    29200x256 M = 1 4.1 / 6.3).
 bool stream_choice(int M, int N, int K, int* nt, int* ks) {
@@ -748,8 +752,12 @@ bool stream_choice(int M, int N, int K, int* nt, int* ks) {
     if (KB <= 2) return M <= 8 && tiles <= 64;
     return mweights <= 8 && (M <= 8 || tiles <= 512);
   }
-  *nt = 2;
   *ks = KB < 24 ? 8 : 16;
+  if (KB >= 24 && tiles <= device_cus() && (M <= 4 || (M <= 8 && KB > 64))) {
+    *nt = 1;
+    return KB <= (M <= 4 ? 160 : 112);
+  }
+  *nt = 2;
   if (KB > 64 || mweights > 48) return false;
   if (M > 8) return KB <= 36 && (KB < 24 || tiles >= 64) && mweights <= 18;
   return KB < 24 ? pairs <= 2 * device_cus() : pairs <= device_cus() || 2 * pairs >= 3 * device_cus();
@@ -787,11 +795,6 @@ int qlinear_impl(const void* x, const void* qweight, const void* scales, const v
     a.rb_rows = kc.rows;
     a.rb_counters = p.col_groups;
   }
-  int snt = 0, sks = 0;
-  if (path == SUBSPEC_PATH_AUTO && stream_choice(M, N, K, &snt, &sks)) {
-    const hipError_t e = subspec::launch_qstream(snt, sks, bits, group, a, st);
-    return e == hipSuccess ? SUBSPEC_OK : hip_fail(e, "qlinear launch");
-  }
   if (p.workspace_bytes) {
     void* ws = nullptr;
     if (noalloc) {
@@ -812,7 +815,12 @@ int qlinear_impl(const void* x, const void* qweight, const void* scales, const v
     a.ws = reinterpret_cast<float*>(base + subspec::kSplitCounterBytes + xsb);
   }
   hipError_t e = hipSuccess;
-  if (kc.shape == 32) {
+  int snt = 0, sks = 0;
+  if (path == SUBSPEC_PATH_AUTO && stream_choice(M, N, K, &snt, &sks)) {
+    // needs no workspace, which the described launch has been given all the same: what a
+    // call allocates, and where it is refused, does not depend on this choice
+    e = subspec::launch_qstream(snt, sks, bits, group, a, st);
+  } else if (kc.shape == 32) {
     if (kc.rows == 128) e = subspec::launch_xsum(a.x, M, K, group, const_cast<float*>(a.xsum), st);
     if (e == hipSuccess)
       e = subspec::launch_qmma(kc.waves, kc.teams, kc.rows / 32, kc.nt / 2, kc.prefetch, bits, group, a, p.grid,

@@ -319,10 +319,12 @@ def test_qlinear_refined_launches(M, N, K, bits, group):
     (3, 528, 1152, 4, 128), (16, 1040, 2048, 3, 128),  # two tiles, the last one alone; eight wavefronts
     (1, 4608, 3584, 4, 128), (6, 3584, 3584, 4, 64),  # sixteen
     (16, 1024, 4480, 2, 64), (7, 528, 8192, 3, 64), (8, 7168, 5120, 2, 128),
+    (4, 3600, 3200, 2, 128), (1, 64, 18944, 4, 64),   # one tile, sixteen wavefronts; up to 4 rows
+    (5, 272, 8320, 3, 128), (8, 1040, 14336, 4, 64),  # and up to 8
 ])
 def test_qlinear_small_batches_over_whole_k(M, N, K, bits, group):
     """Small launches that would split K across workgroups run on workgroups whose
-    wavefronts split it (no workspace): against the oracle, and repeatable."""
+    wavefronts split it: against the oracle, and repeatable."""
     p = device_projection(torch.from_numpy(_w(N, K, 370, M, N, K, bits, group)).to(DEV), bits, group)
     q, s16, z16 = p["codes"].cpu().numpy(), p["scales"].cpu().numpy(), p["zeros"].cpu().numpy()
     x = synth.activations(M, K, 371, M, N, K)
