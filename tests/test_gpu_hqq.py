@@ -42,6 +42,24 @@ def test_hqq_quantizer_bit_exact(bits, group, N, K):
     assert np.array_equal(s16, s0) and (z16 != z0).mean() > 0.3
 
 
+@pytest.mark.parametrize("bits,group,N,K,scale", [(4, 64, 48, 512, 100.0), (2, 128, 16, 512, 30.0),
+                                                  (3, 64, 80, 256, 18.0), (3, 128, 64, 384, 16.0)])
+def test_hqq_quantizer_bit_exact_with_large_residuals(bits, group, N, K, scale):
+    """Weights whose residuals reach the soft threshold (|x| > 0.125): all groups at the
+    large scales, some of them at the small ones, beside groups of the usual size."""
+    w = synth.weights_np(N, K, 33, bits, group) * np.float32(scale)
+    w[: N // 4] = synth.weights_np(N // 4, K, 34, bits, group)
+    codes, sc, zr = _hqq_gpu(w, bits, group)
+    q, s16, z16 = oracle.quantize_hqq(w, bits, group)
+    assert np.array_equal(sc.cpu().numpy().view(np.uint16), s16.view(np.uint16))
+    assert np.array_equal(zr.cpu().numpy().view(np.uint16), z16.view(np.uint16))
+    assert np.array_equal(codes.cpu().numpy(), q)
+    x = np.abs(w.reshape(N, K // group, group) - (q.reshape(N, K // group, group).astype(np.float64)
+               - z16.T.astype(np.float64)[:, :, None]) * s16.T.astype(np.float64)[:, :, None])
+    over = (x.max(axis=2) > 0.125).mean()
+    assert 0.1 < over < 1.0, over
+
+
 def test_hqq_weights_through_qlinear():
     bits, group, N, K, M = 4, 64, 512, 1024, 8
     w = synth.weights_np(N, K, 41)
