@@ -50,9 +50,9 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0
 # and which kernel names belong to it.
 FAMILIES = {
     "qlinear": {"json": os.path.join(ROOT, "profiles", "traffic.json"),
-                "sources": ("kernels_qlinear.hip", "kernels_qmma.hip", "qmma_kernel.h", "qlinear_device.h",
-                            "device_common.h", "kernels.h"),
-                "kernels": ("k_qgemv", "k_qgemm_mfma", "k_qmma")},
+                "sources": ("kernels_qlinear.hip", "kernels_qmma.hip", "kernels_qstream.hip", "qmma_kernel.h",
+                            "qlinear_device.h", "device_common.h", "kernels.h"),
+                "kernels": ("k_qgemv", "k_qgemm_mfma", "k_qmma", "k_qstream")},
     "tree": {"json": os.path.join(ROOT, "profiles", "traffic_tree.json"),
              "sources": ("kernels_tree.hip", "kernels_tree.h", "device_common.h", "kernels.h"),
              "kernels": ("k_tree_expand",)},

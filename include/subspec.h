@@ -215,7 +215,10 @@ int subspec_qlinear_path(const void* x, const void* qweight, const void* scales,
                          void* y, int path, hipStream_t stream);
 
 /* Host only, no GPU needed: validate the shape and fill *plan with the launch
- * configuration subspec_qlinear_path would use for `path` (AUTO allowed). */
+ * configuration of `path` (AUTO allowed), whose workspace_bytes is what
+ * subspec_qlinear_path obtains.  Where another launch of the same function measured
+ * faster, the call runs that one within the same workspace: M <= 16 without partial
+ * sums, and 32x32 tiles with other rows, wavefronts or ring depth above M = 32. */
 int subspec_qlinear_plan(int M, int N, int K, int bits, int group, int path,
                          subspec_plan* plan);
 
