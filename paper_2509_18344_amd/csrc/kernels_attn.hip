@@ -313,6 +313,17 @@ __device__ __forceinline__ void stream_load(const AttnArgs& a, int g, int key0, 
   }
 }
 
+// Values of keys at and past `live` become zeros: their probability is zero, and zero times
+// an infinite value (the repeated last key's) would be NaN.
+__device__ __forceinline__ void zero_values(StreamRegs& r, int live, int lane) {
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+    if (2 * (lane & 15) + h >= live) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) r.v[j][h] = make_uint4(0, 0, 0, 0);
+    }
+}
+
 __device__ __forceinline__ void store_values(uint16_t (&vt)[kAttnD][kVRow], const StreamRegs& r, int lane) {
   // two keys (adjacent slots) of one dimension per 32-bit word
   const int slot = value_slot(2 * (lane & 15));
@@ -386,6 +397,8 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
   }
   auto& vt = L.w[wave].vt;
   for (int n = kw; n < ntiles; n += KW) {
+    const int key0 = k_begin + n * kAttnTile;
+    if (key0 + kAttnTile > k_end) zero_values(r, k_end - key0, lane);
     store_values(vt, r, lane);
     // S^T = K Q^T: lane holds keys 16u + 4 quarter + r of its query
     f32x4_t st[QW][2];
@@ -399,7 +412,6 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
           st[t][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[t][j], j == 0 ? f32x4_t{0.f, 0.f, 0.f, 0.f} : st[t][u],
                                                              0, 0, 0);
       }
-    const int key0 = k_begin + n * kAttnTile;
     if (n + KW < ntiles) stream_load(a, g, k_begin + (n + KW) * kAttnTile, k_end, lane, r);
     bf16x8_t pfh[QW], pfl[QW];
 #pragma unroll

@@ -91,6 +91,36 @@ def test_tree_attention_long_ranges(M, Hq, Hkv, P, T):
     _check(M, Hq, Hkv, P, T, 6, 11 * P + T + M, q_scale=1.5, S=P + T + M, what=f"long M={M} Hq={Hq} Hkv={Hkv} P={P} T={T}")
 
 
+@pytest.mark.parametrize("P,Hkv", [(4150, 16), (100, 2)])  # long ranges and short ones
+def test_tree_attention_infinite_value_of_the_last_key(P, Hkv):
+    """The last key's infinite value carries a weight, so the output is infinite in that
+    dimension and finite elsewhere: what fills the last tile past that key must add
+    nothing (zero times infinity is NaN)."""
+    S = P + 1
+    assert (P + 1) % 32  # the last tile is not full
+    assert (ss.subspec_tree_attention_plan(1, Hkv, Hkv, P, 0)[1] >= 8) == (P > 4000)
+    q, kn = np.zeros((1, Hkv, D), np.float32), np.zeros((1, Hkv, D), np.float32)
+    kc, vc = np.zeros((Hkv, S, D), np.float32), np.zeros((Hkv, S, D), np.float32)
+    vn = np.ones((1, Hkv, D), np.float32)
+    # scores 0, of the last committed key 1 and of the new one 1 - 0.3515625: its weight
+    # exp(-0.3515625) = 0.7036 lies just above a bf16 value (180 / 256), so both of the
+    # bf16 terms it is held in are positive and their products with infinity add up
+    q[:, :, 0] = 1.0
+    kc[:, P - 1, 0] = 1.0
+    kn[:, :, 0] = 0.6484375
+    vn[:, :, 5] = np.inf
+    d = {n: torch.from_numpy(a).to(DEV).to(torch.bfloat16) for n, a in
+         dict(q=q, kc=kc, vc=vc, kn=kn, vn=vn).items()}
+    out = torch.empty((1, Hkv, D), dtype=torch.bfloat16, device=DEV)
+    ss.subspec_tree_attention(d["q"], d["kc"], d["vc"], d["kn"], d["vn"],
+                              torch.ones((1, 1), dtype=torch.int32, device=DEV), 1, Hkv, Hkv, S, P, 0, 1.0, out)
+    o = out.float().cpu().numpy()
+    assert np.all(np.isposinf(o[..., 5])), o[..., 5]
+    w = np.exp(0.6484375) / ((P - 1) + np.exp(1.0) + np.exp(0.6484375))
+    rest = np.delete(o, 5, axis=2)
+    assert np.all(np.abs(rest - w) <= 2.0 ** -8 * w), (rest.min(), rest.max(), w)
+
+
 def test_tree_attention_query_without_visible_keys_gets_zeros():
     M, Hq, Hkv, P, T = 2, 4, 2, 0, 3
     mask = np.zeros((M, 1), np.uint32)
