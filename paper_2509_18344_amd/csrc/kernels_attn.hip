@@ -342,6 +342,14 @@ __device__ __forceinline__ void store_values(uint16_t (&vt)[kAttnD][kVRow], cons
   }
 }
 
+// Orders LDS accesses of a wavefront's lanes to each other's words, for the compiler (the
+// hardware keeps a wavefront's LDS operations in order; no instruction is emitted).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // QT: query tiles of 16 rows (1 .. 4); a wavefront takes QW of them.
 template <int QT>
 __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_attn_stream(AttnArgs a) {
@@ -400,6 +408,7 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
     const int key0 = k_begin + n * kAttnTile;
     if (key0 + kAttnTile > k_end) zero_values(r, k_end - key0, lane);
     store_values(vt, r, lane);
+    wave_lds_fence();  // the products below read other lanes' words
     // S^T = K Q^T: lane holds keys 16u + 4 quarter + r of its query
     f32x4_t st[QW][2];
 #pragma unroll
@@ -467,6 +476,7 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
         o[t][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pfl[t], o[t][dt], 0, 0, 0);
       }
     }
+    wave_lds_fence();  // the next stores overwrite what other lanes read
   }
 
   // The workgroup's maximum per row; every wavefront scales its output and sum to it.
