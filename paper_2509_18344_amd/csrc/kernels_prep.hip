@@ -115,8 +115,9 @@ constexpr int kHqqIters = 20;
 //    zero: |x| - |x|^(p-1) / beta > 0 needs |x|^(2-p) > 1 / beta.  For |x| <= kHqqNoShrink
 //    it cannot hold in any round (the largest beta of the rounds is 12.2, and
 //    0.125^(p-1) / 12.2 = 0.153 > 0.125, a margin far beyond rounding): e is zero and
-//    the refitted term is q - w / s.  A group that meets a larger residual (or a NaN)
-//    starts over with the plain rounds (hqq_group).
+//    the refitted term is q - w / s.  A group that meets a larger residual starts over with
+//    the plain rounds (hqq_group).  (A NaN among the weights leaves no error sum below the
+//    first one in either form, so the min/max zero stays.)
 //  - the error sum of a new zero and the next refit need the same codes: one pass
 //    computes both (the refit of the last pass is not used).
 // Every value that decides anything comes from the same operations in the same order as
@@ -138,30 +139,70 @@ __device__ __forceinline__ uint32_t hqq_word(const double* quot, double z, doubl
 }
 
 // The plain rounds for one group from its weights in memory: returns the zero's fp16
-// bits and stores the codes.
+// bits and stores the codes.  W elements at a time: one or two wavefronts per SIMD leave
+// a float64 power's chain of operations exposed otherwise.  W residuals within
+// kHqqNoShrink in every lane need no power.  W is four for groups of 64, where eight would
+// take the registers of the second wavefront (3584 x 3584, every group beyond the bound:
+// 2680 us against 3050; one element at a time 3050, all rounds in this form with the weights
+// in LDS 2610; 3584 x 18944 10800 us, in LDS 11100), and eight for groups of 128
+// (3584 x 3584 3190 us against 3310; one element at a time 4030, in LDS 4280).
+template <int W>
 __device__ __attribute__((noinline)) uint16_t hqq_group(const float* src, uint8_t* dst, int group, double s,
                                                         uint16_t z16, double qmax) {
+  // W elements' weights, quotients, codes and residuals under zero z
+  struct Part {
+    double x[W], quot[W], q[W], r[W];
+    __device__ __forceinline__ Part(const float* p, double s, double z, double qmax) {
+#pragma unroll
+      for (int k = 0; k < W; k += 4) {
+        const float4 f = *reinterpret_cast<const float4*>(p + k);
+        x[k] = f.x, x[k + 1] = f.y, x[k + 2] = f.z, x[k + 3] = f.w;
+      }
+#pragma unroll
+      for (int k = 0; k < W; ++k) {
+        quot[k] = x[k] / s;
+        q[k] = hqq_code(quot[k], z, qmax);
+        r[k] = x[k] - (q[k] - z) * s;
+      }
+    }
+  };
   auto l1 = [&](double z) {
     double tot = 0.0;
-    for (int i = 0; i < group; ++i) {
-      const double x = src[i];
-      tot += fabs(x - (hqq_code(x / s, z, qmax) - z) * s);
+    for (int i = 0; i < group; i += W) {
+      const Part v(src + i, s, z, qmax);
+#pragma unroll
+      for (int k = 0; k < W; ++k) tot += fabs(v.r[k]);
     }
     return tot;
   };
   const double z0 = f16_bits_to_f64(z16);
-  const double e0 = l1(z0);
-  double z = z0, best_z = z0, best = e0, beta = kHqqBeta;
+  double z = z0, best_z = z0, best = 0.0, e0 = 0.0, beta = kHqqBeta;
   for (int it = 0; it < kHqqIters; ++it) {
-    double acc = 0.0;
-    for (int i = 0; i < group; ++i) {
-      const double x = src[i];
-      const double q = hqq_code(x / s, z, qmax);
-      const double r = x - (q - z) * s;
-      const double a = fabs(r);
-      const double e = r == 0.0 ? 0.0 : copysign(fmax(a - pow(a, kHqqP - 1.0) / beta, 0.0), r);
-      acc += q - (x - e) / s;
+    double acc = 0.0, tot = 0.0;  // the refit sum, and the error sum of the zero it starts from
+    for (int i = 0; i < group; i += W) {
+      const Part v(src + i, s, z, qmax);
+      double t[W];
+      bool within = true;
+#pragma unroll
+      for (int k = 0; k < W; ++k) {
+        t[k] = v.quot[k];
+        within = within && fabs(v.r[k]) <= kHqqNoShrink;
+      }
+      if (__ballot(!within)) {
+#pragma unroll
+        for (int k = 0; k < W; ++k) {
+          const double a = fabs(v.r[k]);
+          const double e = v.r[k] == 0.0 ? 0.0 : copysign(fmax(a - pow(a, kHqqP - 1.0) / beta, 0.0), v.r[k]);
+          t[k] = (v.x[k] - e) / s;
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < W; ++k) {
+        acc += v.q[k] - t[k];
+        tot += fabs(v.r[k]);
+      }
     }
+    if (it == 0) e0 = best = tot;
     const double z_new = acc / group;
     const double err = l1(z_new);
     if (!(err < best)) break;
@@ -173,10 +214,10 @@ __device__ __attribute__((noinline)) uint16_t hqq_group(const float* src, uint8_
   const uint16_t zb = f64_to_f16_bits(best_z);
   if (l1(f16_bits_to_f64(zb)) < e0) z16 = zb;
   const double zf = f16_bits_to_f64(z16);
-  for (int i = 0; i < group; i += 4) {
-    double quot[4];
-    for (int k = 0; k < 4; ++k) quot[k] = static_cast<double>(src[i + k]) / s;
-    *reinterpret_cast<uint32_t*>(dst + i) = hqq_word(quot, zf, qmax);
+  for (int i = 0; i < group; i += W) {
+    const Part v(src + i, s, zf, qmax);
+#pragma unroll
+    for (int k = 0; k < W; k += 4) *reinterpret_cast<uint32_t*>(dst + i + k) = hqq_word(v.quot + k, zf, qmax);
   }
   return z16;
 }
@@ -216,14 +257,18 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(GROUP == 
   } else {
     z16 = f64_to_f16_bits(-wmin / s);
   }
+  // Residuals of unclamped weights spread over half a scale: with a scale well above twice
+  // the bound one of them passes it all but surely, and the group starts with the plain rounds.
+  bool large = !degenerate && s > 2.4 * kHqqNoShrink;
   double quot[GROUP];
+  if (!large) {
 #pragma unroll
-  for (int i = 0; i < GROUP; ++i) {
-    quot[i] = static_cast<double>(wv[i]) / s;
-    asm volatile("" : "+v"(quot[i]));
+    for (int i = 0; i < GROUP; ++i) {
+      quot[i] = static_cast<double>(wv[i]) / s;
+      asm volatile("" : "+v"(quot[i]));
+    }
   }
   // The error sum of zero z, and the refit sum of the round that starts from it.
-  bool large = false;
   auto pass = [&](double z, double& refit) __attribute__((always_inline)) {
     double err = 0.0, acc = 0.0, amax = 0.0;
 #pragma unroll
@@ -242,7 +287,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(GROUP == 
     large = !(amax <= kHqqNoShrink);
     return err;
   };
-  if (!degenerate) {
+  if (!degenerate && !large) {
     const double z0 = f16_bits_to_f64(z16);
     // Pass 0 is the min/max zero, pass p > 0 the zero of round p - 1; the pass after the
     // search ended is the best zero in fp16.  One copy of the unrolled pass serves all.
@@ -274,7 +319,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(GROUP == 
   }
   uint8_t* dst = codes + n * K + static_cast<long long>(g) * GROUP;
   if (large) {
-    z16 = hqq_group(src, dst, GROUP, s, z16, qmax);
+    z16 = hqq_group<GROUP == 64 ? 4 : 8>(src, dst, GROUP, s, z16, qmax);
   } else {
     const double zf = f16_bits_to_f64(z16);
 #pragma unroll
