@@ -299,8 +299,8 @@ size_t subspec_tree_workspace_bytes(int R, int V, int k);
 
 /* Launch shape subspec_tree_expand uses for (R, V, k), computed on the host with no
  * device access: every row is cut into `chunks` slices of `chunk_len` logits (the
- * last may be shorter), one 256-thread workgroup each, so the grid has at most
- * R * chunks workgroups (small R takes fewer, longer slices); `list_len` is the per-thread candidate list length (8, 16 or 32, the
+ * last may be shorter), one 256-thread workgroup each, so the grid has R * chunks
+ * workgroups; `list_len` is the per-thread candidate list length (8, 16 or 32, the
  * kernel's template argument).  Outputs are host pointers.  Returns SUBSPEC_OK,
  * SUBSPEC_EINVAL for a null output, or SUBSPEC_EUNSUPPORTED for an (R, V, k) that
  * subspec_tree_expand would reject. */

@@ -1106,7 +1106,7 @@ int subspec_tree_plan(int R, int V, int k, int* chunks, int* chunk_len, int* lis
   if (R < 1 || R > subspec::kTreeMaxRows || V < 8 || V % 8 || k < 1 || k > subspec::kTreeMaxK ||
       static_cast<long long>(R) * V >= (1LL << 31) || k > static_cast<long long>(R) * V)
     return fail(SUBSPEC_EUNSUPPORTED, "tree_plan: (R, V, k) out of the supported range");
-  subspec::tree_plan(R, V, chunks, chunk_len);
+  subspec::tree_plan(R, V, k, chunks, chunk_len);
   *list_len = k <= 8 ? 8 : k <= 16 ? 16 : 32;
   return SUBSPEC_OK;
 }
@@ -1139,7 +1139,7 @@ int subspec_tree_expand(const void* logits, const float* parent_logp, int R, int
   a.V = V;
   a.k = k;
   a.inv_t = 1.f / temperature;
-  subspec::tree_launch_plan(R, V, &a.chunks, &a.chunk_len);
+  subspec::tree_plan(R, V, k, &a.chunks, &a.chunk_len);
   char* base = static_cast<char*>(ws);
   a.cnt = reinterpret_cast<unsigned*>(base);
   char* p = base + subspec::kSplitCounterBytes;

@@ -22,9 +22,8 @@ struct TreeArgs {
   int* out_token;
   float* out_score;
 };
-void tree_plan(int R, int V, int* chunks, int* chunk_len);
-// The slices the launch takes: at most tree_plan's number (whose workspace they use).
-void tree_launch_plan(int R, int V, int* chunks, int* chunk_len);
+// The slices of a row and the logits of each.
+void tree_plan(int R, int V, int k, int* chunks, int* chunk_len);
 size_t tree_workspace_bytes(int R, int V, int k);
 hipError_t launch_tree_expand(const TreeArgs& a, hipStream_t st);
 

@@ -16,9 +16,9 @@
 //
 // What bounds it is the chain of latencies of the two phases, not the logits: of 20.2 us
 // at R = 6, V = 152064, k = 6 with 450 workgroups, 2.2 were the launch, 3.0 the logits, 3.5
-// the workgroup's selection, 4.1 the completion and 7.4 the second phase.  So at most 256
-// workgroups run (one thread of the second phase per workgroup's list, half the atomics
-// on the counter), the lists arrive in the second phase's registers with one wait, and
+// the workgroup's selection, 4.1 the completion and 7.4 the second phase.  So up to
+// 32 rows at most 256 workgroups run (one thread of the second phase per workgroup's list,
+// half the atomics on the counter), the lists arrive in the second phase's registers with one wait, and
 // the reductions stay in DPP moves.
 #include <climits>
 #include <cmath>
@@ -591,10 +591,12 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree_expand(TreeArgs a) {
 
 }  // namespace
 
-void tree_plan(int R, int V, int* chunks, int* chunk_len) {
-  // About two workgroups per CU of the 256, at least 2048 logits (one 16-byte load
-  // per thread) each.
-  int c = (512 + R - 1) / R;
+void tree_plan(int R, int V, int k, int* chunks, int* chunk_len) {
+  // At least 2048 logits (one 16-byte load per thread) per workgroup, and up to 32 rows at
+  // most one workgroup per thread of the second phase (256 in all; see the head of this
+  // file).  With more rows the slices get long (R = 64: 29.5 us with 256 workgroups, 28.3
+  // with 512).
+  int c = R <= 32 ? kTreeThreads / R : (2 * kTreeThreads + R - 1) / R;
   const int cmax = (V + 2047) / 2048;
   if (c > cmax) c = cmax;
   if (c < 1) c = 1;
@@ -604,22 +606,9 @@ void tree_plan(int R, int V, int* chunks, int* chunk_len) {
   *chunks = (V + len - 1) / len;
 }
 
-void tree_launch_plan(int R, int V, int* chunks, int* chunk_len) {
-  // At most one workgroup per thread of the second phase (256 in all; see the head of this
-  // file).  With more rows the slices get long (R = 64: 29.5 us with 256 workgroups, 28.3
-  // with 512).
-  tree_plan(R, V, chunks, chunk_len);
-  if (R > 32) return;
-  const int most = kTreeThreads / R;
-  if (*chunks <= most) return;
-  const int len = ((V + most - 1) / most + 7) / 8 * 8;
-  *chunk_len = len;
-  *chunks = (V + len - 1) / len;
-}
-
 size_t tree_workspace_bytes(int R, int V, int k) {
   int chunks = 0, len = 0;
-  tree_plan(R, V, &chunks, &len);
+  tree_plan(R, V, k, &chunks, &len);
   const size_t blocks = static_cast<size_t>(R) * chunks;
   return kSplitCounterBytes + blocks * 2 * sizeof(float) + blocks * k * (sizeof(float) + sizeof(int));
 }
