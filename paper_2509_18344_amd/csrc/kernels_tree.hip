@@ -16,9 +16,9 @@
 //
 // What bounds it is the chain of latencies of the two phases, not the logits: of 20.2 us
 // at R = 6, V = 152064, k = 6 with 450 workgroups, 2.2 were the launch, 3.0 the logits, 3.5
-// the workgroup's selection, 4.1 the completion and 7.4 the second phase.  So up to
-// 32 rows at most 256 workgroups run (one thread of the second phase per workgroup's list,
-// half the atomics on the counter), the lists arrive in the second phase's registers with one wait, and
+// the workgroup's selection, 4.1 the completion and 7.4 the second phase.  So no more
+// workgroups run than the second phase's threads hold lists (256 up to 32 rows; tree_plan),
+// the lists arrive in the second phase's registers with one wait, and
 // the reductions stay in DPP moves.
 #include <climits>
 #include <cmath>
@@ -592,11 +592,20 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree_expand(TreeArgs a) {
 }  // namespace
 
 void tree_plan(int R, int V, int k, int* chunks, int* chunk_len) {
-  // At least 2048 logits (one 16-byte load per thread) per workgroup, and up to 32 rows at
-  // most one workgroup per thread of the second phase (256 in all; see the head of this
-  // file).  With more rows the slices get long (R = 64: 29.5 us with 256 workgroups, 28.3
-  // with 512).
-  int c = R <= 32 ? kTreeThreads / R : (2 * kTreeThreads + R - 1) / R;
+  // Workgroups in all, at least 2048 logits (one 16-byte load per thread) each:
+  //  - up to 32 rows 256, one list per thread of the second phase (see the head of this
+  //    file), while the slices stay short: with lists of 32 (k > 16) the insertions of a long
+  //    slice cost more, and how many depends on the logits (eight sets each, k = 32: R = 24,
+  //    V = 32000 37 to 64 us with 256 and 43 to 53 with 512; R = 32, V = 152064 90 and 62;
+  //    R = 16 31 to 49 and the same, 152064 48 to 60 and 52 to 55), so there up to 16 rows;
+  //  - up to 128 rows at most 512, two lists per thread, which are held in registers: the
+  //    16 slices a row that 512 / 33 rounds up to leave a third list for 16 threads, read
+  //    only when needed (R = 33, k = 6 26.2 us, with 15 slices 24.2; R = 63 30.9 and 26.8);
+  //  - with more rows the number is rounded up (171 rows of 152064 in two workgroups each
+  //    42.8 us at k = 6 against 46.9, 300 rows 57 against 71), except for lists of 32, of
+  //    which a thread holds one (R = 300, k = 32 212 us and 188).
+  const int total = R <= 16 || (R <= 32 && k <= 16) ? kTreeThreads : 2 * kTreeThreads;
+  int c = R <= 128 || k > 16 ? total / R : (total + R - 1) / R;
   const int cmax = (V + 2047) / 2048;
   if (c > cmax) c = cmax;
   if (c < 1) c = 1;

@@ -252,8 +252,8 @@ def test_tree_expand_argument_errors_need_no_gpu():
 
 
 def test_tree_plan_shapes():
-    # the launch's own slices: at most 256 workgroups up to 32 rows and about 512 beyond,
-    # each at least 2048 logits (one 16-byte load per thread) unless the row is shorter;
+    # the launch's own slices: at most 256 workgroups up to 32 rows (16 with lists of 32),
+    # at most 512 up to 128 and about as many beyond, each at least 2048 logits (one 16-byte load per thread) unless the row is shorter;
     # slices are multiples of 8 and cover the row
     assert ss.subspec_tree_plan(6, 152064, 6) == (42, 3624, 8)
     assert ss.subspec_tree_plan(64, 152064, 6) == (8, 19008, 8)
@@ -261,6 +261,14 @@ def test_tree_plan_shapes():
     assert ss.subspec_tree_plan(1024, 64, 32) == (1, 64, 32)
     assert ss.subspec_tree_plan(37, 4096, 17) == (2, 2048, 32)
     assert ss.subspec_tree_plan(3, 2048, 9)[2] == 16
+    for R in range(1, 129):
+        for k in (1, 6, 8, 16, 17, 32):
+            c, n, _ = ss.subspec_tree_plan(R, 152064, k)
+            # what the threads of the second phase hold in registers at k <= 8: two lists each
+            assert R * c <= (256 if R <= 16 or (R <= 32 and k <= 16) else 512), (R, k, c)
+    assert ss.subspec_tree_plan(33, 152064, 6) == (15, 10144, 8)
+    assert ss.subspec_tree_plan(32, 152064, 32) == (16, 9504, 32)
+    assert ss.subspec_tree_plan(171, 152064, 6)[0] == 3 and ss.subspec_tree_plan(171, 152064, 32)[0] == 2
     for R, V, k in [(1, 8, 1), (6, 1000, 6), (128, 152064, 6), (1000, 2048, 32), (7, 152064, 16)]:
         c, n, _ = ss.subspec_tree_plan(R, V, k)
         assert n % 8 == 0 and (c - 1) * n < V <= c * n and R * c <= 1024, (R, V, k)
