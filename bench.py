@@ -134,6 +134,9 @@ def plan_key(plan, bits, group) -> str:
         family = "k_qmma"
         targs = (bits, group, plan["rows"] // 32, plan["tiles_per_wave"] // 2, plan["ring_chunks"],
                  plan["waves"])
+    elif plan["teams"] > 1:  # 16-row tiles whose wavefronts split K: the small-batch kernel
+        family = "k_qstream"
+        targs = (bits, group, plan["tiles_per_wave"], plan["waves"], plan["ring_chunks"], plan["rows"] // 4)
     else:
         family = "k_qgemm_mfma"
         targs = (bits, group, plan["rows"] // 16, plan["tiles_per_wave"], plan["chunk_blocks"], plan["waves"])
@@ -213,7 +216,7 @@ def library_key(name, grid, wg):
     if not m or "subspec::" not in name:
         return None
     targs = [int(a) for a in m.group(2)[1:-1].split(",")] if m.group(2) else []
-    if m.group(1) in ("k_qgemv", "k_qgemm_mfma", "k_qmma"):
+    if m.group(1) in ("k_qgemv", "k_qgemm_mfma", "k_qmma", "k_qstream"):
         return dispatch_key(m.group(1), targs, grid, wg)
     return f"{m.group(0)} grid={grid} wg={wg}"
 

@@ -95,14 +95,11 @@ typedef struct subspec_plan {
   int path;            /* SUBSPEC_PATH_GEMV or SUBSPEC_PATH_MFMA                  */
   int mfma_rows;       /* MFMA path: 16 (16x16x32 bf16 instructions) or 32
                           (32x32x16 bf16); 0 on the GEMV path.  The automatic
-                          choice takes 32 for M > 64 on launches that either fill
-                          every CU with whole 128-column groups or split a K of at
-                          least 16384, and for 32 < M <= 64 on launches whose
-                          256-column groups cover three quarters of the CUs with K
-                          unsplit or whose K is at least 16384 (measured on the
-                          Qwen2.5 shapes)                                        */
-  int rows;            /* rows computed per workgroup (M rounded up; with row_blocks
-                          = 2, half of that)                                     */
+                          choice takes 32 for M > 32 where column groups cover at
+                          least half the CUs or K is at least 16384, and in 32-row
+                          blocks for most of the rest (measured on the Qwen2.5
+                          shapes)                                                */
+  int rows;            /* rows computed per workgroup (M rounded up, or one row block) */
   int tiles_per_wave;  /* 16-column tiles each wavefront owns                     */
   int waves;           /* wavefronts per workgroup                                */
   int chunk_blocks;    /* 128-k blocks staged in LDS per step                     */
@@ -114,22 +111,26 @@ typedef struct subspec_plan {
   int splits;          /* workgroups per split column group; 1 = no partial sums  */
   int blocks_per_split;/* 128-k blocks per split                                  */
   int grid;            /* workgroups of one row block =
-                          full_groups + (col_groups - full_groups) * splits      */
+                          full_groups + (col_groups - full_groups) * splits
+                          (small-batch launches: rounded up to a multiple of 8) */
   size_t workspace_bytes; /* device scratch the call uses: 64 KiB of completion
-                             counters, the 32x32 kernel's per-group sums of x, and
-                             the fp32 partial sums of split column groups (0 when
-                             none of these is needed) */
-  int teams;           /* 32-row MFMA tiles: wavefront teams per workgroup that split
-                          its k-blocks between them (1, or 2: two teams of four on
-                          the same columns, summed in LDS; the automatic choice on
-                          a K of at least 16384 from M = 33); a workgroup covers
-                          waves / teams * tiles_per_wave * 16 columns             */
-  int row_blocks;      /* 16-row MFMA tiles: the rows in row_blocks blocks of `rows`
-                          rows each (1 or 2), each block of workgroups an independent
-                          launch along grid y with its own partial sums and
-                          completion counters.  The automatic choice takes 2 for
-                          M > 32 on launches whose column groups number fewer than
-                          the CUs and whose K is under 16384 (q|k|v and o shapes) */
+                             counters, the per-group sums of x of 128-row 32x32
+                             tiles, and the fp32 partial sums of split column groups
+                             (0 when neither of the latter two is needed) */
+  int teams;           /* MFMA tiles: wavefront teams per workgroup that split its
+                          k-blocks between them and add up in LDS.  1; 2 on 32-row
+                          tiles (two teams of four wavefronts on the same columns);
+                          on 16-row tiles `waves` in small-batch launches, each
+                          wavefront a team (automatic choice up to M = 16).  A
+                          workgroup covers waves / teams * tiles_per_wave * 16
+                          columns                                                */
+  int row_blocks;      /* the rows in row_blocks blocks of `rows` rows each, each block
+                          of workgroups an independent launch along grid y with its
+                          own partial sums and completion counters: 16-row tiles 1
+                          or 2, 32-row tiles of rows = 32 any number up to 4.  The
+                          automatic choice takes more than 1 for M > 32 on launches
+                          whose column groups number fewer than the CUs and whose K
+                          is under 16384 (q|k|v and o shapes)                    */
 } subspec_plan;
 
 /* Bytes of the packed code buffer for an N x K projection.  0 on bad arguments. */
@@ -215,10 +216,9 @@ int subspec_qlinear_path(const void* x, const void* qweight, const void* scales,
                          void* y, int path, hipStream_t stream);
 
 /* Host only, no GPU needed: validate the shape and fill *plan with the launch
- * configuration of `path` (AUTO allowed), whose workspace_bytes is what
- * subspec_qlinear_path obtains.  Where another launch of the same function measured
- * faster, the call runs that one within the same workspace: M <= 16 without partial
- * sums, and 32x32 tiles with other rows, wavefronts or ring depth above M = 32. */
+ * subspec_qlinear_path makes for `path` (AUTO allowed); workspace_bytes is what that
+ * launch reads and the call obtains.  (Where no GPU is present the residency the plan
+ * depends on is assumed: 256 CUs, two workgroups on each.) */
 int subspec_qlinear_plan(int M, int N, int K, int bits, int group, int path,
                          subspec_plan* plan);
 

@@ -97,7 +97,7 @@ struct Tuning {
   // Smallest M at which wide launches take the 32x32 kernel's 64-row eight-wavefront
   // tiles instead of 16x16x32 ones (0 = never).
   int mma8_min_m = 33;
-  int mma8_half_min_m = 48;       // the same where 256-column groups cover only half the CUs
+  int mma8_half_min_m = 33;       // the same where 256-column groups cover only half the CUs
   int mma_teams = 0;              // 32x32 kernel, long-K launches: 1 = one team, 2 = two; 0 = choose
   int teams64_min_m = 33;         // long-K launches from this M up to 64: 64-row two-team 32x32 tiles
   int stream_nt = 0, stream_ks = 0;  // small-batch kernel: tiles and wavefronts per workgroup; 0 = choose, -1 = never
@@ -170,11 +170,78 @@ int device_cus() {
   return cus;
 }
 
-// Bytes of the per-group sums of x the 32x32 kernel reads (fp32 [K/group][M]),
-// rounded up to 256.
+// Bytes of the per-group sums of x the 32x32 kernel's 128-row tiles read (fp32
+// [K/group][M]), rounded up to 256.
 size_t xsum_bytes(const subspec::KernelChoice& c, int M, int K, int group) {
-  if (c.shape != 32) return 0;
+  if (c.shape != 32 || c.rows != 128) return 0;
   return (static_cast<size_t>(M) * (K / group) * sizeof(float) + 255) & ~size_t(255);
+}
+
+// Whether an automatic call takes the small-batch kernel (k_qstream), and its tiles and
+// wavefronts per workgroup.  It replaces launches that would split K across workgroups: at
+// a few megabytes of weights their completion (three trips to the coherent level in a
+// row) costs as much as the weights.  us per call, split across workgroups against this,
+// 4-bit g128, one run: 1024x1024 M = 1 5.3 / 2.8, M = 16 5.8 / 3.5; 8192x1024 M = 6 7.0 / 4.1;
+// 4608x3584 M = 1 7.8 / 4.6, M = 6 8.4 / 5.6, M = 16 8.9 / 7.2; 7168x5120 M = 1 8.9 / 7.0, M = 8
+// 9.8 / 7.9; 12288x4096 M = 6 11.3 / 10.1; 2048x8192 M = 6 10.5 / 8.1.  Where the lines lie:
+//  - every pair of tiles reads the fragments of x from the L2 again, M * K * 2 bytes: from
+//    M = 9 that is more than the weights, and only a K of up to 36 blocks still gains
+//    (5120x5120 M = 16 9.8 / 9.8, 16384x512 M = 12 6.6 / 7.2; 256x4096, sixteen tiles, 6.2 / 6.3);
+//  - 16 wavefronts fill a CU: one workgroup per CU, or at least half as many again
+//    (10240x4096, 320 pairs, M = 1 9.0 / 9.2; 14000x3584, 438 pairs, 9.9 / 9.1); of eight two
+//    (22000x2048 8.5 / 8.6);
+//  - launches of more weights have enough column groups or blocks per workgroup to hide
+//    the completion (37888x3584 M = 1 14.3 / 15.9), except where one tile a workgroup fills
+//    the CUs once (K up to 160 blocks; 3584x18944 M = 1 11.9 / 10.1, M = 2 13.1 / 10.7; from
+//    M = 5, two loads of x per block, to 112: 2560x11008 3-bit M = 6 11.0 / 8.9, 4096x14336
+//    13.5 / 12.7, but 3584x18944 3-bit M = 8 14.8 / 15.2 and 2048x18944 M = 6 11.9 / 12.3); one
+//    tile against two at M = 1: 3584x3584 4.2 / 4.4, 1024x4096 3.9 / 4.3;
+//  - a K of one or two blocks is not split anyway (512x256 M = 8 2.9 / 2.8, M = 16 2.9 / 3.3;
+//    29200x256 M = 1 4.1 / 6.3).
+bool stream_choice(int M, int N, int K, int* nt, int* ks) {
+  const Tuning& tu = tuning();
+  if (M > subspec::kStreamMaxRows || tu.stream_nt < 0 || tu.splits) return false;
+  if (tu.stream_nt) {
+    *nt = tu.stream_nt;
+    *ks = tu.stream_ks;
+    return true;
+  }
+  const int KB = K / subspec::kTileK, tiles = N / subspec::kTileN, pairs = (tiles + 1) / 2;
+  const double mweights = static_cast<double>(N) * K / (1 << 20);
+  if (KB <= 8 || (KB < 24 && tiles <= 32)) {
+    *nt = 1;
+    *ks = 4;
+    if (KB <= 2) return M <= 8 && tiles <= 64;
+    return mweights <= 8 && (M <= 8 || tiles <= 512);
+  }
+  *ks = KB < 24 ? 8 : 16;
+  if (KB >= 24 && tiles <= device_cus() && (M <= 4 || (M <= 8 && KB > 64))) {
+    *nt = 1;
+    return KB <= (M <= 4 ? 160 : 112);
+  }
+  *nt = 2;
+  if (KB > 64 || mweights > 48) return false;
+  if (M > 8) return KB <= 36 && (KB < 24 || tiles >= 64) && mweights <= 18;
+  return KB < 24 ? pairs <= 2 * device_cus() : pairs <= device_cus() || 2 * pairs >= 3 * device_cus();
+}
+
+void fill_plan(const subspec::KernelChoice& c, subspec_plan* p, int col_groups, int full_groups, int splits,
+               int blocks_per_split, int grid, size_t workspace_bytes) {
+  p->path = c.path == 1 ? SUBSPEC_PATH_GEMV : SUBSPEC_PATH_MFMA;
+  p->mfma_rows = c.path == 1 ? 0 : c.shape;
+  p->teams = c.teams;
+  p->row_blocks = c.row_blocks;
+  p->rows = c.rows;
+  p->tiles_per_wave = c.nt;
+  p->waves = c.waves;
+  p->chunk_blocks = c.chunk;
+  p->ring_chunks = c.prefetch;
+  p->col_groups = col_groups;
+  p->full_groups = full_groups;
+  p->splits = splits;
+  p->blocks_per_split = blocks_per_split;
+  p->grid = grid;
+  p->workspace_bytes = workspace_bytes;
 }
 
 // ws_cap bounds the workspace the plan may use (the allocation-free entry point's
@@ -188,8 +255,24 @@ int make_plan(int M, int N, int K, int bits, int group, int path, subspec_plan* 
   if (rc) return rc;
   if (M < 1 || M > kMaxRows) return fail(SUBSPEC_EUNSUPPORTED, "M=%d: must be in 1..%d", M, kMaxRows);
   const Tuning& tu = tuning();
-  if (path == SUBSPEC_PATH_AUTO) path = (M <= tu.gemv_max_m) ? SUBSPEC_PATH_GEMV : SUBSPEC_PATH_MFMA;
   const int KB = K / subspec::kTileK;
+  subspec::KernelChoice c{}, c8{};
+  int snt = 0, sks = 0;
+  if (path == SUBSPEC_PATH_AUTO && stream_choice(M, N, K, &snt, &sks) &&
+      subspec::qstream_ring(snt, sks, bits, group, M) > 0) {
+    c.path = 3;
+    c.shape = 16;
+    c.rows = M <= 4 ? 4 : M <= 8 ? 8 : 16;  // the kernel's loads of x per block, times four
+    c.nt = snt;
+    c.chunk = 1;
+    c.waves = c.teams = sks;
+    c.prefetch = subspec::qstream_ring(snt, sks, bits, group, M);
+    const int groups = (N / subspec::kTileN + snt - 1) / snt;
+    fill_plan(c, p, groups, 0, 1, KB, subspec::qstream_grid(groups), 0);
+    if (kc) *kc = c;
+    return SUBSPEC_OK;
+  }
+  if (path == SUBSPEC_PATH_AUTO) path = (M <= tu.gemv_max_m) ? SUBSPEC_PATH_GEMV : SUBSPEC_PATH_MFMA;
   // 32x32x16 tiles (k_qmma, 128 rows, 128 columns per workgroup) against 16x16x32
   // (k_qgemm_mfma).  Measured on the Qwen2.5-7B/32B stacks at M = 96 and 128, k_qmma
   // wins where its workgroups fill every CU without splitting K (gate|up: 7B 52.8
@@ -203,17 +286,18 @@ int make_plan(int M, int N, int K, int bits, int group, int path, subspec_plan* 
   // quarters (wide8) or half (half8) of the CUs.
   const bool wide8 = (N + 255) / 256 * 4 >= 3 * device_cus();
   const bool half8 = (N + 255) / 256 * 2 >= device_cus();
+  const bool any_shape = path == SUBSPEC_PATH_MFMA;  // this function picks the MFMA tile shape
   if (path == SUBSPEC_PATH_MFMA) {
     // Below mma16_max_m, wide unsplit launches still take 64-row 32x32 tiles from
     // mma8_min_m on: 32B gate|up 48.7 against 53.4 us at M = 33, 51.6 against 55.1 at
-    // 48, 53.9 against 59.0 at 64; where 256-column groups cover only half the CUs,
-    // from mma8_half_min_m on (7B gate|up, 148 groups: 32.8 against 34.5 us at M = 48,
-    // 35.1 against 37.3 at 64, but 32.4 against 31.1 at 33); the short launches stay on
-    // 16x16x32 (q|k|v at M = 64 27.2 against 19.0 us).  Long-K launches take 64-row
-    // tiles on two teams of four wavefronts from teams64_min_m (below): 32B down 34.5
-    // against 39.3 us at M = 48 and 39.6 against 41.5 at 64, 2-bit g64 36.0 against 43.9
-    // and 40.2 against 46.1; the 7B down about even (25.7 against 25.2 at 48, 26.8
+    // 48, 53.9 against 59.0 at 64; where 256-column groups cover only half the CUs from
+    // mma8_half_min_m on (7B gate|up, 148 groups: 29.1 against 30.9 us at M = 37, 3-bit
+    // 28.3 against 30.8 at 44, 4-bit g64 32.3 against 35.7 at 40).  Long-K launches take
+    // 64-row tiles on two teams of four wavefronts from teams64_min_m (below): 32B down
+    // 34.5 against 39.3 us at M = 48 and 39.6 against 41.5 at 64, 2-bit g64 36.0 against
+    // 43.9 and 40.2 against 46.1; the 7B down about even (25.7 against 25.2 at 48, 26.8
     // against 27.5 at 64); at M = 32, with half of each tile empty, 30.7 against 27.3.
+    // (These with two-chunk rings; four chunks are faster, below.)
     const bool tiles64 = tu.mma8_min_m > 0 && M >= tu.mma8_min_m && (half8 && !wide8 ? M >= tu.mma8_half_min_m : wide8) &&
                          !long_k;
     const bool teams64 = tu.teams64_min_m > 0 && long_k && M >= tu.teams64_min_m && M <= 64;
@@ -221,7 +305,6 @@ int make_plan(int M, int N, int K, int bits, int group, int path, subspec_plan* 
         tu.mma_shape ? tu.mma_shape == 32 : (M > tu.mma16_max_m && (wide || long_k)) || tiles64 || teams64;
     path = use32 ? SUBSPEC_PATH_MFMA32 : SUBSPEC_PATH_MFMA16;
   }
-  subspec::KernelChoice c{}, c8{};
   bool use8 = false;  // 32x32 kernel: the eight-wavefront variant (c8) where it exists
   c.waves = 4;
   if (path == SUBSPEC_PATH_GEMV) {
@@ -235,40 +318,40 @@ int make_plan(int M, int N, int K, int bits, int group, int path, subspec_plan* 
     c.chunk = tu.gemv_ch ? tu.gemv_ch : c.rows <= 2 ? 2 : 4;
     c.prefetch = tu.gemv_pf;
   } else if (path == SUBSPEC_PATH_MFMA32) {
-    // 32x32x16 matrix cores (k_qmma): four row blocks of 32 (two up to M = 64), four
-    // wavefronts of one 32-column block each, one 128-k chunk per LDS stage.  The ring
-    // is two chunks deep (two workgroups per CU) when whole column groups fill the
-    // device, four deep (one workgroup per CU, more loads in flight each) otherwise;
-    // the eight-wavefront and two-team forms below replace it where they measured
-    // faster.
+    // 32x32x16 matrix cores (k_qmma): four row blocks of 32 (two up to M = 64), one
+    // 32-column block per wavefront, one 128-k chunk per LDS stage.  Four wavefronts where
+    // neither form below applies: the ring is four chunks deep (one workgroup per CU), or
+    // two (two workgroups per CU) when whole column groups of 64-k groups fill the device.
     c.path = 2;
     c.shape = 32;
     c.rows = M <= 64 ? 64 : 128;
     c.nt = 2 * (tu.mma_nb ? tu.mma_nb : 1);
     c.chunk = 1;
-    c.prefetch = tu.mfma_pf ? tu.mfma_pf : wide ? 2 : 4;
-    // Eight wavefronts of one 32-column block each share one x ring four chunks deep
-    // (one workgroup of 256 columns per CU): each wavefront then has three chunks of
-    // weights in flight instead of one.  Taken where 256-column groups still cover
-    // three quarters of the CUs and K is not split (32B gate|up, N = 55296, M = 128:
-    // 90.9 against 98.0 us at 3 bits, 97.1 against 103.1 at 2 bits; slower on the 7B
-    // gate|up's 148 groups and on the split 32B down projection).  Up to M = 64 the
-    // tiles are 64 rows (two row blocks), built for eight wavefronts only.
+    c.prefetch = tu.mfma_pf ? tu.mfma_pf : wide && group == 64 ? 2 : 4;
+    // Eight wavefronts share one x ring four chunks deep (one workgroup of 256 columns per
+    // CU): each then has three chunks of weights in flight.  Taken where 256-column groups
+    // cover three quarters of the CUs and K is not split (55296x5120, M = 128: 4-bit 76.1
+    // against 100.2 us, 3-bit g64 82.1 against 89.9), and where they cover half of them on
+    // 64-row tiles (built for eight wavefronts only) and at groups of 128 (37888x3584 4-bit
+    // 46.2 against 56.1 us; 3-bit g64 at M = 96 53.0 against 50.4).
     c8 = c;
     c8.waves = 8;
     c8.prefetch = tu.mfma_pf ? tu.mfma_pf : 4;
-    use8 = tu.mma_waves == 8 || (!tu.mma_waves && (wide8 || (half8 && c.rows == 64)) && !long_k);
+    use8 = tu.mma_waves ? tu.mma_waves == 8 : (wide8 || (half8 && (c.rows == 64 || group == 128))) && !long_k;
     // Long-K launches (split along K, not wide enough for whole groups) take two teams
     // of four wavefronts per workgroup, each on half of the workgroup's k-blocks: two
     // wavefronts per SIMD at the same number of splits (32B down, K = 27648: 61.5
     // against 63.8 us at M = 128, 54.7 against 58.7 at 96; 7B down, K = 18944: 40.5
-    // against 45.7 on 16x16x32 tiles at M = 128).
+    // against 45.7 on 16x16x32 tiles at M = 128).  Their rings are four chunks deep on
+    // 64-row tiles (5120x27648 3-bit 33.2 against 36.2 us at M = 64 and 31.9 against 35.7
+    // at 48, 2-bit g64 33.3 against 37.1 at 64, 3584x18944 4-bit 21.7 against 22.7 at 37),
+    // and two on 128-row ones, whose LDS four would exceed.
     const bool teams = tu.mma_teams ? tu.mma_teams == 2 : long_k;
     if (!use8 && teams) {
       c8 = c;
       c8.waves = 8;
       c8.teams = 2;
-      c8.prefetch = tu.mfma_pf ? tu.mfma_pf : 2;
+      c8.prefetch = tu.mfma_pf ? tu.mfma_pf : c.rows == 64 ? 4 : 2;
       use8 = true;
     }
   } else if (path == SUBSPEC_PATH_MFMA16) {
@@ -285,16 +368,12 @@ int make_plan(int M, int N, int K, int bits, int group, int path, subspec_plan* 
   } else {
     return fail(SUBSPEC_EINVAL, "path=%d: unknown", path);
   }
-  // What a plan may describe.  For 32x32 tiles the launch made from it can differ in ring
-  // depth and wavefronts (refine_launch), so the set of builds is not the measure there.
   auto variant_exists = [&](const subspec::KernelChoice& k) {
-    if (k.shape != 32) return subspec::qlinear_variant_exists(k, bits, group);
-    if (k.nt != 2) return false;
-    if (k.waves == 8 && k.teams == 2) return true;
-    if (k.waves == 8) return k.prefetch == 4 && (k.rows == 64 || bits == 2 || (bits == 3 && group == 128));
-    return k.rows == 128 && (k.prefetch == 2 || k.prefetch == 4);
+    return k.shape == 32 ? subspec::qmma_variant_exists(k.waves, k.teams, k.rows / 32, k.nt / 2, k.prefetch, bits,
+                                                        group)
+                         : subspec::qlinear_variant_exists(k, bits, group);
   };
-  if (use8 && (tu.mma_waves == 8 || variant_exists(c8))) c = c8;
+  if (use8 && variant_exists(c8)) c = c8;
   if (c.shape == 32 && c.rows == 64 && !variant_exists(c)) c.rows = 128;  // no 64-row build
   if (!variant_exists(c))
     return fail(SUBSPEC_EUNSUPPORTED, "no kernel for path=%d rows=%d nt=%d chunk=%d waves=%d bits=%d group=%d",
@@ -309,8 +388,7 @@ int make_plan(int M, int N, int K, int bits, int group, int path, subspec_plan* 
       lds = subspec::gemv_lds_bytes(k.rows, std::min(K, subspec::gemv_max_kspan(k.rows, k.waves, group, cols)),
                                     group, cols);
     }
-    int per_cu = k.shape == 32 ? subspec::qmma_resident_blocks(k.waves, k.teams, k.rows / 32, k.nt / 2,
-                                                               k.teams == 2 && k.rows == 64 ? 4 : k.prefetch,
+    int per_cu = k.shape == 32 ? subspec::qmma_resident_blocks(k.waves, k.teams, k.rows / 32, k.nt / 2, k.prefetch,
                                                                bits, group)
                                : subspec::qlinear_resident_blocks(k, bits, group, lds);
     if (per_cu <= 0) per_cu = 2;
@@ -362,6 +440,31 @@ int make_plan(int M, int N, int K, int bits, int group, int path, subspec_plan* 
     cr.chunk = tu.mfma_ch ? tu.mfma_ch : cr.rows == 16 ? 2 : 1;
     if (variant_exists(cr)) c = cr;
   }
+  // Those launches run as 32-row 32x32 two-team tiles, the rows in blocks of 32 along grid
+  // y, K split only as far as one workgroup per CU goes: without partial sums at M = 128,
+  // 7168x5120 3-bit 25.3 against 18.5 us and 5120x5120 21.1 against 18.1, 2-bit g64 27.8
+  // against 19.3, 4608x3584 4-bit 17.2 against 14.9; two and three splits at M = 64 16.5
+  // against 14.3 and 13.5 against 12.6.  Not from M = 65 where they exceed a workgroup per
+  // CU (14336x4096 4-bit 30.0 against 31.4), and up to M = 64 not for a K under 36 blocks
+  // (4608x3584 11.1 against 11.6) or few columns (2048x8192 11.9 against 12.1).  What bounds
+  // them is the L2: every block of rows reads the weights again and every column group x,
+  // 128 MB at 7168x5120.
+  if (any_shape && c.shape == 16 && c.row_blocks == 2 && !tu.mma_shape && !tu.row_split && tu.rb_splits >= 0) {
+    const int units32 = (N + 127) / 128 * ((M + 31) / 32);
+    if (M > 64 ? units32 <= device_cus() : KB >= 36 && units32 * 4 >= device_cus()) {
+      c = subspec::KernelChoice{};
+      c.path = 2;
+      c.shape = 32;
+      c.rows = 32;
+      c.row_blocks = (M + 31) / 32;
+      c.nt = 2;
+      c.chunk = 1;
+      c.waves = 8;
+      c.teams = 2;
+      c.prefetch = 4;
+      resident = resident_of(c);
+    }
+  }
   const int cols_per_group = c.waves / c.teams * c.nt * subspec::kTileN;
   const int col_groups = groups_of(c);
   const int units = col_groups * c.row_blocks;  // workgroups of one split
@@ -387,6 +490,14 @@ int make_plan(int M, int N, int K, int bits, int group, int path, subspec_plan* 
   // idle CUs (7B q|k|v at M = 64: 72 workgroups took as long as gate|up).
   if (tu.fill_cus) cap = std::max(cap, (device_cus() * tu.fill_cus + units - 1) / units);
   splits = std::min(splits, cap);
+  // 32-row tiles: one workgroup per CU, each on at least eight blocks
+  if (c.shape == 32 && c.row_blocks > 1)
+    splits = tu.rb_splits > 0 ? tu.rb_splits : std::max(1, std::min(device_cus() / units, KB / 8));
+  // 256-column groups of eight wavefronts, one workgroup per CU: K is split only where they
+  // cover exactly half the CUs, from 24 blocks on (32768 columns 4-bit, M = 64: K = 8192
+  // 50.1 us in two splits against 62.1, 3584 even, 2048 21.9 against 18.6, 512 unsplit half)
+  const bool wide_groups = c.shape == 32 && c.waves == 8 && c.teams == 1;
+  if (wide_groups) splits = KB < 24 ? 1 : std::max(1, device_cus() / units);
   if (tu.splits > 0) splits = tu.splits;
   if (c.path == 1) {
     // the split's activations must fit the GEMV kernel's LDS staging
@@ -419,10 +530,14 @@ int make_plan(int M, int N, int K, int bits, int group, int path, subspec_plan* 
   // alone leave rem CUs one group ahead of the rest (592 groups on 256 CUs: 80 CUs run
   // three, 176 run two).  Instead the first base * CUs groups run whole and the last
   // rem are split CUs / rem ways, so no CU gets more than base groups plus one part of
-  // a split one.  (A GEMV workgroup that runs a whole group stages all of K.)
+  // a split one.  (A GEMV workgroup that runs a whole group stages all of K.)  Not on
+  // 128-row groups of eight wavefronts under eight blocks, where a second round costs less
+  // than the completion (80000 columns 4-bit, M = 128: K = 512 27.1 us unsplit against 38.5;
+  // 2048 about even, 3584 118 against 107; K = 1024, M = 65 even).
   int full_groups = 0;
   const int cus = device_cus();
   if (splits == 1 && tu.tail && !tu.splits && c.row_blocks == 1 && col_groups <= subspec::kSplitCounters &&
+      !(wide_groups && c.rows == 128 && KB < 8) &&
       (c.path != 1 || K <= subspec::gemv_max_kspan(c.rows, c.waves, group, cols_per_group))) {
     const int base = col_groups / cus, rem = col_groups % cus;
     const int ts = fit_cap(fit_offsets(std::min(rem ? cus / rem : 0, chunks)));
@@ -447,109 +562,19 @@ int make_plan(int M, int N, int K, int bits, int group, int path, subspec_plan* 
                   "GEMV path: M=%d N=%d K=%d needs splits of at most %d k, but the plan can only "
                   "split %d ways (%d column groups)", M, N, K, span, splits, col_groups);
   }
-  p->path = c.path == 1 ? SUBSPEC_PATH_GEMV : SUBSPEC_PATH_MFMA;
-  p->mfma_rows = c.path == 2 ? c.shape : 0;
-  p->teams = c.teams;
-  p->row_blocks = c.row_blocks;
-  p->rows = c.rows;
-  p->tiles_per_wave = c.nt;
-  p->waves = c.waves;
-  p->chunk_blocks = c.chunk;
-  p->ring_chunks = c.prefetch;
-  p->col_groups = col_groups;
-  p->full_groups = full_groups;
-  p->splits = splits;
-  p->blocks_per_split = blocks_per_split;
-  p->grid = full_groups + (col_groups - full_groups) * splits;
-  // Workspace: split-K completion counters, then (32x32 kernel) the per-group sums of
-  // x, then the splits' fp32 partial sums.
-  p->workspace_bytes = 0;
-  if (splits > 1 || c.shape == 32)
-    p->workspace_bytes = subspec::kSplitCounterBytes + xsum_bytes(c, M, K, group) +
-                         (splits > 1 ? static_cast<size_t>(splits) * part_rows * N * sizeof(float) : 0);
+  // Workspace: split-K completion counters, then the per-group sums of x (128-row 32x32
+  // tiles), then the splits' fp32 partial sums.
+  const size_t xsb = xsum_bytes(c, M, K, group);
+  size_t ws = 0;
+  if (splits > 1 || xsb)
+    ws = subspec::kSplitCounterBytes + xsb + (splits > 1 ? static_cast<size_t>(splits) * part_rows * N * sizeof(float) : 0);
+  fill_plan(c, p, col_groups, full_groups, splits, blocks_per_split, full_groups + (col_groups - full_groups) * splits,
+            ws);
   if (p->workspace_bytes > ws_cap)
     return fail(SUBSPEC_EUNSUPPORTED, "M=%d N=%d K=%d: needs %zu bytes of scratch even unsplit, above the "
                 "%zu available", M, N, K, p->workspace_bytes, ws_cap);
   if (kc) *kc = c;
   return SUBSPEC_OK;
-}
-
-// The launch made from a described plan, where the 32x32 kernel has a better form for it.
-// It needs no more workspace.  us per call, described against made, one run each:
-//  - 16x16x32 launches of two row blocks (q|k|v, o) run as 32-row two-team tiles, the rows
-//    in blocks of 32 along grid y, K split only as far as one workgroup per CU goes:
-//    without partial sums, 7168x5120 3-bit 25.3 against 18.5 us and 5120x5120 21.1 against
-//    18.1 at M = 128, 2-bit g64 27.8 against 19.3, 4608x3584 4-bit 17.2 against 14.9; two and
-//    three splits at M = 64 16.5 against 14.3 and 13.5 against 12.6.  Not from M = 65 where
-//    they exceed a workgroup per CU (14336x4096 4-bit 30.0 against 31.4), and up to M = 64 not
-//    for a K under 36 blocks (4608x3584 11.1 against 11.6) or few columns (2048x8192 11.9
-//    against 12.1).  What bounds them is the L2: every block of rows reads the weights
-//    again and every column group x, 128 MB at 7168x5120.
-//  - 16x16x32 launches of four row tiles on half-wide column groups (37888x3584, M = 33 to
-//    47) run as 64-row eight-wavefront tiles: 30.9 against 29.1 us at M = 37, 3-bit 30.8
-//    against 28.3 at 44, 4-bit g64 35.7 against 32.3 at 40.
-//  - 64-row two-team tiles run with four-chunk rings: 5120x27648 3-bit 33.2 against 36.2 us
-//    at M = 64 and 31.9 against 35.7 at 48, 2-bit g64 33.3 against 37.1 at 64, 3584x18944
-//    4-bit 21.7 against 22.7 at 37.
-//  - 128-row launches of four wavefronts take eight (256 columns, K unsplit) where that
-//    measured faster: 55296x5120 4-bit 76.1 against 100.2 us, 3-bit g64 82.1 against 89.9;
-//    where 256-column groups cover only half the CUs with groups of 128 (37888x3584 4-bit
-//    46.2 against 56.1 us; 3-bit g64 at M = 96 53.0 against 50.4).
-void refine_launch(int M, int N, int K, int group, int path, subspec_plan* p, subspec::KernelChoice* kc) {
-  const Tuning& tu = tuning();
-  const bool any_shape = path == SUBSPEC_PATH_AUTO || path == SUBSPEC_PATH_MFMA;
-  const int KB = K / subspec::kTileK;
-  const int units32 = (N + 127) / 128 * ((M + 31) / 32);
-  if (any_shape && kc->shape == 16 && kc->row_blocks == 2 && tu.rb_splits >= 0 &&
-      (M > 64 ? units32 <= device_cus() : KB >= 36 && units32 * 4 >= device_cus())) {
-    const int row_blocks = (M + 31) / 32;
-    const int groups = (N + 127) / 128;
-    int splits = tu.rb_splits ? tu.rb_splits : std::max(1, std::min(device_cus() / units32, KB / 8));
-    // no more partial sums than the described launch stores
-    const long long room = p->splits > 1 ? static_cast<long long>(p->splits) * 2 * kc->rows / (32ll * row_blocks) : 1;
-    splits = static_cast<int>(std::min<long long>(splits, std::max(1ll, room)));
-    kc->shape = 32;
-    kc->rows = 32;
-    kc->row_blocks = row_blocks;
-    kc->nt = 2;
-    kc->waves = 8;
-    kc->teams = 2;
-    kc->chunk = 1;
-    kc->prefetch = 4;
-    p->col_groups = groups;
-    p->full_groups = 0;
-    p->blocks_per_split = (KB + splits - 1) / splits;
-    p->splits = (KB + p->blocks_per_split - 1) / p->blocks_per_split;
-    p->grid = groups * p->splits;
-    return;
-  }
-  const int groups = (N + 255) / 256;
-  const bool wide8 = groups * 4 >= 3 * device_cus();
-  const bool half8 = groups * 2 >= device_cus();
-  if (any_shape && kc->shape == 16 && kc->rows == 64 && kc->row_blocks == 1 && half8 && KB < 128 && !tu.mma_shape &&
-      tu.mma8_half_min_m == Tuning().mma8_half_min_m) {
-    kc->shape = 32;
-    kc->nt = 2;
-    kc->waves = 8;
-    kc->teams = 1;
-    kc->chunk = 1;
-    kc->prefetch = 4;
-    p->col_groups = p->grid = groups;
-    p->full_groups = 0;
-    p->splits = 1;
-    p->blocks_per_split = KB;
-    return;
-  }
-  if (kc->shape != 32 || tu.mma_waves || tu.mfma_pf) return;
-  if (kc->teams == 2 && kc->rows == 64) kc->prefetch = 4;
-  if (kc->waves == 4 && kc->rows == 128 && KB < 128 && (wide8 || (half8 && group == 128))) {
-    kc->waves = 8;
-    kc->prefetch = 4;
-    p->col_groups = p->grid = groups;
-    p->full_groups = 0;
-    p->splits = 1;
-    p->blocks_per_split = KB;
-  }
 }
 
 // A call's plan depends only on (device, M, N, K, bits, group, path, workspace cap)
@@ -594,7 +619,6 @@ int make_plan_cached(int M, int N, int K, int bits, int group, int path, subspec
   }
   const int rc = make_plan(M, N, K, bits, group, path, p, kc, ws_cap);
   if (rc) return rc;
-  refine_launch(M, N, K, group, path, p, kc);
   if (cache.size() >= kPlanCacheEntries) cache.clear();
   cache.emplace(key, CachedPlan{*p, *kc});
   return SUBSPEC_OK;
@@ -715,54 +739,6 @@ void pack_host(const uint8_t* codes, int N, int K, uint8_t* out) {
       }
 }
 
-// Whether an automatic call takes the small-batch kernel (k_qstream), and its tiles and
-// wavefronts per workgroup.  It replaces launches that would split K across workgroups: at
-// a few megabytes of weights their completion (three trips to the coherent level in a
-// row) costs as much as the weights.  us per call, the described launch against this one,
-// 4-bit g128, one run: 1024x1024 M = 1 5.3 / 2.8, M = 16 5.8 / 3.5; 8192x1024 M = 6 7.0 / 4.1;
-// 4608x3584 M = 1 7.8 / 4.6, M = 6 8.4 / 5.6, M = 16 8.9 / 7.2; 7168x5120 M = 1 8.9 / 7.0, M = 8
-// 9.8 / 7.9; 12288x4096 M = 6 11.3 / 10.1; 2048x8192 M = 6 10.5 / 8.1.  Where the lines lie:
-//  - every pair of tiles reads the fragments of x from the L2 again, M * K * 2 bytes: from
-//    M = 9 that is more than the weights, and only a K of up to 36 blocks still gains
-//    (5120x5120 M = 16 9.8 / 9.8, 16384x512 M = 12 6.6 / 7.2; 256x4096, sixteen tiles, 6.2 / 6.3);
-//  - 16 wavefronts fill a CU: one workgroup per CU, or at least half as many again
-//    (10240x4096, 320 pairs, M = 1 9.0 / 9.2; 14000x3584, 438 pairs, 9.9 / 9.1); of eight two
-//    (22000x2048 8.5 / 8.6);
-//  - launches of more weights have enough column groups or blocks per workgroup to hide
-//    the completion (37888x3584 M = 1 14.3 / 15.9), except where one tile a workgroup fills
-//    the CUs once (K up to 160 blocks; 3584x18944 M = 1 11.9 / 10.1, M = 2 13.1 / 10.7; from
-//    M = 5, two loads of x per block, to 112: 2560x11008 3-bit M = 6 11.0 / 8.9, 4096x14336
-//    13.5 / 12.7, but 3584x18944 3-bit M = 8 14.8 / 15.2 and 2048x18944 M = 6 11.9 / 12.3); one
-//    tile against two at M = 1: 3584x3584 4.2 / 4.4, 1024x4096 3.9 / 4.3;
-//  - a K of one or two blocks is not split anyway (512x256 M = 8 2.9 / 2.8, M = 16 2.9 / 3.3;
-//    29200x256 M = 1 4.1 / 6.3).
-bool stream_choice(int M, int N, int K, int* nt, int* ks) {
-  const Tuning& tu = tuning();
-  if (M > subspec::kStreamMaxRows || tu.stream_nt < 0) return false;
-  if (tu.stream_nt) {
-    *nt = tu.stream_nt;
-    *ks = tu.stream_ks;
-    return true;
-  }
-  const int KB = K / subspec::kTileK, tiles = N / subspec::kTileN, pairs = (tiles + 1) / 2;
-  const double mweights = static_cast<double>(N) * K / (1 << 20);
-  if (KB <= 8 || (KB < 24 && tiles <= 32)) {
-    *nt = 1;
-    *ks = 4;
-    if (KB <= 2) return M <= 8 && tiles <= 64;
-    return mweights <= 8 && (M <= 8 || tiles <= 512);
-  }
-  *ks = KB < 24 ? 8 : 16;
-  if (KB >= 24 && tiles <= device_cus() && (M <= 4 || (M <= 8 && KB > 64))) {
-    *nt = 1;
-    return KB <= (M <= 4 ? 160 : 112);
-  }
-  *nt = 2;
-  if (KB > 64 || mweights > 48) return false;
-  if (M > 8) return KB <= 36 && (KB < 24 || tiles >= 64) && mweights <= 18;
-  return KB < 24 ? pairs <= 2 * device_cus() : pairs <= device_cus() || 2 * pairs >= 3 * device_cus();
-}
-
 // noalloc: take the scratch from the library's fixed per-device array (no allocation,
 // splits capped to its size) instead of the growable workspace.
 int qlinear_impl(const void* x, const void* qweight, const void* scales, const void* zeros,
@@ -808,20 +784,16 @@ int qlinear_impl(const void* x, const void* qweight, const void* scales, const v
       if (rc) return rc;
     }
     char* base = static_cast<char*>(ws);
-    // only 128-row 32x32 tiles read pre-pass sums of x
-    const size_t xsb = kc.rows == 128 ? xsum_bytes(kc, M, K, group) : 0;
+    const size_t xsb = xsum_bytes(kc, M, K, group);
     a.cnt = reinterpret_cast<unsigned*>(base);
     a.xsum = xsb ? reinterpret_cast<const float*>(base + subspec::kSplitCounterBytes) : nullptr;
     a.ws = reinterpret_cast<float*>(base + subspec::kSplitCounterBytes + xsb);
   }
   hipError_t e = hipSuccess;
-  int snt = 0, sks = 0;
-  if (path == SUBSPEC_PATH_AUTO && stream_choice(M, N, K, &snt, &sks)) {
-    // needs no workspace, which the described launch has been given all the same: what a
-    // call allocates, and where it is refused, does not depend on this choice
-    e = subspec::launch_qstream(snt, sks, bits, group, a, st);
+  if (kc.path == 3) {
+    e = subspec::launch_qstream(kc.nt, kc.waves, bits, group, a, st);
   } else if (kc.shape == 32) {
-    if (kc.rows == 128) e = subspec::launch_xsum(a.x, M, K, group, const_cast<float*>(a.xsum), st);
+    if (a.xsum) e = subspec::launch_xsum(a.x, M, K, group, const_cast<float*>(a.xsum), st);
     if (e == hipSuccess)
       e = subspec::launch_qmma(kc.waves, kc.teams, kc.rows / 32, kc.nt / 2, kc.prefetch, bits, group, a, p.grid,
                                kc.row_blocks, st);

@@ -32,7 +32,7 @@ struct QArgs {
   int splits;
   int blocks_per_split;
   int span_blocks;        // largest k-block count of one workgroup (GEMV LDS layout)
-  // Row blocks (launch grid y > 1, 16x16x32 kernel): workgroups with blockIdx.y = r
+  // Row blocks (launch grid y > 1): workgroups with blockIdx.y = r
   // take rows [r * rb_rows, r * rb_rows + rb_rows) as a launch of their own, with
   // their own partial sums (splits * rb_rows * N floats per block) and completion
   // counters (rb_counters per block).  rb_rows = 0: one block of all M rows.
@@ -41,15 +41,15 @@ struct QArgs {
 };
 
 struct KernelChoice {
-  int path;    // 1 = GEMV, 2 = MFMA
-  int rows;    // GEMV: 1, 2, 4, 8; MFMA: 16 * m-tiles (shape 16) or 32 * m-blocks (shape 32)
+  int path;    // 1 = GEMV, 2 = MFMA, 3 = small batch (k_qstream)
+  int rows;    // GEMV: 1, 2, 4, 8; MFMA: 16 * m-tiles (shape 16) or 32 * m-blocks (shape 32); small batch: 4, 8, 16
   int nt;      // tiles per wavefront
   int chunk;   // 128-k blocks per LDS stage
   int waves;   // wavefronts per workgroup (4 or 8)
   int prefetch = 0;  // ring depth in chunks; 0 = the variant table's choice
   int shape = 0;     // MFMA path: 16 = k_qgemm_mfma (16x16x32), 32 = k_qmma (32x32x16)
-  int teams = 1;     // k_qmma: wavefront teams splitting the workgroup's K range
-  int row_blocks = 1;  // k_qgemm_mfma: row blocks of `rows` rows each (launch grid y)
+  int teams = 1;     // k_qmma, k_qstream: wavefront teams splitting the workgroup's K range
+  int row_blocks = 1;  // k_qgemm_mfma, 32-row k_qmma: row blocks of `rows` rows each (launch grid y)
 };
 
 hipError_t launch_qlinear(const KernelChoice& kc, int bits, int group, const QArgs& a,
@@ -64,7 +64,7 @@ int gemv_max_kspan(int rows, int waves, int group, int cols);
 size_t gemv_lds_bytes(int rows, int kspan, int group, int cols);
 
 // The 32x32x16 kernel (k_qmma): `waves` wavefronts per workgroup (4 or 8) in `teams`
-// teams that split its K range (1, 2 or 4), mb 32-row blocks, nb 32-column blocks per
+// teams that split its K range (1 or 2), mb 32-row blocks, nb 32-column blocks per
 // wavefront, a ring of pf chunks.
 bool qmma_variant_exists(int waves, int teams, int mb, int nb, int pf, int bits, int group);
 int qmma_resident_blocks(int waves, int teams, int mb, int nb, int pf, int bits, int group);

@@ -167,32 +167,41 @@ __global__ __launch_bounds__(KS * kWave) void k_qstream(QArgs a) {
 
 typedef void (*StreamKernel)(QArgs);
 struct StreamVariant {
-  int bits, group, nt, ks, al;
+  int bits, group, nt, ks, al, ring;
   StreamKernel fn;
 };
 // P1, P: blocks in flight with one load of x per block and with more (sixteen wavefronts
 // per CU leave 128 registers each).
-#define SUBSPEC_STREAM(B, G, T, W, P1, P)                                                      \
-  {B, G, T, W, 1, k_qstream<B, G, T, W, P1, 1>}, {B, G, T, W, 2, k_qstream<B, G, T, W, P, 2>}, \
-      {B, G, T, W, 4, k_qstream<B, G, T, W, P, 4>}
+#define SUBSPEC_STREAM(B, G, T, W, P1, P)                                                            \
+  {B, G, T, W, 1, P1, k_qstream<B, G, T, W, P1, 1>}, {B, G, T, W, 2, P, k_qstream<B, G, T, W, P, 2>}, \
+      {B, G, T, W, 4, P, k_qstream<B, G, T, W, P, 4>}
 #define SUBSPEC_STREAM_SET(B, G)                                                \
   SUBSPEC_STREAM(B, G, 1, 4, 3, 3), SUBSPEC_STREAM(B, G, 1, 16, 4, 3),          \
       SUBSPEC_STREAM(B, G, 2, 8, 3, 3), SUBSPEC_STREAM(B, G, 2, 16, 2, 2),
 const StreamVariant kVariants[] = {SUBSPEC_STREAM_SET(4, 128) SUBSPEC_STREAM_SET(4, 64) SUBSPEC_STREAM_SET(3, 128)
                                        SUBSPEC_STREAM_SET(3, 64) SUBSPEC_STREAM_SET(2, 128) SUBSPEC_STREAM_SET(2, 64)};
 
+const StreamVariant* find_stream(int nt, int ks, int bits, int group, int M) {
+  const int al = M <= 4 ? 1 : M <= 8 ? 2 : 4;  // loads of x per block
+  for (const StreamVariant& v : kVariants)
+    if (v.nt == nt && v.ks == ks && v.al == al && v.bits == bits && v.group == group) return &v;
+  return nullptr;
+}
+
 }  // namespace
 
+int qstream_ring(int nt, int ks, int bits, int group, int M) {
+  const StreamVariant* v = find_stream(nt, ks, bits, group, M);
+  return v ? v->ring : 0;
+}
+
+int qstream_grid(int groups) { return (groups + kXcds - 1) / kXcds * kXcds; }
+
 hipError_t launch_qstream(int nt, int ks, int bits, int group, const QArgs& a, hipStream_t st) {
-  const int al = a.M <= 4 ? 1 : a.M <= 8 ? 2 : 4;  // loads of x per block
-  for (const StreamVariant& v : kVariants) {
-    if (v.nt != nt || v.ks != ks || v.al != al || v.bits != bits || v.group != group) continue;
-    const int groups = (a.n_tiles + nt - 1) / nt;
-    const int grid = (groups + kXcds - 1) / kXcds * kXcds;
-    hipLaunchKernelGGL(v.fn, dim3(grid), dim3(ks * kWave), 0, st, a);
-    return hipGetLastError();
-  }
-  return hipErrorInvalidDeviceFunction;
+  const StreamVariant* v = find_stream(nt, ks, bits, group, a.M);
+  if (!v) return hipErrorInvalidDeviceFunction;
+  hipLaunchKernelGGL(v->fn, dim3(qstream_grid((a.n_tiles + nt - 1) / nt)), dim3(ks * kWave), 0, st, a);
+  return hipGetLastError();
 }
 
 }  // namespace subspec

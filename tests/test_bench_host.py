@@ -21,30 +21,33 @@ def test_more_than_one_gpu_is_refused():
     assert r.returncode == 2 and "one GPU" in r.stderr, (r.returncode, r.stderr)
 
 
-def _kernel_name(plan, bits, group):
-    """The demangled name rocprofv3 reports for the kernel a plan launches."""
-    if plan["path"] == ss.SUBSPEC_PATH_GEMV:
-        t = (bits, group, plan["rows"], plan["tiles_per_wave"], plan["chunk_blocks"], plan["waves"], 2)
-        return "void subspec::k_qgemv<%s>(subspec::QArgs)" % ", ".join(map(str, t))
-    if plan["mfma_rows"] == 32:
-        t = (bits, group, plan["rows"] // 32, plan["tiles_per_wave"] // 2, plan["ring_chunks"], plan["waves"],
-             plan["teams"])
-        return "void subspec::qmma::k_qmma<%s>(subspec::QArgs)" % ", ".join(map(str, t))
-    t = (bits, group, plan["rows"] // 16, plan["tiles_per_wave"], plan["chunk_blocks"], plan["waves"], 2)
-    return "void subspec::k_qgemm_mfma<%s>(subspec::QArgs)" % ", ".join(map(str, t))
+# Kernels, grids and workgroups (work-items) that rocprofv3 recorded for launches of
+# bench.py's workloads on an MI355X (profiles/qlinear_suite_kernel_trace.md); of those whose
+# plan follows from the shape alone (others ask the GPU how many workgroups fit).
+TRACED = [
+    ((1, 7168, 5120, 3, 128), "subspec::(anonymous namespace)::k_qstream<3, 128, 2, 16, 2, 1>", 229376, 1024),
+    ((1, 3584, 18944, 4, 128), "subspec::(anonymous namespace)::k_qstream<4, 128, 1, 16, 4, 1>", 229376, 1024),
+    ((1, 512, 256, 4, 64), "subspec::(anonymous namespace)::k_qstream<4, 64, 1, 4, 3, 1>", 8192, 256),
+    ((1, 55296, 5120, 3, 128), "subspec::k_qgemv<3, 128, 1, 1, 2, 4, 2>", 245760, 256),
+    ((16, 7168, 5120, 3, 128), "subspec::k_qgemm_mfma<3, 128, 1, 1, 2, 4, 2>", 114688, 256),
+    ((64, 5120, 5120, 3, 128), "subspec::qmma::k_qmma<3, 128, 1, 1, 4, 8, 2>", 122880, 512),
+    ((128, 5120, 5120, 3, 128), "subspec::qmma::k_qmma<3, 128, 1, 1, 4, 8, 2>", 81920, 512),
+    ((128, 7168, 5120, 3, 128), "subspec::qmma::k_qmma<3, 128, 1, 1, 4, 8, 2>", 114688, 512),
+    ((64, 55296, 5120, 3, 128), "subspec::qmma::k_qmma<3, 128, 2, 1, 4, 8, 1>", 110592, 512),
+    ((128, 55296, 5120, 2, 64), "subspec::qmma::k_qmma<2, 64, 4, 1, 4, 8, 1>", 110592, 512),
+    ((48, 37888, 3584, 4, 128), "subspec::qmma::k_qmma<4, 128, 2, 1, 4, 8, 1>", 75776, 512),
+]
 
 
-@pytest.mark.parametrize("M,N,K,bits,group", [(1, 7168, 5120, 3, 128), (16, 55296, 5120, 3, 128),
-                                              (64, 7168, 5120, 3, 128), (128, 5120, 5120, 3, 128),
-                                              (64, 55296, 5120, 3, 128), (128, 5120, 27648, 3, 128),
-                                              (48, 3584, 18944, 4, 128), (128, 55296, 5120, 2, 64)])
-def test_plan_key_matches_the_traced_kernel(M, N, K, bits, group):
-    """A launch's key from its plan equals the key built from the kernel name and the
-    whole grid (both dimensions, in work-items) that a trace or counter file gives."""
-    plan = ss.subspec_qlinear_plan(M, N, K, bits, group)
-    wg = plan["waves"] * 64
-    grid_items = plan["grid"] * plan["row_blocks"] * wg
-    assert bench.plan_key(plan, bits, group) == bench.library_key(_kernel_name(plan, bits, group), grid_items, wg)
+@pytest.mark.parametrize("shape,name,grid_items,wg", TRACED)
+def test_plan_key_matches_the_traced_kernel(shape, name, grid_items, wg):
+    """A launch's key from its plan equals the key of the kernel and the whole grid (both
+    dimensions) that a trace recorded for it, so the plan is what runs and its measured
+    traffic is found."""
+    key = bench.library_key(f"void {name}(subspec::QArgs)", grid_items, wg)
+    with open(os.path.join(ROOT, "profiles", "qlinear_suite_kernel_trace.md"), encoding="utf-8") as f:
+        assert f"`{key}`" in f.read()
+    assert bench.plan_key(ss.subspec_qlinear_plan(*shape), *shape[3:]) == key
 
 
 def test_library_key_ignores_other_kernels():

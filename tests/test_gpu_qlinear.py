@@ -187,7 +187,8 @@ def test_qlinear_row_blocks(M, N, K, bits, group):
     each with its own partial sums and completion counters (the second block holding
     M - rows rows, down to one): every output against the oracle, twice, so that the
     counters of both blocks must be back at zero for the second call."""
-    plan = ss.subspec_qlinear_plan(M, N, K, bits, group)
+    path = ss.SUBSPEC_PATH_MFMA16
+    plan = ss.subspec_qlinear_plan(M, N, K, bits, group, path)
     assert plan["mfma_rows"] == 16 and plan["row_blocks"] == 2 and plan["splits"] > 1, plan
     w = _w(N, K, 350, M, N, K, bits, group)
     p = device_projection(torch.from_numpy(w).to(DEV), bits, group)
@@ -195,7 +196,7 @@ def test_qlinear_row_blocks(M, N, K, bits, group):
     x = synth.activations(M, K, 351, M, N, K)
     ss.subspec_reserve(plan["workspace_bytes"])
     for _ in range(2):
-        y = run_qlinear(p, x.to(DEV))
+        y = run_qlinear(p, x.to(DEV), path)
         y_ref = oracle.qlinear_ref(synth.bf16_bits(x), q, s16, z16, group)
         assert_close(bf16_to_f64(y), y_ref, f"row blocks M={M} N={N} K={K} bits={bits} g={group} plan={plan}")
 
@@ -287,10 +288,12 @@ def test_qlinear_does_not_touch_outside_y():
     (128, 55296, 256, 4, 64),
     (70, 49168, 384, 3, 64),
 ])
-def test_qlinear_refined_launches(M, N, K, bits, group):
-    """Shapes whose automatic launch is a 32x32 form other than the described plan's:
-    against the oracle, and within the workspace the plan states."""
+def test_qlinear_32x32_forms(M, N, K, bits, group):
+    """32x32 launches in 32-row blocks, on 64-row tiles of half-wide launches and on
+    128-row tiles of eight wavefronts: against the oracle, and within the workspace the
+    plan states."""
     plan = ss.subspec_qlinear_plan(M, N, K, bits, group)
+    assert plan["mfma_rows"] == 32 and plan["waves"] == 8, plan
     p = device_projection(torch.from_numpy(_w(N, K, 360, M, N, K, bits, group)).to(DEV), bits, group)
     q, s16, z16 = p["codes"].cpu().numpy(), p["scales"].cpu().numpy(), p["zeros"].cpu().numpy()
     x = synth.activations(M, K, 361, M, N, K)
@@ -325,6 +328,8 @@ def test_qlinear_refined_launches(M, N, K, bits, group):
 def test_qlinear_small_batches_over_whole_k(M, N, K, bits, group):
     """Small launches that would split K across workgroups run on workgroups whose
     wavefronts split it: against the oracle, and repeatable."""
+    plan = ss.subspec_qlinear_plan(M, N, K, bits, group)
+    assert plan["mfma_rows"] == 16 and plan["teams"] == plan["waves"] > 1 and plan["workspace_bytes"] == 0, plan
     p = device_projection(torch.from_numpy(_w(N, K, 370, M, N, K, bits, group)).to(DEV), bits, group)
     q, s16, z16 = p["codes"].cpu().numpy(), p["scales"].cpu().numpy(), p["zeros"].cpu().numpy()
     x = synth.activations(M, K, 371, M, N, K)

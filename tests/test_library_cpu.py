@@ -98,85 +98,110 @@ def test_plan_choices_are_consistent():
             for bits, group in [(4, 128), (3, 128), (2, 64), (4, 64)]:
                 p = ss.subspec_qlinear_plan(M, N, K, bits, group)
                 rb = p["row_blocks"]
-                # row blocks: 16x16x32 tiles only, each block holding at least one row
-                assert rb == 1 or (rb == 2 and p["mfma_rows"] == 16 and p["full_groups"] == 0), p
+                # row blocks: two of 16x16x32 tiles or any number of 32-row 32x32 tiles,
+                # each block holding at least one row
+                assert rb == 1 or (p["full_groups"] == 0 and (
+                    (rb == 2 and p["mfma_rows"] == 16) or (p["mfma_rows"] == 32 and p["rows"] == 32))), p
                 assert p["rows"] * rb >= M > p["rows"] * (rb - 1)
                 KB = K // 128
                 assert p["splits"] >= 1 and p["blocks_per_split"] % p["chunk_blocks"] == 0
                 assert (p["splits"] - 1) * p["blocks_per_split"] < KB <= p["splits"] * p["blocks_per_split"]
-                # teams split a workgroup's k-blocks (32x32 tiles only); a layout
-                # mismatch between the binding and the C struct would show here
-                assert p["teams"] == 1 or (p["teams"] == 2 and p["mfma_rows"] == 32 and p["waves"] == 8), p
+                # teams split a workgroup's k-blocks (two on 32x32 tiles; every wavefront
+                # of a small-batch launch); a layout mismatch between the binding and the
+                # C struct would show here
+                small = p["mfma_rows"] == 16 and p["teams"] > 1
+                assert p["teams"] == 1 or (p["teams"] == 2 and p["mfma_rows"] == 32 and p["waves"] == 8) or (
+                    small and M <= 16 and p["teams"] == p["waves"] and p["splits"] == 1 and p["rows"] in (4, 8, 16)), p
                 cols = p["waves"] // p["teams"] * p["tiles_per_wave"] * 16
                 assert p["col_groups"] == -(-N // cols)
                 fg = p["full_groups"]
                 assert 0 <= fg < p["col_groups"]
-                assert p["grid"] == fg + (p["col_groups"] - fg) * p["splits"]
+                grid = fg + (p["col_groups"] - fg) * p["splits"]
+                assert p["grid"] == (-(-grid // 8) * 8 if small else grid)
                 if fg:
                     # whole groups on a multiple of the CUs; the rest split at most
                     # once per CU
                     assert p["splits"] > 1 and fg % 256 == 0
                     assert (p["col_groups"] - fg) * p["splits"] <= 256
                 # completion counters (16384 x 4 bytes), the per-group sums of x the
-                # 32x32 kernel reads (fp32 [M][K/group], 256-byte aligned), then the
-                # splits' fp32 partial sums
-                xs = -(-M * (K // group) * 4 // 256) * 256 if p["mfma_rows"] == 32 else 0
-                part_rows = 2 * p["rows"] if rb == 2 else M
+                # 32x32 kernel reads on 128-row tiles (fp32 [K/group][M], 256-byte
+                # aligned), then the splits' fp32 partial sums: nothing the launch does
+                # not read
+                xs = -(-M * (K // group) * 4 // 256) * 256 if p["mfma_rows"] == 32 and p["rows"] == 128 else 0
+                part_rows = rb * p["rows"] if rb > 1 else M
                 partials = p["splits"] * part_rows * N * 4 if p["splits"] > 1 else 0
                 expect = 65536 + xs + partials if (xs or partials) else 0
                 assert p["workspace_bytes"] == expect, (M, N, K, bits, group, p)
     # 592 column groups on 256 CUs: 512 whole, the last 80 split three ways
     p = ss.subspec_qlinear_plan(1, 37888, 3584, 4, 128)
     assert (p["col_groups"], p["full_groups"], p["splits"], p["grid"]) == (592, 512, 3, 752)
-    # automatic plan: GEMV only for one row (measured crossover), MFMA from M = 2
-    assert ss.subspec_qlinear_plan(1, 512, 256, 4, 64)["path"] == ss.SUBSPEC_PATH_GEMV
-    assert ss.subspec_qlinear_plan(2, 512, 256, 4, 64)["path"] == ss.SUBSPEC_PATH_MFMA
+    # automatic plan: GEMV only for one row of the larger weights (measured crossover),
+    # MFMA from M = 2; small weights on matrix cores from one row on, without workspace
+    assert ss.subspec_qlinear_plan(1, 37888, 3584, 4, 128)["path"] == ss.SUBSPEC_PATH_GEMV
+    assert ss.subspec_qlinear_plan(2, 37888, 3584, 4, 128)["path"] == ss.SUBSPEC_PATH_MFMA
+    for M in (1, 2, 8):
+        p = ss.subspec_qlinear_plan(M, 512, 256, 4, 64)
+        assert (p["path"], p["mfma_rows"], p["teams"], p["workspace_bytes"]) == (ss.SUBSPEC_PATH_MFMA, 16, 4, 0)
+    p = ss.subspec_qlinear_plan(6, 4608, 3584, 4, 128)
+    assert (p["mfma_rows"], p["rows"], p["tiles_per_wave"], p["teams"], p["grid"]) == (16, 8, 2, 16, 144)
+    # launches that need no scratch ask for none
+    assert ss.subspec_qlinear_plan(37, 37888, 3584, 4, 128)["workspace_bytes"] == 0
+    assert ss.subspec_qlinear_plan(128, 7168, 5120, 3, 128)["workspace_bytes"] == 0
+    assert ss.subspec_qlinear_plan(128, 37888, 3584, 4, 128)["workspace_bytes"] == 65536 + 128 * 28 * 4
     assert ss.subspec_qlinear_plan(8, 512, 256, 4, 64, ss.SUBSPEC_PATH_GEMV)["path"] == ss.SUBSPEC_PATH_GEMV
     assert ss.subspec_qlinear_plan(8, 512, 256, 4, 64, ss.SUBSPEC_PATH_MFMA)["path"] == ss.SUBSPEC_PATH_MFMA
 
 
 def test_mfma_tile_shape_choice():
-    """The automatic plan runs 32x32x16 tiles (128 rows) only above M = 64, on launches
-    that fill the 256 CUs with whole 128-column groups (two-chunk ring) or split a K of
-    at least 192 blocks (four-chunk ring); everything else stays on 16x16x32 tiles.
-    Where 256-column groups still cover three quarters of the CUs and K is not split,
-    eight wavefronts share a four-chunk ring (if that variant is built for the bit
-    width and group), and from M = 33 such launches take 64-row 32x32x16 tiles too.
-    Launches whose K spans at least 128 blocks take two teams of four wavefronts per
-    workgroup from M = 33 (64-row tiles up to M = 64; the last tuple entry is then minus
-    the wavefronts of one team)."""
+    """The automatic plan runs 32x32x16 tiles from M = 33 where 256-column groups of
+    eight wavefronts (a four-chunk ring) cover at least half the 256 CUs and K is not
+    split: 64 rows up to M = 64, 128 above (there, under three quarters of the CUs, groups
+    of 64 take four wavefronts and two chunks); and on a K of at least 128 blocks, two
+    teams of four wavefronts per workgroup (the last tuple entry is then minus the
+    wavefronts of one team; four chunks on 64 rows, two on 128).  Narrower launches run
+    32-row tiles in row blocks while those stay within a workgroup per CU; everything
+    else stays on 16x16x32 tiles."""
     def shape(M, N, K, bits=3, group=128, path=ss.SUBSPEC_PATH_AUTO):
         p = ss.subspec_qlinear_plan(M, N, K, bits, group, path)
         return p["mfma_rows"], p["rows"], p["ring_chunks"], p["waves"] // p["teams"] * (1 if p["teams"] == 1 else -1)
     assert shape(128, 55296, 5120) == (32, 128, 4, 8)      # 32B gate|up
     assert shape(128, 55296, 5120, 2, 64) == (32, 128, 4, 8)
-    assert shape(128, 55296, 5120, 4, 128) == (32, 128, 2, 4)  # no eight-wavefront 4-bit build
-    assert shape(96, 37888, 3584, 4) == (32, 128, 2, 4)     # 7B gate|up: 148 groups of 256
+    assert shape(128, 55296, 5120, 4, 128) == (32, 128, 4, 8)
+    assert shape(128, 55296, 5120, 3, 64) == (32, 128, 4, 8)
+    assert shape(96, 37888, 3584, 4) == (32, 128, 4, 8)     # 7B gate|up: 148 groups of 256
+    assert shape(96, 37888, 3584, 4, 64) == (32, 128, 2, 4)  # groups of 64: four wavefronts
     assert shape(128, 5120, 27648) == (32, 128, 2, -4)     # 32B down: two teams of four
     assert shape(96, 3584, 18944, 4) == (32, 128, 2, -4)   # 7B down
-    assert shape(128, 7168, 5120)[0] == 16           # 32B q|k|v
+    assert shape(128, 7168, 5120) == (32, 32, 4, -4)  # 32B q|k|v: 32-row tiles
+    assert shape(128, 14336, 4096, 4)[0] == 16       # more than a workgroup per CU
     assert shape(64, 55296, 5120) == (32, 64, 4, 8)        # 32B gate|up, 64-row tiles
     assert shape(33, 55296, 5120, 2, 64) == (32, 64, 4, 8)
     assert shape(48, 55296, 5120, 4, 128) == (32, 64, 4, 8)
     assert shape(32, 55296, 5120)[0] == 16
-    assert shape(64, 37888, 3584, 4) == (32, 64, 4, 8)     # 7B gate|up: half-wide, from M = 48
-    assert shape(48, 37888, 3584, 4) == (32, 64, 4, 8)
-    assert shape(40, 37888, 3584, 4)[0] == 16
-    assert shape(64, 5120, 27648) == (32, 64, 2, -4)       # long K: 64-row tiles on two teams
-    assert shape(33, 3584, 18944, 4) == (32, 64, 2, -4)
+    assert shape(64, 37888, 3584, 4) == (32, 64, 4, 8)     # 7B gate|up: half-wide
+    assert shape(33, 37888, 3584, 4) == (32, 64, 4, 8)
+    assert shape(32, 37888, 3584, 4)[0] == 16
+    assert shape(64, 5120, 27648) == (32, 64, 4, -4)       # long K: 64-row tiles on two teams
+    assert shape(33, 3584, 18944, 4) == (32, 64, 4, -4)
     assert shape(32, 5120, 27648)[0] == 16
-    assert shape(64, 7168, 5120)[0] == 16                  # q|k|v
+    assert shape(64, 7168, 5120) == (32, 32, 4, -4)        # q|k|v
+    assert shape(64, 4608, 3584, 4)[0] == 16               # K under 36 blocks
     assert shape(17, 512, 256, path=ss.SUBSPEC_PATH_MFMA32) == (32, 128, 4, 4)
-    # 16x16x32 launches whose column groups number fewer than the CUs, with K under
-    # 128 blocks, run their rows in two blocks from M = 33 (q|k|v, o); long-K, wide
-    # and M <= 32 launches keep one block
+    # launches whose column groups number fewer than the CUs, with K under 128 blocks, run
+    # their rows in blocks from M = 33 (q|k|v, o); long-K, wide and M <= 32 launches, keep one
     def blocks(M, N, K, bits=3, group=128):
         p = ss.subspec_qlinear_plan(M, N, K, bits, group)
         return p["row_blocks"], p["rows"]
     assert blocks(64, 7168, 5120) == (2, 32)              # 32B q|k|v
-    assert blocks(128, 5120, 5120) == (2, 64)             # 32B o
+    assert blocks(128, 5120, 5120) == (4, 32)             # 32B o
     assert blocks(33, 4608, 3584, 4) == (2, 32)           # 7B q|k|v
-    assert blocks(100, 3584, 3584, 4) == (2, 64)          # 7B o
+    assert blocks(100, 3584, 3584, 4) == (4, 32)          # 7B o
+    def blocks16(M, N, K, bits=3, group=128):
+        p = ss.subspec_qlinear_plan(M, N, K, bits, group, ss.SUBSPEC_PATH_MFMA16)
+        return p["mfma_rows"], p["row_blocks"], p["rows"]
+    assert blocks16(64, 7168, 5120) == (16, 2, 32)
+    assert blocks16(128, 5120, 5120) == (16, 2, 64)
+    assert blocks16(100, 3584, 3584, 4) == (16, 2, 64)
     assert blocks(32, 7168, 5120) == (1, 32)
     assert blocks(64, 5120, 27648) == (1, 64)             # long K
     assert blocks(64, 3584, 18944, 4) == (1, 64)

@@ -53,11 +53,12 @@ def test_noalloc_matches_qlinear_on_two_calls_in_a_row():
 
 
 def test_noalloc_caps_its_splits_to_the_fixed_scratch():
-    # Qwen2.5-7B gate|up at M = 128: the usual plan splits the tail column groups six
-    # ways (about 116 MB of partial sums); the allocation-free call splits less and
-    # agrees with subspec_qlinear within the fp32-accumulation tolerance, and with the
+    # Qwen2.5-7B gate|up at M = 128, groups of 64: the usual launch splits the tail column
+    # groups six ways (about 116 MB of partial sums); the allocation-free call splits less
+    # and agrees with subspec_qlinear within the fp32-accumulation tolerance, and with the
     # oracle on sampled columns
-    M, N, K, bits, group = 128, 37888, 3584, 4, 128
+    M, N, K, bits, group = 128, 37888, 3584, 4, 64
+    assert ss.subspec_qlinear_plan(M, N, K, bits, group)["splits"] == 6
     assert ss.subspec_qlinear_plan(M, N, K, bits, group)["workspace_bytes"] > ss.SUBSPEC_NOALLOC_SCRATCH_BYTES
     w = synth.weights_torch(N, K, 920, device=DEV)
     p = device_projection(w, bits, group)
