@@ -1,8 +1,11 @@
 """CPU-only checks of the native library: it loads, exports every entry point the
 header declares, validates arguments, plans launches, and its host packer writes
 the specified layout (pinned against hand-derived bytes and the oracle's reader)."""
+import json
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -209,6 +212,31 @@ def test_mfma_tile_shape_choice():
     assert shape(128, 55296, 5120, path=ss.SUBSPEC_PATH_MFMA16)[0] == 16
     for path in (ss.SUBSPEC_PATH_MFMA16, ss.SUBSPEC_PATH_MFMA32):
         assert ss.subspec_qlinear_plan(40, 512, 256, 4, 64, path)["path"] == ss.SUBSPEC_PATH_MFMA
+
+
+@pytest.mark.parametrize("tune,shape,expect", [
+    ("mma_shape=16", (128, 7168, 5120, 3, 128), dict(mfma_rows=16, row_blocks=2)),
+    ("mma_shape=16", (40, 37888, 3584, 4, 128), dict(mfma_rows=16)),
+    ("row_split=2", (128, 7168, 5120, 3, 128), dict(mfma_rows=16, row_blocks=1)),
+    ("rb_splits=-1", (128, 7168, 5120, 3, 128), dict(mfma_rows=16, row_blocks=2)),
+    ("splits=3", (128, 7168, 5120, 3, 128), dict(mfma_rows=32, splits=3)),
+    ("splits=2", (1, 4608, 3584, 4, 128), dict(splits=2)),  # not the small-batch launch
+    ("mma8_half_min_m=48", (40, 37888, 3584, 4, 128), dict(mfma_rows=16)),
+    # no such build (two-chunk rings of four wavefronts exist for groups of 64 only): the
+    # four-chunk one, or the general choice
+    ("mma_waves=4", (128, 55296, 5120, 3, 128), dict(mfma_rows=32, waves=4, ring_chunks=4)),
+    ("mma_waves=4", (40, 3584, 18944, 4, 128), dict(mfma_rows=32, waves=8, teams=2, rows=64, ring_chunks=4)),
+    ("mfma_pf=2", (40, 3584, 18944, 4, 64), dict(rows=128, waves=4, ring_chunks=2)),
+    ("stream_nt=2,stream_ks=4", (6, 4608, 3584, 4, 128), dict(teams=1)),
+])
+def test_tuning_overrides_are_honoured(tune, shape, expect):
+    """Measurement overrides reach the launch, and never one that was not built."""
+    code = ("import paper_2509_18344_amd as ss, json; print(json.dumps(ss.subspec_qlinear_plan(*%r)))" % (shape,))
+    out = subprocess.run([sys.executable, "-c", code], env=dict(os.environ, SUBSPEC_TUNE=tune), text=True,
+                         capture_output=True, timeout=120, cwd=ROOT)
+    assert out.returncode == 0, out.stderr
+    plan = json.loads(out.stdout)
+    assert {k: plan[k] for k in expect} == expect, plan
 
 
 def test_gemv_plan_refuses_splits_longer_than_its_staging():
