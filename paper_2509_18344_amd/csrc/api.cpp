@@ -292,13 +292,14 @@ int make_plan(int M, int N, int K, int bits, int group, int path, subspec_plan* 
     // mma8_min_m on: 32B gate|up 48.7 against 53.4 us at M = 33, 51.6 against 55.1 at
     // 48, 53.9 against 59.0 at 64; where 256-column groups cover only half the CUs from
     // mma8_half_min_m on (7B gate|up, 148 groups: 29.1 against 30.9 us at M = 37, 3-bit
-    // 28.3 against 30.8 at 44, 4-bit g64 32.3 against 35.7 at 40).  Long-K launches take
+    // 28.3 against 30.8 at 44, 4-bit g64 32.3 against 35.7 at 40; under M = 48 from three
+    // k-blocks on: 44032x256 3-bit 6.8 against 6.4 at 47).  Long-K launches take
     // 64-row tiles on two teams of four wavefronts from teams64_min_m (below): 32B down
     // 34.5 against 39.3 us at M = 48 and 39.6 against 41.5 at 64, 2-bit g64 36.0 against
     // 43.9 and 40.2 against 46.1; the 7B down about even (25.7 against 25.2 at 48, 26.8
     // against 27.5 at 64); at M = 32, with half of each tile empty, 30.7 against 27.3.
     // (These with two-chunk rings; four chunks are faster, below.)
-    const bool tiles64 = tu.mma8_min_m > 0 && M >= tu.mma8_min_m && (half8 && !wide8 ? M >= tu.mma8_half_min_m : wide8) &&
+    const bool tiles64 = tu.mma8_min_m > 0 && M >= tu.mma8_min_m && (half8 && !wide8 ? M >= tu.mma8_half_min_m && (M >= 48 || KB >= 3) : wide8) &&
                          !long_k;
     const bool teams64 = tu.teams64_min_m > 0 && long_k && M >= tu.teams64_min_m && M <= 64;
     const bool use32 =
@@ -333,11 +334,19 @@ int make_plan(int M, int N, int K, int bits, int group, int path, subspec_plan* 
     // cover three quarters of the CUs and K is not split (55296x5120, M = 128: 4-bit 76.1
     // against 100.2 us, 3-bit g64 82.1 against 89.9), and where they cover half of them on
     // 64-row tiles (built for eight wavefronts only) and at groups of 128 (37888x3584 4-bit
-    // 46.2 against 56.1 us; 3-bit g64 at M = 96 53.0 against 50.4).
+    // 46.2 against 56.1 us; 3-bit g64 at M = 96 53.0 against 50.4).  Not for up to four
+    // k-blocks of 64-k groups at 3 and 4 bits where four wavefronts need no split tail: two workgroups per CU
+    // hide the start of a launch better (55296 columns 4-bit, M = 65: K = 256 12.2 us
+    // against 10.8, 512 15.6 against 14.4, 768 18.6 against 18.2; 49152 columns, whose tail
+    // splits, 11.9 against 16.6 at K = 256).
     c8 = c;
     c8.waves = 8;
     c8.prefetch = tu.mfma_pf ? tu.mfma_pf : 4;
-    use8 = tu.mma_waves ? tu.mma_waves == 8 : (wide8 || (half8 && (c.rows == 64 || group == 128))) && !long_k;
+    const int rem128 = (N + 127) / 128 % device_cus();
+    const bool short_k = group == 64 && bits > 2 && c.rows == 128 && KB <= 4 &&
+                         (KB == 1 || rem128 == 0 || 2 * rem128 > device_cus());
+    use8 = tu.mma_waves ? tu.mma_waves == 8
+                        : (wide8 || (half8 && (c.rows == 64 || group == 128))) && !long_k && !short_k;
     // Long-K launches (split along K, not wide enough for whole groups) take two teams
     // of four wavefronts per workgroup, each on half of the workgroup's k-blocks: two
     // wavefronts per SIMD at the same number of splits (32B down, K = 27648: 61.5
@@ -446,12 +455,20 @@ int make_plan(int M, int N, int K, int bits, int group, int path, subspec_plan* 
   // against 19.3, 4608x3584 4-bit 17.2 against 14.9; two and three splits at M = 64 16.5
   // against 14.3 and 13.5 against 12.6.  Not from M = 65 where they exceed a workgroup per
   // CU (14336x4096 4-bit 30.0 against 31.4), and up to M = 64 not for a K under 36 blocks
-  // (4608x3584 11.1 against 11.6) or few columns (2048x8192 11.9 against 12.1).  What bounds
-  // them is the L2: every block of rows reads the weights again and every column group x,
-  // 128 MB at 7168x5120.
+  // (4608x3584 11.1 against 11.6) or few columns (2048x8192 11.9 against 12.1); not for a
+  // single k-block (2304x128, M = 128 4.5 against 3.7); and not from M = 97 where the
+  // unsplit launch leaves CUs without work that three splits of the other would use and K
+  // is long enough to show it: 48 blocks, or 30 where the column groups are no multiple of
+  // eight, so that the row blocks of a group land on different XCDs and each L2 reads its
+  // weights (4-bit, M = 97: 5120 columns, 160 workgroups, K = 14336 42.7 us against 38.7,
+  // 6016 0.99 of the other, 5120 0.91; 5376 columns, 168, 6016 24.0 against 21.2, 4736 20.0
+  // against 18.7, 3584 even; 6144 columns, two splits for the other, 0.84).  What bounds them is the L2: every block
+  // of rows reads the weights again and every column group x, 128 MB at 7168x5120.
   if (any_shape && c.shape == 16 && c.row_blocks == 2 && !tu.mma_shape && !tu.row_split && tu.rb_splits >= 0) {
     const int units32 = (N + 127) / 128 * ((M + 31) / 32);
-    if (M > 64 ? units32 <= device_cus() : KB >= 36 && units32 * 4 >= device_cus()) {
+    const bool idle = M > 96 && KB >= ((N + 127) / 128 % 8 ? 30 : 48) && units32 * 2 > device_cus() &&
+                      groups_of(c) * c.row_blocks * 3 <= 2 * device_cus();
+    if (M > 64 ? units32 <= device_cus() && KB > 1 && !idle : KB >= 36 && units32 * 4 >= device_cus()) {
       c = subspec::KernelChoice{};
       c.path = 2;
       c.shape = 32;

@@ -278,15 +278,15 @@ def test_qlinear_does_not_touch_outside_y():
 @pytest.mark.parametrize("M,N,K,bits,group", [
     (128, 7168, 1152, 3, 128),   # 32-row blocks, K unsplit: nine k-blocks on two teams
     (65, 528, 1024, 4, 64),      # a last row block of one row, columns past N
-    (97, 512, 128, 2, 128),      # one k-block: the second team has none
+    (97, 512, 256, 2, 128),      # a k-block for each team
     (128, 48, 384, 3, 64),       # fewer columns than a wavefront's block; three k-blocks
     (33, 7168, 5120, 3, 128),    # up to M = 64: K split two or three ways
     (64, 5120, 5120, 2, 64),
-    (40, 32768, 256, 4, 128),    # 64-row tiles from M = 33 on half-wide launches
+    (40, 32768, 384, 4, 128),    # 64-row tiles from M = 33 on half-wide launches
     (47, 32784, 640, 3, 64),
     (100, 32784, 384, 4, 128),   # eight wavefronts at four row blocks, 4-bit
-    (128, 55296, 256, 4, 64),
-    (70, 49168, 384, 3, 64),
+    (128, 55296, 640, 4, 64),
+    (70, 49168, 640, 3, 64),
 ])
 def test_qlinear_32x32_forms(M, N, K, bits, group):
     """32x32 launches in 32-row blocks, on 64-row tiles of half-wide launches and on
@@ -313,6 +313,29 @@ def test_qlinear_32x32_forms(M, N, K, bits, group):
     other = run_qlinear(p, x.to(DEV), ss.SUBSPEC_PATH_MFMA16)
     assert_close(bf16_to_f64(y), bf16_to_f64(other), "against 16x16x32 tiles")
     assert ss.subspec_workspace_info()["allocations"] <= before + 1
+
+
+@pytest.mark.parametrize("M,N,K,bits,group,rows,waves", [
+    (97, 5376, 4864, 4, 128, 64, 4),    # CUs left without work by unsplit 32-row tiles
+    (128, 4240, 6144, 2, 64, 64, 4),
+    (65, 1040, 128, 3, 64, 64, 4),      # a single k-block
+    (128, 55296, 512, 4, 64, 128, 4),   # short K: four wavefronts, two-chunk ring
+    (65, 49168, 128, 3, 64, 128, 4),
+    (47, 32784, 256, 4, 128, 64, 4),    # half-wide, under three blocks
+])
+def test_qlinear_short_and_idle_launches(M, N, K, bits, group, rows, waves):
+    """Launches the 32-row and eight-wavefront forms are not taken for, on either side of
+    their lines: against the oracle, and repeatable."""
+    plan = ss.subspec_qlinear_plan(M, N, K, bits, group)
+    assert (plan["rows"], plan["waves"]) == (rows, waves), plan
+    p = device_projection(torch.from_numpy(_w(N, K, 380, M, N, K, bits, group)).to(DEV), bits, group)
+    q, s16, z16 = p["codes"].cpu().numpy(), p["scales"].cpu().numpy(), p["zeros"].cpu().numpy()
+    x = synth.activations(M, K, 381, M, N, K)
+    cols = np.unique(np.r_[0:min(N, 512), max(0, N - 512):N])
+    y_ref = oracle.qlinear_ref(synth.bf16_bits(x), q[cols], s16[:, cols], z16[:, cols], group)
+    y = run_qlinear(p, x.to(DEV))
+    assert_close(bf16_to_f64(y)[:, cols], y_ref, f"M={M} N={N} K={K} bits={bits} g={group} plan={plan}")
+    assert torch.equal(y, run_qlinear(p, x.to(DEV)))
 
 
 @pytest.mark.parametrize("M,N,K,bits,group", [

@@ -184,6 +184,11 @@ def test_mfma_tile_shape_choice():
     assert shape(64, 37888, 3584, 4) == (32, 64, 4, 8)     # 7B gate|up: half-wide
     assert shape(33, 37888, 3584, 4) == (32, 64, 4, 8)
     assert shape(32, 37888, 3584, 4)[0] == 16
+    assert shape(47, 44032, 256)[0] == 16 and shape(48, 44032, 256) == (32, 64, 4, 8)  # short K
+    assert shape(128, 55296, 512, 4, 64) == (32, 128, 2, 4)   # short K, no split tail: four wavefronts
+    assert shape(128, 49152, 512, 4, 64) == (32, 128, 4, 8)
+    assert shape(128, 49152, 128, 4, 64) == (32, 128, 2, 4)
+    assert shape(128, 55296, 640, 4, 64) == (32, 128, 4, 8)
     assert shape(64, 5120, 27648) == (32, 64, 4, -4)       # long K: 64-row tiles on two teams
     assert shape(33, 3584, 18944, 4) == (32, 64, 4, -4)
     assert shape(32, 5120, 27648)[0] == 16
@@ -205,6 +210,12 @@ def test_mfma_tile_shape_choice():
     assert blocks16(64, 7168, 5120) == (16, 2, 32)
     assert blocks16(128, 5120, 5120) == (16, 2, 64)
     assert blocks16(100, 3584, 3584, 4) == (16, 2, 64)
+    # a single k-block, and a K long enough to show the CUs left without work, keep two
+    # 16x16x32 blocks
+    assert blocks(128, 4608, 128, 4) == (2, 64) and blocks(128, 4608, 256, 4) == (4, 32)
+    assert blocks(128, 5120, 6144) == (2, 64) and blocks(128, 5120, 6016) == (4, 32)
+    assert blocks(97, 5376, 3840) == (2, 64) and blocks(97, 5376, 3712) == (4, 32)
+    assert blocks(96, 5120, 6144) == (3, 32) and blocks(128, 6144, 6144) == (4, 32)
     assert blocks(32, 7168, 5120) == (1, 32)
     assert blocks(64, 5120, 27648) == (1, 64)             # long K
     assert blocks(64, 3584, 18944, 4) == (1, 64)
