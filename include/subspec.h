@@ -114,8 +114,8 @@ typedef struct subspec_plan {
                           full_groups + (col_groups - full_groups) * splits
                           (small-batch launches: rounded up to a multiple of 8) */
   size_t workspace_bytes; /* device scratch the call uses: 64 KiB of completion
-                             counters, the per-group sums of x of 128-row 32x32
-                             tiles, and the fp32 partial sums of split column groups
+                             counters, the per-group sums of x of 96- and 128-row
+                             32x32 tiles, and the fp32 partial sums of split column groups
                              (0 when neither of the latter two is needed) */
   int teams;           /* MFMA tiles: wavefront teams per workgroup that split its
                           k-blocks between them and add up in LDS.  1; 2 on 32-row

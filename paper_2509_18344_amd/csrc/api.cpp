@@ -170,10 +170,10 @@ int device_cus() {
   return cus;
 }
 
-// Bytes of the per-group sums of x the 32x32 kernel's 128-row tiles read (fp32
+// Bytes of the per-group sums of x the 32x32 kernel's 96- and 128-row tiles read (fp32
 // [K/group][M]), rounded up to 256.
 size_t xsum_bytes(const subspec::KernelChoice& c, int M, int K, int group) {
-  if (c.shape != 32 || c.rows != 128) return 0;
+  if (c.shape != 32 || c.rows <= 64) return 0;
   return (static_cast<size_t>(M) * (K / group) * sizeof(float) + 255) & ~size_t(255);
 }
 
@@ -319,7 +319,7 @@ int make_plan(int M, int N, int K, int bits, int group, int path, subspec_plan* 
     c.chunk = tu.gemv_ch ? tu.gemv_ch : c.rows <= 2 ? 2 : 4;
     c.prefetch = tu.gemv_pf;
   } else if (path == SUBSPEC_PATH_MFMA32) {
-    // 32x32x16 matrix cores (k_qmma): four row blocks of 32 (two up to M = 64), one
+    // 32x32x16 matrix cores (k_qmma): four row blocks of 32 (two up to M = 64; three below), one
     // 32-column block per wavefront, one 128-k chunk per LDS stage.  Four wavefronts where
     // neither form below applies: the ring is four chunks deep (one workgroup per CU), or
     // two (two workgroups per CU) when whole column groups of 64-k groups fill the device.
@@ -342,6 +342,10 @@ int make_plan(int M, int N, int K, int bits, int group, int path, subspec_plan* 
     c8 = c;
     c8.waves = 8;
     c8.prefetch = tu.mfma_pf ? tu.mfma_pf : 4;
+    // Up to M = 96 the half-wide ones take 96 rows: with 128, a quarter of them padding, they
+    // are slower than four wavefronts were (37888x3584 M = 65 4-bit 42.8 us against 39.3, now
+    // 35.6; 43008x5120 M = 80 2-bit 59.6 before either, 47.1).
+    if (half8 && !wide8 && M > 64 && M <= 96 && group == 128) c8.rows = 96;
     const int rem128 = (N + 127) / 128 % device_cus();
     const bool short_k = group == 64 && bits > 2 && c.rows == 128 && KB <= 4 &&
                          (KB == 1 || rem128 == 0 || 2 * rem128 > device_cus());
@@ -579,8 +583,8 @@ int make_plan(int M, int N, int K, int bits, int group, int path, subspec_plan* 
                   "GEMV path: M=%d N=%d K=%d needs splits of at most %d k, but the plan can only "
                   "split %d ways (%d column groups)", M, N, K, span, splits, col_groups);
   }
-  // Workspace: split-K completion counters, then the per-group sums of x (128-row 32x32
-  // tiles), then the splits' fp32 partial sums.
+  // Workspace: split-K completion counters, then the per-group sums of x (96- and
+  // 128-row 32x32 tiles), then the splits' fp32 partial sums.
   const size_t xsb = xsum_bytes(c, M, K, group);
   size_t ws = 0;
   if (splits > 1 || xsb)

@@ -21,7 +21,7 @@ struct QArgs {
   uint16_t* y;            // bf16 [M][N]
   float* ws;              // fp32 [splits][M][N] partial sums (splits > 1)
   unsigned* cnt;          // per column group: workgroups done (zero between launches)
-  const float* xsum;      // k_qmma, 128-row tiles: fp32 [K/group][M] per-group sums of x (k_xsum)
+  const float* xsum;      // k_qmma, 96- and 128-row tiles: fp32 [K/group][M] per-group sums of x (k_xsum)
   int M, N, K;
   int KB;                 // K / 128
   int n_tiles;            // N / 16
@@ -70,7 +70,7 @@ bool qmma_variant_exists(int waves, int teams, int mb, int nb, int pf, int bits,
 int qmma_resident_blocks(int waves, int teams, int mb, int nb, int pf, int bits, int group);
 hipError_t launch_qmma(int waves, int teams, int mb, int nb, int pf, int bits, int group, const QArgs& a,
                        int grid, int row_blocks, hipStream_t st);
-// The sums of x over every group of k that k_qmma needs on 128-row tiles: out[g][m] = sum over the
+// The sums of x over every group of k that k_qmma needs on 96- and 128-row tiles: out[g][m] = sum over the
 // group's k of x[m][k] (fp32), x bf16 [M][K].
 hipError_t launch_xsum(const uint16_t* x, int M, int K, int group, float* out, hipStream_t st);
 

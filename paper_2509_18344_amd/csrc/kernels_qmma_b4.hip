@@ -10,6 +10,7 @@ namespace subspec {
 // the ring four chunks deep; four wavefronts with the ring two chunks deep (two workgroups
 // per CU, groups of 64) or four.  Two teams of four wavefronts with two-chunk rings on
 // long-K launches.
+// Three row blocks (M = 65..96 on half-wide launches): eight wavefronts likewise.
 // Two row blocks (M = 33..64): eight wavefronts with the ring four chunks deep; two teams
 // of four on long-K launches, each with a four-chunk ring.
 // One row block: two teams of four with four-chunk rings, the rows in blocks of 32 (q|k|v
@@ -17,6 +18,7 @@ namespace subspec {
 static const MmaVariant kVariants[] = {
     SUBSPEC_QMMA(128, 4, 1, 4, 4), SUBSPEC_QMMA(64, 4, 1, 2, 4),
     SUBSPEC_QMMA(64, 4, 1, 4, 4),
+    SUBSPEC_QMMA(128, 3, 1, 4, 8),
     SUBSPEC_QMMA(128, 2, 1, 4, 8), SUBSPEC_QMMA(64, 2, 1, 4, 8),
     SUBSPEC_QMMA(128, 4, 1, 4, 8), SUBSPEC_QMMA(64, 4, 1, 4, 8),
     SUBSPEC_QMMA_TEAMS(128, 4, 2, 2), SUBSPEC_QMMA_TEAMS(64, 4, 2, 2),

@@ -15,8 +15,8 @@
 // then tot += s * acc (one FMA per output per group).  The second term for a pair of
 // groups at once: one fp32 32x32x2 MFMA with A = the two groups' sums of x and
 // B = -s*(128+z) of the two groups (a rank-2 update of the 32x32 output block).
-// The sums of x per (row, group): 64-row tiles take them from the x chunk in LDS (SumX),
-// 128-row tiles, which have no registers left for it, from a small kernel per call
+// The sums of x per (row, group): tiles of up to 64 rows take them from the x chunk in LDS
+// (SumX), taller ones, which have no registers left for it, from a small kernel per call
 // (k_xsum), copied into LDS beside the chunk.
 //
 // What bounds it: two wavefronts per SIMD must keep the matrix pipe busy through LDS
@@ -120,11 +120,12 @@ struct MmaBody {
   // which the buffer's range check covers (rows past M read zeros); the chunk's
   // position in the row is the scalar offset.
   // Who sums x over the groups: 64-row tiles the workgroup itself (SumX; a pre-pass
-  // kernel costs 5 us there), 128-row tiles, which have no registers for it, a pre-pass
+  // kernel costs 5 us there), taller ones, which have no registers for it, a pre-pass
   // (k_xsum), whose sums are copied into LDS with the chunk ([group][row], 64 per
-  // wavefront; wavefronts past the last 64 repeat them).
+  // wavefront; wavefronts past the last 64 repeat them, and what the last 64 hold past the
+  // chunk's sums is never read).
   static constexpr bool SUMS = MB <= 2;
-  static constexpr int XSW = GPC * ROWS / kWave;
+  static constexpr int XSW = (GPC * ROWS + kWave - 1) / kWave;
   static constexpr int PIECES = 2 * NB + GPC + (SUMS ? 0 : 1) + DMA;
   static constexpr int VM = 2 * NB + 2 * GPC * NB + (SUMS ? 0 : 1) + DMA;  // vector memory operations of one chunk
   static __device__ __forceinline__ void stage(u32x4_t* xb, const QBuffers& bu, const Lanes& ln, int K, int kb,
@@ -262,7 +263,8 @@ struct MmaBody {
     static constexpr int PPL = 16 / LPR;    // pieces of one lane and row
     static constexpr int RPW = kWave / LPR;  // rows of one wavefront at a time
     static constexpr int ROUNDS = ROWS / (RPW * WAVES);
-    static_assert(ROWS % (RPW * WAVES) == 0 && PPL % 2 == 0 && PPL * ROUNDS <= 10, "whole rounds, within the steps");
+    static_assert(!SUMS || (ROWS % (RPW * WAVES) == 0 && PPL % 2 == 0 && PPL * ROUNDS <= 10),
+                  "whole rounds, within the steps");
     static constexpr int LPG = LPR / GPC;  // lanes of one group
     u32x4_t v[2];
     float sum[2];
@@ -352,7 +354,7 @@ __attribute__((amdgpu_waves_per_eu(WAVES == 8 || XB <= 2 ? 2 : 1))) void k_qmma(
   static_assert(NBUF <= 8, "LDS chunk buffers");
   __shared__ u32x4_t xb0[XCH], xb1[XCH], xb2[NBUF > 2 ? XCH : 1], xb3[NBUF > 3 ? XCH : 1],
       xb4[NBUF > 4 ? XCH : 1], xb5[NBUF > 5 ? XCH : 1], xb6[NBUF > 6 ? XCH : 1], xb7[NBUF > 7 ? XCH : 1];
-  constexpr int XSC = GPC * Body::ROWS;  // sums of x of one chunk, [group][row]
+  constexpr int XSC = SUMS ? GPC * Body::ROWS : Body::XSW * kWave;  // sums of x of one chunk, [group][row]
   __shared__ float xs0[XSC], xs1[XSC], xs2[NBUF > 2 ? XSC : 1], xs3[NBUF > 3 ? XSC : 1], xs4[NBUF > 4 ? XSC : 1],
       xs5[NBUF > 5 ? XSC : 1], xs6[NBUF > 6 ? XSC : 1], xs7[NBUF > 7 ? XSC : 1];
   // Chunk buffer I, selected at compile time: separate LDS objects, so that the

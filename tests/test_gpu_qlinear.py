@@ -287,10 +287,14 @@ def test_qlinear_does_not_touch_outside_y():
     (100, 32784, 384, 4, 128),   # eight wavefronts at four row blocks, 4-bit
     (128, 55296, 640, 4, 64),
     (70, 49168, 640, 3, 64),
+    (65, 37888, 1152, 4, 128),   # 96-row tiles: one row in the third block, nine k-blocks
+    (96, 32784, 384, 2, 128),    # full, columns past N
+    (81, 32768, 3072, 3, 128),   # K in two splits
+    (80, 33040, 128, 4, 128),    # one k-block
 ])
 def test_qlinear_32x32_forms(M, N, K, bits, group):
     """32x32 launches in 32-row blocks, on 64-row tiles of half-wide launches and on
-    128-row tiles of eight wavefronts: against the oracle, and within the workspace the
+    96- and 128-row tiles of eight wavefronts: against the oracle, and within the workspace the
     plan states."""
     plan = ss.subspec_qlinear_plan(M, N, K, bits, group)
     assert plan["mfma_rows"] == 32 and plan["waves"] == 8, plan

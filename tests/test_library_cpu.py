@@ -127,10 +127,10 @@ def test_plan_choices_are_consistent():
                     assert p["splits"] > 1 and fg % 256 == 0
                     assert (p["col_groups"] - fg) * p["splits"] <= 256
                 # completion counters (16384 x 4 bytes), the per-group sums of x the
-                # 32x32 kernel reads on 128-row tiles (fp32 [K/group][M], 256-byte
+                # 32x32 kernel reads on taller tiles (fp32 [K/group][M], 256-byte
                 # aligned), then the splits' fp32 partial sums: nothing the launch does
                 # not read
-                xs = -(-M * (K // group) * 4 // 256) * 256 if p["mfma_rows"] == 32 and p["rows"] == 128 else 0
+                xs = -(-M * (K // group) * 4 // 256) * 256 if p["mfma_rows"] == 32 and p["rows"] > 64 else 0
                 part_rows = rb * p["rows"] if rb > 1 else M
                 partials = p["splits"] * part_rows * N * 4 if p["splits"] > 1 else 0
                 expect = 65536 + xs + partials if (xs or partials) else 0
@@ -159,7 +159,7 @@ def test_mfma_tile_shape_choice():
     """The automatic plan runs 32x32x16 tiles from M = 33 where 256-column groups of
     eight wavefronts (a four-chunk ring) cover at least half the 256 CUs and K is not
     split: 64 rows up to M = 64, 128 above (there, under three quarters of the CUs, groups
-    of 64 take four wavefronts and two chunks); and on a K of at least 128 blocks, two
+    of 64 take four wavefronts and two chunks and groups of 128 96 rows up to M = 96); and on a K of at least 128 blocks, two
     teams of four wavefronts per workgroup (the last tuple entry is then minus the
     wavefronts of one team; four chunks on 64 rows, two on 128).  Narrower launches run
     32-row tiles in row blocks while those stay within a workgroup per CU; everything
@@ -171,7 +171,9 @@ def test_mfma_tile_shape_choice():
     assert shape(128, 55296, 5120, 2, 64) == (32, 128, 4, 8)
     assert shape(128, 55296, 5120, 4, 128) == (32, 128, 4, 8)
     assert shape(128, 55296, 5120, 3, 64) == (32, 128, 4, 8)
-    assert shape(96, 37888, 3584, 4) == (32, 128, 4, 8)     # 7B gate|up: 148 groups of 256
+    assert shape(97, 37888, 3584, 4) == (32, 128, 4, 8)     # 7B gate|up: 148 groups of 256
+    assert shape(96, 37888, 3584, 4) == (32, 96, 4, 8)      # 96 rows up to M = 96
+    assert shape(96, 49152, 3584, 4) == (32, 128, 4, 8)     # three quarters of the CUs: 128
     assert shape(96, 37888, 3584, 4, 64) == (32, 128, 2, 4)  # groups of 64: four wavefronts
     assert shape(128, 5120, 27648) == (32, 128, 2, -4)     # 32B down: two teams of four
     assert shape(96, 3584, 18944, 4) == (32, 128, 2, -4)   # 7B down
