@@ -117,19 +117,22 @@ def _ptr(t):
     raise TypeError(f"cannot take the address of {type(t)}")
 
 
-_torch = None
+_torch = _raw_stream = _device = None
 
 
 def _stream(s):
     if s is None:
-        global _torch
+        global _torch, _raw_stream, _device
         if _torch is None:
             import torch as _torch
+            # private to torch: where a version lacks them, the public Stream object below
+            _raw_stream = getattr(_torch._C, "_cuda_getCurrentRawStream", None)
+            _device = getattr(_torch._C, "_cuda_getDevice", None)
         # The current stream's handle without a Stream object around it: a projection of
         # a few microseconds is bound by this marshalling (7.9 us per eager call of a
         # 512 x 256 projection with the object and a ctypes structure per field).
-        if _torch.cuda.is_initialized():
-            return _torch._C._cuda_getCurrentRawStream(_torch._C._cuda_getDevice())
+        if _raw_stream is not None and _device is not None and _torch.cuda.is_initialized():
+            return _raw_stream(_device())
         return _torch.cuda.current_stream().cuda_stream
     if isinstance(s, int):
         return s
@@ -224,7 +227,7 @@ def _projs(projs):
         return b"".join([_PROJ_PACK(
             _ptr(p["x"]) or 0, _ptr(p["qweight"]) or 0, _ptr(p["scales"]) or 0, _ptr(p["zeros"]) or 0,
             _ptr(p["y"]) or 0, int(p["N"]), int(p["K"])) for p in projs])
-    except struct.error:  # a value outside its C type: ctypes' own conversion
+    except (struct.error, OverflowError):  # a value outside its C type: ctypes' own conversion
         pass
     arr = (SubspecProj * len(projs))()
     for i, p in enumerate(projs):

@@ -292,6 +292,25 @@ def test_qlinear_argument_errors_need_no_gpu():
         ss.subspec_quantize(16, 4, 64, 16, 100, 16, 16, 16, stream=0)
 
 
+def test_current_stream_without_torchs_private_names(monkeypatch):
+    """The current stream comes from torch's public Stream object where the private names
+    that give its handle directly are missing."""
+    import types
+    fake = types.SimpleNamespace(
+        _C=types.SimpleNamespace(),
+        cuda=types.SimpleNamespace(is_initialized=lambda: True,
+                                   current_stream=lambda: types.SimpleNamespace(cuda_stream=0x5150)))
+    monkeypatch.setitem(sys.modules, "torch", fake)
+    monkeypatch.setattr(_binding, "_torch", None)
+    for n in ("_raw_stream", "_device"):
+        monkeypatch.setattr(_binding, n, None, raising=False)
+    assert _binding._stream(None) == 0x5150
+    # and through them where they are there
+    fake._C._cuda_getCurrentRawStream, fake._C._cuda_getDevice = lambda d: 0x1000 + d, lambda: 3
+    monkeypatch.setattr(_binding, "_torch", None)
+    assert _binding._stream(None) == 0x1003
+
+
 def test_binding_fails_loudly_without_library(monkeypatch, tmp_path):
     monkeypatch.setattr(_binding, "_lib", None)
     monkeypatch.setattr(_binding, "_HERE", str(tmp_path))
