@@ -186,15 +186,19 @@ size_t xsum_bytes(const subspec::KernelChoice& c, int M, int K, int group) {
 // 9.8 / 7.9; 12288x4096 M = 6 11.3 / 10.1; 2048x8192 M = 6 10.5 / 8.1.  Where the lines lie:
 //  - every pair of tiles reads the fragments of x from the L2 again, M * K * 2 bytes: from
 //    M = 9 that is more than the weights, and only a K of up to 36 blocks still gains
-//    (5120x5120 M = 16 9.8 / 9.8, 16384x512 M = 12 6.6 / 7.2; 256x4096, sixteen tiles, 6.2 / 6.3);
+//    (5120x5120 M = 16 9.8 / 9.8, 16384x512 M = 12 6.6 / 7.2; 256x4096, sixteen tiles, 6.2 /
+//    6.3), and from M = 10 only with one workgroup per CU (9008x1536, 282 pairs, M = 16 7.9 / 8.8,
+//    M = 12 2-bit 7.3 / 7.9; M = 9 8.1 / 7.8; 6144x1536 M = 16 7.8 / 5.9);
 //  - 16 wavefronts fill a CU: one workgroup per CU, or at least half as many again
 //    (10240x4096, 320 pairs, M = 1 9.0 / 9.2; 14000x3584, 438 pairs, 9.9 / 9.1); of eight two
 //    (22000x2048 8.5 / 8.6);
 //  - launches of more weights have enough column groups or blocks per workgroup to hide
 //    the completion (37888x3584 M = 1 14.3 / 15.9), except where one tile a workgroup fills
-//    the CUs once (K up to 160 blocks; 3584x18944 M = 1 11.9 / 10.1, M = 2 13.1 / 10.7; from
-//    M = 5, two loads of x per block, to 112: 2560x11008 3-bit M = 6 11.0 / 8.9, 4096x14336
-//    13.5 / 12.7, but 3584x18944 3-bit M = 8 14.8 / 15.2 and 2048x18944 M = 6 11.9 / 12.3); one
+//    the CUs once.  There each wavefront takes KB / 16 blocks in a row, each a load of codes
+//    and one (M <= 4), two (8) or four loads of x, so K reaches to 160 blocks (3584x18944 M = 1
+//    11.9 / 10.1, M = 2 13.1 / 10.7; M = 4 under 64 tiles to 128: 512x18944 10.6 / 11.1), to 112
+//    up to M = 6 (2560x11008 3-bit 11.0 / 8.9, 2880x14336 0.95 of the other, 2048x18944 11.9 /
+//    12.3) and to 96 up to M = 8 (2880x12288 0.9, 2880x14336 11.3 / 12.4, 256x8320 1.09); one
 //    tile against two at M = 1: 3584x3584 4.2 / 4.4, 1024x4096 3.9 / 4.3;
 //  - a K of one or two blocks is not split anyway (512x256 M = 8 2.9 / 2.8, M = 16 2.9 / 3.3;
 //    29200x256 M = 1 4.1 / 6.3).
@@ -217,11 +221,11 @@ bool stream_choice(int M, int N, int K, int* nt, int* ks) {
   *ks = KB < 24 ? 8 : 16;
   if (KB >= 24 && tiles <= device_cus() && (M <= 4 || (M <= 8 && KB > 64))) {
     *nt = 1;
-    return KB <= (M <= 4 ? 160 : 112);
+    return KB <= (M <= 2 || (M <= 4 && tiles >= 64) ? 160 : M <= 4 ? 128 : M <= 6 ? 112 : 96) && (M <= 6 || tiles >= 32);
   }
   *nt = 2;
   if (KB > 64 || mweights > 48) return false;
-  if (M > 8) return KB <= 36 && (KB < 24 || tiles >= 64) && mweights <= 18;
+  if (M > 8) return KB <= 36 && (KB < 24 || tiles >= 64) && mweights <= 18 && (M == 9 || pairs <= device_cus());
   return KB < 24 ? pairs <= 2 * device_cus() : pairs <= device_cus() || 2 * pairs >= 3 * device_cus();
 }
 
@@ -460,7 +464,7 @@ int make_plan(int M, int N, int K, int bits, int group, int path, subspec_plan* 
   // against 14.3 and 13.5 against 12.6.  Not from M = 65 where they exceed a workgroup per
   // CU (14336x4096 4-bit 30.0 against 31.4), and up to M = 64 not for a K under 36 blocks
   // (4608x3584 11.1 against 11.6) or few columns (2048x8192 11.9 against 12.1); not for a
-  // single k-block (2304x128, M = 128 4.5 against 3.7); and not from M = 97 where the
+  // single k-block (2304x128, M = 128 4.5 against 3.7); and not from M = 65 where the
   // unsplit launch leaves CUs without work that three splits of the other would use and K
   // is long enough to show it: 48 blocks, or 30 where the column groups are no multiple of
   // eight, so that the row blocks of a group land on different XCDs and each L2 reads its
@@ -470,7 +474,7 @@ int make_plan(int M, int N, int K, int bits, int group, int path, subspec_plan* 
   // of rows reads the weights again and every column group x, 128 MB at 7168x5120.
   if (any_shape && c.shape == 16 && c.row_blocks == 2 && !tu.mma_shape && !tu.row_split && tu.rb_splits >= 0) {
     const int units32 = (N + 127) / 128 * ((M + 31) / 32);
-    const bool idle = M > 96 && KB >= ((N + 127) / 128 % 8 ? 30 : 48) && units32 * 2 > device_cus() &&
+    const bool idle = KB >= ((N + 127) / 128 % 8 ? 30 : 48) && units32 * 2 > device_cus() &&
                       groups_of(c) * c.row_blocks * 3 <= 2 * device_cus();
     if (M > 64 ? units32 <= device_cus() && KB > 1 && !idle : KB >= 36 && units32 * 4 >= device_cus()) {
       c = subspec::KernelChoice{};

@@ -145,6 +145,12 @@ def test_plan_choices_are_consistent():
     for M in (1, 2, 8):
         p = ss.subspec_qlinear_plan(M, 512, 256, 4, 64)
         assert (p["path"], p["mfma_rows"], p["teams"], p["workspace_bytes"]) == (ss.SUBSPEC_PATH_MFMA, 16, 4, 0)
+    # the small-batch lines: blocks a wavefront takes in a row, workgroups per CU
+    for M, N, K, small in [(2, 3584, 20480, True), (2, 3584, 20608, False), (4, 512, 16384, True), (4, 512, 16512, False),
+                           (4, 1024, 20480, True), (6, 2880, 14336, True), (8, 2880, 12288, True), (8, 2880, 12416, False),
+                           (8, 256, 9216, False), (9, 9008, 1536, True), (10, 9008, 1536, False), (16, 8192, 1536, True),
+                           (16, 8208, 1536, False)]:
+        assert (ss.subspec_qlinear_plan(M, N, K, 4, 128)["teams"] > 1) == small, (M, N, K)
     p = ss.subspec_qlinear_plan(6, 4608, 3584, 4, 128)
     assert (p["mfma_rows"], p["rows"], p["tiles_per_wave"], p["teams"], p["grid"]) == (16, 8, 2, 16, 144)
     # launches that need no scratch ask for none
