@@ -1,5 +1,5 @@
 // The substitute-layer linear y = x * dequant(q, s, z)^T (SubSpec Sec. 4.1) for draft
-// batches of 17 to 128 tree tokens, on 32x32x16 bf16 matrix cores (k_qmma).
+// batches of 33 to 128 tree tokens (fewer on request), on 32x32x16 bf16 matrix cores (k_qmma).
 //
 // Roles of the operands: the activations are the A operand (32 rows of x per row
 // block, read from LDS), the unpacked codes the B operand (32 columns per column
@@ -25,7 +25,8 @@
 // across the barrier; a group's scale FMAs run between the next group's first MFMAs; and
 // a chunk's loads are spread over its steps.  us per call, before (burst of loads and
 // block of FMAs per chunk, the next chunk's first A read after the barrier, gathered x
-// sums) and after: 55296x5120 M = 128 3-bit 89.0 / 68.5, 2-bit g64 93.3 / 75.8, 4-bit
+// sums) and after, weights in the last-level cache in part (a stack that rotates them takes
+// 75.8 at M = 128 3-bit): 55296x5120 M = 128 3-bit 89.0 / 68.5, 2-bit g64 93.3 / 75.8, 4-bit
 // 99.5 / 71.4, M = 64 3-bit 47.9 / 43.3; 5120x27648 3-bit M = 128 58.8 / 51.8, M = 64
 // 37.8 / 31.6; 37888x3584 4-bit M = 128 50.0 / 45.6, M = 64 34.5 / 29.5.
 //
@@ -312,8 +313,9 @@ constexpr int wait_vm_lds(int vm) { return (vm & 15) | (7 << 4) | ((vm >> 4) << 
 // order, so waiting until only the VM operations issued after those copies are
 // outstanding is exact; a fenced __syncthreads() would drain all of them, and leaving the
 // wait to the compiler (its own tracking of copies into LDS) missed copies whose
-// instructions are spread over the steps.  The empty assembly statements keep the
-// compiler from moving LDS accesses across the barrier.
+// instructions are spread over the steps.  (tests/test_compiled_waits.py counts the loads
+// in the built library.)  The empty assembly statements keep the compiler from moving LDS
+// accesses across the barrier.
 template <int VM>
 __device__ __forceinline__ void chunk_barrier() {
   static_assert(VM < 64, "vmcnt has six bits");
