@@ -58,7 +58,7 @@ FAMILIES = {
              "kernels": ("k_tree_expand",)},
     "attn": {"json": os.path.join(ROOT, "profiles", "traffic_attn.json"),
              "sources": ("kernels_attn.hip", "kernels_attn.h", "device_common.h", "kernels.h"),
-             "kernels": ("k_attn_partial", "k_attn_combine")},
+             "kernels": ("k_attn_partial", "k_attn_stream", "k_attn_combine")},
 }
 WORKLOAD_FAMILY = {"tree_expand": "tree", "tree_attn": "attn"}
 
@@ -1271,7 +1271,7 @@ def run_hqq(args, torch, ss):
         "roofline": {"bound": "hbm", "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(gbs / HBM_PEAK_GBS, 4), "traffic": None,
                      "kernel": "k_quantize_hqq<64> (7 launches per step)", "alg_bytes_per_step": nbytes,
-                     "note": "float64 arithmetic (a power per weight and round) bounds it, not HBM"},
+                     "note": "float64 arithmetic bounds it, not HBM"},
     }
     if not args.no_cpu_baseline:
         out["cpu_baseline"] = hqq_cpu_baseline()
