@@ -297,14 +297,19 @@ int make_plan(int M, int N, int K, int bits, int group, int path, subspec_plan* 
     // 48, 53.9 against 59.0 at 64; where 256-column groups cover only half the CUs from
     // mma8_half_min_m on (7B gate|up, 148 groups: 29.1 against 30.9 us at M = 37, 3-bit
     // 28.3 against 30.8 at 44, 4-bit g64 32.3 against 35.7 at 40; under M = 48 from three
-    // k-blocks on: 44032x256 3-bit 6.8 against 6.4 at 47).  Long-K launches take
+    // k-blocks on: 44032x256 3-bit 6.8 against 6.4 at 47, 32768x256 6.3 against 5.4 at 41; and
+    // at two where the other would split its last groups, up to a quarter more of 128 columns
+    // than there are CUs: 37456x256 6.9 against 9.8 at 40).  Long-K launches take
     // 64-row tiles on two teams of four wavefronts from teams64_min_m (below): 32B down
     // 34.5 against 39.3 us at M = 48 and 39.6 against 41.5 at 64, 2-bit g64 36.0 against
     // 43.9 and 40.2 against 46.1; the 7B down about even (25.7 against 25.2 at 48, 26.8
     // against 27.5 at 64); at M = 32, with half of each tile empty, 30.7 against 27.3.
     // (These with two-chunk rings; four chunks are faster, below.)
-    const bool tiles64 = tu.mma8_min_m > 0 && M >= tu.mma8_min_m && (half8 && !wide8 ? M >= tu.mma8_half_min_m && (M >= 48 || KB >= 3) : wide8) &&
-                         !long_k;
+    const int groups128 = (N + 127) / 128;
+    const bool tail = groups128 > device_cus() && 4 * groups128 <= 5 * device_cus();
+    const bool half_tiles = M >= tu.mma8_half_min_m && (M >= 48 || KB >= 3 || (KB == 2 && tail));
+    const bool tiles64 =
+        tu.mma8_min_m > 0 && M >= tu.mma8_min_m && (half8 && !wide8 ? half_tiles : wide8) && !long_k;
     const bool teams64 = tu.teams64_min_m > 0 && long_k && M >= tu.teams64_min_m && M <= 64;
     const bool use32 =
         tu.mma_shape ? tu.mma_shape == 32 : (M > tu.mma16_max_m && (wide || long_k)) || tiles64 || teams64;

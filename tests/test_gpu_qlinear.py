@@ -325,7 +325,8 @@ def test_qlinear_32x32_forms(M, N, K, bits, group):
     (65, 1040, 128, 3, 64, 64, 4),      # a single k-block
     (128, 55296, 512, 4, 64, 128, 4),   # short K: four wavefronts, two-chunk ring
     (65, 49168, 128, 3, 64, 128, 4),
-    (47, 32784, 256, 4, 128, 64, 4),    # half-wide, under three blocks
+    (47, 40976, 256, 4, 128, 64, 4),    # half-wide, two blocks, no split tail
+    (47, 32784, 256, 4, 128, 64, 8),    # and where the other would split one
 ])
 def test_qlinear_short_and_idle_launches(M, N, K, bits, group, rows, waves):
     """Launches the 32-row and eight-wavefront forms are not taken for, on either side of

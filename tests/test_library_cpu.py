@@ -193,6 +193,8 @@ def test_mfma_tile_shape_choice():
     assert shape(33, 37888, 3584, 4) == (32, 64, 4, 8)
     assert shape(32, 37888, 3584, 4)[0] == 16
     assert shape(47, 44032, 256)[0] == 16 and shape(48, 44032, 256) == (32, 64, 4, 8)  # short K
+    for N, rows in ((32768, 16), (32784, 32), (40960, 32), (40976, 16)):  # a tail of up to 64 column groups
+        assert shape(47, N, 256)[0] == rows and shape(33, N, 128)[0] == 16, N
     assert shape(128, 55296, 512, 4, 64) == (32, 128, 2, 4)   # short K, no split tail: four wavefronts
     assert shape(128, 49152, 512, 4, 64) == (32, 128, 4, 8)
     assert shape(128, 49152, 128, 4, 64) == (32, 128, 2, 4)
