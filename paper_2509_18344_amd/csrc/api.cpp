@@ -196,10 +196,15 @@ size_t xsum_bytes(const subspec::KernelChoice& c, int M, int K, int group) {
 //    the completion (37888x3584 M = 1 14.3 / 15.9), except where one tile a workgroup fills
 //    the CUs once.  There each wavefront takes KB / 16 blocks in a row, each a load of codes
 //    and one (M <= 4), two (8) or four loads of x, so K reaches to 160 blocks (3584x18944 M = 1
-//    11.9 / 10.1, M = 2 13.1 / 10.7; M = 4 under 64 tiles to 128: 512x18944 10.6 / 11.1), to 112
-//    up to M = 6 (2560x11008 3-bit 11.0 / 8.9, 2880x14336 0.95 of the other, 2048x18944 11.9 /
-//    12.3) and to 96 up to M = 8 (2880x12288 0.9, 2880x14336 11.3 / 12.4, 256x8320 1.09); one
-//    tile against two at M = 1: 3584x3584 4.2 / 4.4, 1024x4096 3.9 / 4.3;
+//    11.9 / 10.1, M = 2 13.1 / 10.7, 768x19712 M = 4 12.6 / 11.0), to 112 up to M = 6 (2560x11008
+//    3-bit 11.0 / 8.9, 2880x14336 0.95 of the other, 2048x18944 11.9 / 12.3) and to 108 at M = 7
+//    and 104 at 8 (2880x12288 0.9, 768x13312 even, 2048x13824 10.8 / 11.6; 464x12416 12.9 /
+//    9.1, and under 40 tiles to 112 and 110: 512x13824 13.6 / 11.4).  With few tiles the
+//    splits of the other fill one round of CUs and its partial sums are small: M = 4 and 24 to
+//    32 tiles from 145 blocks on (448x20480 0.87 of this, 512x18944 0.95), M = 3 and 4 under 8
+//    too (64x19200 9.8 / 11.2, 112x17152 10.0 / 8.2), M = 7 under 12 (128x8320 0.93), M = 8 under
+//    16 (192x10240 0.9, 192x12288 even) and with 16 to 19 under 72 blocks (256x8320 0.9).
+//    One tile against two at M = 1: 3584x3584 4.2 / 4.4, 1024x4096 3.9 / 4.3;
 //  - a K of one or two blocks is not split anyway (512x256 M = 8 2.9 / 2.8, M = 16 2.9 / 3.3;
 //    29200x256 M = 1 4.1 / 6.3).
 bool stream_choice(int M, int N, int K, int* nt, int* ks) {
@@ -221,7 +226,11 @@ bool stream_choice(int M, int N, int K, int* nt, int* ks) {
   *ks = KB < 24 ? 8 : 16;
   if (KB >= 24 && tiles <= device_cus() && (M <= 4 || (M <= 8 && KB > 64))) {
     *nt = 1;
-    return KB <= (M <= 2 || (M <= 4 && tiles >= 64) ? 160 : M <= 4 ? 128 : M <= 6 ? 112 : 96) && (M <= 6 || tiles >= 32);
+    if (M <= 2) return KB <= 160;
+    if (M <= 4) return KB <= (tiles < 8 || (M == 4 && tiles >= 24 && tiles <= 32) ? 144 : 160);
+    if (M <= 6) return KB <= 112;
+    if (M == 7) return tiles >= 12 && KB <= (tiles < 40 ? 112 : 108);
+    return tiles >= (KB < 72 ? 20 : 16) && KB <= (tiles < 40 ? 110 : 104);
   }
   *nt = 2;
   if (KB > 64 || mweights > 48) return false;

@@ -352,6 +352,7 @@ def test_qlinear_short_and_idle_launches(M, N, K, bits, group, rows, waves):
     (16, 1024, 4480, 2, 64), (7, 528, 8192, 3, 64), (8, 7168, 5120, 2, 128),
     (4, 3600, 3200, 2, 128), (1, 64, 18944, 4, 64),   # one tile, sixteen wavefronts; up to 4 rows
     (5, 272, 8320, 3, 128), (8, 1040, 12288, 4, 64),  # and up to 8
+    (7, 496, 14336, 2, 64), (8, 496, 14080, 4, 128),  # the longest K at 7 and 8
 ])
 def test_qlinear_small_batches_over_whole_k(M, N, K, bits, group):
     """Small launches that would split K across workgroups run on workgroups whose

@@ -146,9 +146,14 @@ def test_plan_choices_are_consistent():
         p = ss.subspec_qlinear_plan(M, 512, 256, 4, 64)
         assert (p["path"], p["mfma_rows"], p["teams"], p["workspace_bytes"]) == (ss.SUBSPEC_PATH_MFMA, 16, 4, 0)
     # the small-batch lines: blocks a wavefront takes in a row, workgroups per CU
-    for M, N, K, small in [(2, 3584, 20480, True), (2, 3584, 20608, False), (4, 512, 16384, True), (4, 512, 16512, False),
-                           (4, 1024, 20480, True), (6, 2880, 14336, True), (8, 2880, 12288, True), (8, 2880, 12416, False),
-                           (8, 256, 9216, False), (9, 9008, 1536, True), (10, 9008, 1536, False), (16, 8192, 1536, True),
+    for M, N, K, small in [(2, 3584, 20480, True), (2, 3584, 20608, False), (3, 512, 20480, True), (4, 512, 18432, True),
+                           (4, 512, 18560, False), (4, 528, 20480, True), (4, 112, 18432, True),
+                           (4, 112, 18560, False), (4, 128, 20480, True),
+                           (4, 1024, 20480, True), (6, 2880, 14336, True), (7, 768, 13824, True), (7, 768, 13952, False),
+                           (7, 464, 14336, True), (7, 176, 9216, False), (7, 192, 9216, True), (8, 2880, 12288, True),
+                           (8, 2880, 13312, True), (8, 2880, 13440, False), (8, 464, 13824, True), (8, 464, 14208, False),
+                           (8, 256, 9088, False), (8, 256, 9216, True), (8, 240, 9216, False), (8, 320, 9088, True),
+                           (9, 9008, 1536, True), (10, 9008, 1536, False), (16, 8192, 1536, True),
                            (16, 8208, 1536, False)]:
         assert (ss.subspec_qlinear_plan(M, N, K, 4, 128)["teams"] > 1) == small, (M, N, K)
     p = ss.subspec_qlinear_plan(6, 4608, 3584, 4, 128)
