@@ -480,15 +480,17 @@ int make_plan(int M, int N, int K, int bits, int group, int path, subspec_plan* 
   // (4608x3584 11.1 against 11.6) or few columns (2048x8192 11.9 against 12.1); not for a
   // single k-block (2304x128, M = 128 4.5 against 3.7); and not from M = 65 where the
   // unsplit launch leaves CUs without work that three splits of the other would use and K
-  // is long enough to show it: 48 blocks, or 30 where the column groups are no multiple of
-  // eight, so that the row blocks of a group land on different XCDs and each L2 reads its
-  // weights (4-bit, M = 97: 5120 columns, 160 workgroups, K = 14336 42.7 us against 38.7,
-  // 6016 0.99 of the other, 5120 0.91; 5376 columns, 168, 6016 24.0 against 21.2, 4736 20.0
-  // against 18.7, 3584 even; 6144 columns, two splits for the other, 0.84).  What bounds them is the L2: every block
+  // is long enough to show it.  With groups of 128, whose scales the other applies half as
+  // often, past 40 blocks (M = 97 to 128, 3-bit at 40 0.96 of the other's time, at 42 to 50
+  // 1.03, 4-bit at 73 1.17; 5120x14336 4-bit M = 97 42.7 us against 38.7), with groups of 64
+  // past 64 (at 56 0.96 to 1.03, at 72 0.98 to 1.06); where the column groups are a multiple
+  // of eight, so that the row blocks of a group share an XCD's L2, from 72 blocks (5120 columns,
+  // M = 128: 64 0.94, 80 1.02, 126 1.09) and not at all (64 0.90, 126 0.98).  What bounds them is the L2: every block
   // of rows reads the weights again and every column group x, 128 MB at 7168x5120.
   if (any_shape && c.shape == 16 && c.row_blocks == 2 && !tu.mma_shape && !tu.row_split && tu.rb_splits >= 0) {
     const int units32 = (N + 127) / 128 * ((M + 31) / 32);
-    const bool idle = KB >= ((N + 127) / 128 % 8 ? 30 : 48) && units32 * 2 > device_cus() &&
+    const bool xcd = (N + 127) / 128 % 8 == 0;
+    const bool idle = KB > (group == 128 ? (xcd ? 71 : 40) : (xcd ? 127 : 64)) && units32 * 2 > device_cus() &&
                       groups_of(c) * c.row_blocks * 3 <= 2 * device_cus();
     if (M > 64 ? units32 <= device_cus() && KB > 1 && !idle : KB >= 36 && units32 * 4 >= device_cus()) {
       c = subspec::KernelChoice{};

@@ -228,8 +228,10 @@ def test_mfma_tile_shape_choice():
     # a single k-block, and a K long enough to show the CUs left without work, keep two
     # 16x16x32 blocks
     assert blocks(128, 4608, 128, 4) == (2, 64) and blocks(128, 4608, 256, 4) == (4, 32)
-    assert blocks(128, 5120, 6144) == (2, 64) and blocks(128, 5120, 6016) == (4, 32)
-    assert blocks(97, 5376, 3840) == (2, 64) and blocks(97, 5376, 3712) == (4, 32)
+    assert blocks(128, 5120, 9216) == (2, 64) and blocks(128, 5120, 9088) == (4, 32)
+    assert blocks(97, 5376, 5248) == (2, 64) and blocks(97, 5376, 5120) == (4, 32)
+    assert blocks(128, 5120, 16256, 2, 64) == (4, 32)
+    assert blocks(97, 5376, 8320, 2, 64) == (2, 64) and blocks(97, 5376, 8192, 2, 64) == (4, 32)
     assert blocks(96, 5120, 6144) == (3, 32) and blocks(128, 6144, 6144) == (4, 32)
     assert blocks(32, 7168, 5120) == (1, 32)
     assert blocks(64, 5120, 27648) == (1, 64)             # long K
