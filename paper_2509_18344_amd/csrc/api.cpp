@@ -572,13 +572,15 @@ int make_plan(int M, int N, int K, int bits, int group, int path, subspec_plan* 
   // three, 176 run two).  Instead the first base * CUs groups run whole and the last
   // rem are split CUs / rem ways, so no CU gets more than base groups plus one part of
   // a split one.  (A GEMV workgroup that runs a whole group stages all of K.)  Not on
-  // 128-row groups of eight wavefronts under eight blocks, where a second round costs less
-  // than the completion (80000 columns 4-bit, M = 128: K = 512 27.1 us unsplit against 38.5;
-  // 2048 about even, 3584 118 against 107; K = 1024, M = 65 even).
+  // 128-row groups of eight wavefronts of few blocks, where a second round costs less than the
+  // completion, whose partial sums grow with M: up to 10 blocks at M = 65, 16 at 128 (10 to 64
+  // groups left over, split against unsplit: M = 66 8 blocks 1.02 to 1.09, 12 0.92 to 1.05;
+  // M = 128 12 1.07 to 1.21, 16 0.96 to 1.17, 20 0.90 to 1.13; 69792x1280 4-bit M = 97 49.3 us
+  // against 41.4); at 2 bits under eight blocks.
   int full_groups = 0;
   const int cus = device_cus();
   if (splits == 1 && tu.tail && !tu.splits && c.row_blocks == 1 && col_groups <= subspec::kSplitCounters &&
-      !(wide_groups && c.rows == 128 && KB < 8) &&
+      !(wide_groups && c.rows == 128 && (bits > 2 ? 10 * KB < M + 36 : KB < 8)) &&
       (c.path != 1 || K <= subspec::gemv_max_kspan(c.rows, c.waves, group, cols_per_group))) {
     const int base = col_groups / cus, rem = col_groups % cus;
     const int ts = fit_cap(fit_offsets(std::min(rem ? cus / rem : 0, chunks)));

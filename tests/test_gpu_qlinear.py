@@ -323,6 +323,7 @@ def test_qlinear_32x32_forms(M, N, K, bits, group):
     (97, 5376, 5248, 4, 128, 64, 4),    # CUs left without work by unsplit 32-row tiles
     (128, 4240, 8320, 2, 64, 64, 4),
     (128, 4240, 6144, 2, 64, 32, 8),    # and under that line
+    (97, 66064, 1280, 4, 128, 128, 8),  # a tail left whole
     (65, 1040, 128, 3, 64, 64, 4),      # a single k-block
     (128, 55296, 512, 4, 64, 128, 4),   # short K: four wavefronts, two-chunk ring
     (65, 49168, 128, 3, 64, 128, 4),

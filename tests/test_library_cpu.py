@@ -232,6 +232,9 @@ def test_mfma_tile_shape_choice():
     assert blocks(97, 5376, 5248) == (2, 64) and blocks(97, 5376, 5120) == (4, 32)
     assert blocks(128, 5120, 16256, 2, 64) == (4, 32)
     assert blocks(97, 5376, 8320, 2, 64) == (2, 64) and blocks(97, 5376, 8192, 2, 64) == (4, 32)
+    # the tail of 256-column groups is split where K is long for the rows
+    for M, K, full in [(128, 2048, 0), (128, 2176, 256), (66, 1280, 0), (66, 1408, 256)]:
+        assert ss.subspec_qlinear_plan(M, 69792, K, 4, 128)["full_groups"] == full, (M, K)
     assert blocks(96, 5120, 6144) == (3, 32) and blocks(128, 6144, 6144) == (4, 32)
     assert blocks(32, 7168, 5120) == (1, 32)
     assert blocks(64, 5120, 27648) == (1, 64)             # long K
